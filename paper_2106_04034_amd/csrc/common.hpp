@@ -225,6 +225,13 @@ hipError_t launch_fitness(const RunDev* d_runs, const Params& p, bool init, hipS
 hipError_t launch_target_sums(const RunDev* d_runs, const Params& p, hipStream_t s);
 hipError_t launch_survive(const RunDev* d_runs, const Params& p, int32_t total_blocks, int mode,
                           hipStream_t s);
+// Read-back into contiguous arrays (device memory or mapped host memory).
+hipError_t launch_fetch_semantics(int32_t precision, const RunDev& R, const void* buf, int64_t rows, int64_t row0,
+                                  int64_t case0, int64_t n_cases, int64_t e0, int64_t count, const double* ls,
+                                  double* out, hipStream_t s);
+hipError_t launch_fetch_stats(const RunDev* d_runs, int32_t run0, int32_t gen0, int32_t n, int64_t e0, int64_t count,
+                              gsgp_gen_stats* out, hipStream_t s);
+hipError_t launch_fetch_pair(const double* a, const double* b, int32_t n, double* out, hipStream_t s);
 // Reconstruction helpers.
 hipError_t launch_transpose(const double* X, int64_t n, int32_t l, double* Xfm, int64_t ld,
                             hipStream_t s);

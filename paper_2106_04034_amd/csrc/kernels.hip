@@ -1005,15 +1005,92 @@ __global__ __launch_bounds__(256) void k_replay_nodes(const ReplayNode* __restri
   next[(int64_t)nd.out * ld + c] = o;
 }
 
+// ---------------------------------------------------------------------------
+// Read-back.  A row of a chunk-tiled buffer lies in one 2 KiB piece per chunk,
+// so copying it from the host took a copy call per chunk (about 12 us each:
+// 3.1 ms for one row of 125,000 cases, 30 ms for 1,250,000).  These kernels
+// put what a getter returns into one contiguous array in its final form.
+
+// Elements [e0, e0 + count) of the rows x cases array (row-major, n_cases a
+// row) of semantics row0.., case0.. (train cases first, then test cases), as
+// FP64; with `ls` (the generation's scaling table, [m][2]) as
+// alpha + beta * stored value.  One thread an element: consecutive threads
+// read consecutive stored values.
+template <typename T>
+__global__ __launch_bounds__(256) void k_fetch_semantics(const T* __restrict__ buf, int64_t rows, int64_t tr_pad,
+                                                         int64_t te_pad, int32_t nch_tr, int64_t n_train,
+                                                         int64_t row0, int64_t case0, int64_t n_cases, int64_t e0,
+                                                         int64_t count, const double* __restrict__ ls,
+                                                         double* __restrict__ out) {
+  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= count) return;
+  const int64_t e = e0 + q;
+  const int64_t i = row0 + e / n_cases;
+  const int64_t c = case0 + e % n_cases;
+  const int64_t col = c < n_train ? c : tr_pad + (c - n_train);
+  double v = (double)buf[tiled_index(tr_pad, te_pad, nch_tr, chunk_cases(sizeof(T)), rows, i, col)];
+  if (ls) {
+    const double a = ls[2 * i], b = ls[2 * i + 1];
+    if (a != 0.0 || b != 1.0) v = a + b * v;
+  }
+  out[q] = v;
+}
+
+// Entries [e0, e0 + count) of the runs x n array of summaries gen0 .. of
+// every run from run0 on, as 16-byte halves.
+__global__ __launch_bounds__(256) void k_fetch_stats(const RunDev* __restrict__ runs, int32_t run0, int32_t gen0,
+                                                     int32_t n, int64_t e0, int64_t count, d2* __restrict__ out) {
+  static_assert(sizeof(gsgp_gen_stats) == 2 * sizeof(d2), "a summary is two 16-byte halves");
+  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= 2 * count) return;
+  const int64_t e = e0 + (q >> 1);
+  const gsgp_gen_stats* st = runs[run0 + e / n].stats + gen0 + e % n;
+  out[q] = ((const d2*)st)[q & 1];
+}
+
+// Two arrays of n values one after the other.
+__global__ __launch_bounds__(256) void k_fetch_pair(const double* __restrict__ a, const double* __restrict__ b,
+                                                    int32_t n, double* __restrict__ out) {
+  const int32_t q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= n) return;
+  out[q] = a[q];
+  out[n + q] = b[q];
+}
+
 // Writes one state word of every run (generation counter, replay flags...).
 __global__ void k_set_state(const RunDev* __restrict__ runs, int32_t n_runs, int32_t word, int32_t value) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r < n_runs) runs[r].state[word] = value;
 }
 
-
-
 }  // namespace
+
+hipError_t launch_fetch_semantics(int32_t precision, const RunDev& R, const void* buf, int64_t rows, int64_t row0,
+                                  int64_t case0, int64_t n_cases, int64_t e0, int64_t count, const double* ls,
+                                  double* out, hipStream_t s) {
+  if (count <= 0) return hipSuccess;
+  const dim3 grid(blocks_for(count, 256)), block(256);
+  if (precision == GSGP_FP64)
+    hipLaunchKernelGGL(k_fetch_semantics<double>, grid, block, 0, s, (const double*)buf, rows, R.tr_pad, R.te_pad,
+                       R.nch_tr, R.n_train, row0, case0, n_cases, e0, count, ls, out);
+  else
+    hipLaunchKernelGGL(k_fetch_semantics<float>, grid, block, 0, s, (const float*)buf, rows, R.tr_pad, R.te_pad,
+                       R.nch_tr, R.n_train, row0, case0, n_cases, e0, count, ls, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_fetch_stats(const RunDev* d_runs, int32_t run0, int32_t gen0, int32_t n, int64_t e0, int64_t count,
+                              gsgp_gen_stats* out, hipStream_t s) {
+  if (count <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_fetch_stats, dim3(blocks_for(2 * count, 256)), dim3(256), 0, s, d_runs, run0, gen0, n, e0,
+                     count, (d2*)out);
+  return hipGetLastError();
+}
+
+hipError_t launch_fetch_pair(const double* a, const double* b, int32_t n, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_fetch_pair, dim3(blocks_for(n, 256)), dim3(256), 0, s, a, b, n, out);
+  return hipGetLastError();
+}
 
 hipError_t launch_set_state(const RunDev* d_runs, int32_t n_runs, int32_t word, int32_t value,
                             hipStream_t s) {

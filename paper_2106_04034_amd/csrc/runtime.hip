@@ -63,6 +63,10 @@ gsgp_status fail(gsgp_status s, const char* fmt, ...) {
   return s;
 }
 
+// Mapped host memory of a handle, which getters read small results through
+// (larger ones are copied from device memory).
+constexpr size_t kPinnedBytes = (size_t)256 << 10;
+
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v, size_t a = kAlign) { return (v + a - 1) / a * a; }
 inline int64_t pad_to(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
@@ -236,7 +240,8 @@ struct gsgp_handle {
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph_k = nullptr;     // kGraphGens generations back to back
   hipGraphExec_t exec_k = nullptr;
-  int32_t* pinned = nullptr;  // state read-back, [n_runs][kStWords]
+  int32_t* pinned = nullptr;  // read-back in mapped host memory: state words [n_runs][kStWords], or what a getter returns
+  size_t pinned_bytes = 0;
   int device = 0;
 };
 
@@ -252,6 +257,22 @@ gsgp_status hip_fail(gsgp_handle* h, hipError_t e, const char* what) {
     hipError_t e_ = (call);                              \
     if (e_ != hipSuccess) return hip_fail(h, e_, #call); \
   } while (0)
+
+// The handle's device, current for as long as this lives (getters may be
+// called with another device current, and a NULL stream belongs to the
+// current one).
+struct OnDevice {
+  int before = -1;
+  explicit OnDevice(const gsgp_handle* h) {
+    int d = h->device;
+    if (hipGetDevice(&d) == hipSuccess && d != h->device && hipSetDevice(h->device) == hipSuccess) before = d;
+  }
+  ~OnDevice() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+  OnDevice(const OnDevice&) = delete;
+  OnDevice& operator=(const OnDevice&) = delete;
+};
 
 gsgp_status usable(gsgp_handle* h) {
   if (!h) return fail(GSGP_ERR_ARG, "handle is NULL");
@@ -387,11 +408,17 @@ gsgp_status run_generations(gsgp_handle* h, int32_t n_gens) {
   return GSGP_OK;
 }
 
-gsgp_status copy_stats(gsgp_handle* h, int32_t gen0, int32_t n, gsgp_gen_stats* out, int32_t stride) {
-  HIPCHK(h, hipStreamSynchronize(h->stream));
-  for (int32_t r = 0; r < h->n_runs; ++r)
-    HIPCHK(h, hipMemcpy(out + (size_t)r * stride, h->runs_h[r].stats + gen0, sizeof(gsgp_gen_stats) * n,
-                        hipMemcpyDeviceToHost));
+// Summaries gen0 .. gen0 + n - 1 of n_runs runs from run0 on, [n_runs][n]:
+// gathered by one kernel into mapped host memory, in pieces that fit there.
+gsgp_status copy_stats(gsgp_handle* h, int32_t run0, int32_t n_runs, int32_t gen0, int32_t n, gsgp_gen_stats* out) {
+  const OnDevice here(h);
+  const int64_t total = (int64_t)n_runs * n, most = (int64_t)(h->pinned_bytes / sizeof(gsgp_gen_stats));
+  for (int64_t e = 0; e < total; e += most) {
+    const int64_t count = std::min(most, total - e);
+    HIPCHK(h, launch_fetch_stats(h->runs_d, run0, gen0, n, e, count, (gsgp_gen_stats*)h->pinned, h->stream));
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    memcpy(out + e, h->pinned, sizeof(gsgp_gen_stats) * count);
+  }
   return GSGP_OK;
 }
 
@@ -403,43 +430,35 @@ gsgp_status check_run(gsgp_handle* h, int32_t run) {
   return GSGP_OK;
 }
 
-// Local search: rows row0 .. row0 + n_rows - 1 of the current population
-// are stored unscaled; their semantics are alpha + beta * S with the current
-// generation's scaling (FP64, the same operations the variation kernel
-// applies when it reads a parent).  out holds n_rows rows of `cols` values.
-gsgp_status apply_scaling(gsgp_handle* h, int32_t run, int32_t row0, int32_t n_rows, int64_t cols, double* out) {
-  if (!(h->cfg.flags & GSGP_FLAG_LOCAL_SEARCH)) return GSGP_OK;
-  std::vector<double> ab((size_t)2 * n_rows);
-  const double* table = h->runs_h[run].ls + ((int64_t)h->gen * h->cfg.pop_size + row0) * 2;
-  HIPCHK(h, hipMemcpy(ab.data(), table, sizeof(double) * ab.size(), hipMemcpyDeviceToHost));
-  for (int32_t i = 0; i < n_rows; ++i) {
-    const double a = ab[2 * i], b = ab[2 * i + 1];
-    if (a == 0.0 && b == 1.0) continue;
-    double* row = out + (int64_t)i * cols;
-    for (int64_t c = 0; c < cols; ++c) row[c] = a + b * row[c];
+// Rows row0 .. row0 + n_rows - 1, cases case0 .. case0 + n_cases - 1 of the
+// population (which 0) or the pool, as FP64 rows in h_out.  Local search
+// keeps the population unscaled: its semantics are alpha + beta * S with the
+// current generation's scaling, which the gather applies.
+// The gather's output goes to the mapped host memory when it fits there, and
+// else, in pieces, to the population buffer that holds no generation: between
+// calls only S[gen & 1] is live, and every generation writes all of the
+// other one before it reads it.
+gsgp_status fetch_semantics(gsgp_handle* h, int32_t run, int32_t which, int64_t row0, int64_t n_rows, int64_t case0,
+                            int64_t n_cases, double* h_out) {
+  const OnDevice here(h);
+  const RunDev& R = h->runs_h[run];
+  const int64_t rows = which == 0 ? h->cfg.pop_size : h->cfg.pool_size;
+  const void* buf = which == 0 ? R.S[h->gen & 1] : R.sigR;
+  const bool scaled = which == 0 && (h->cfg.flags & GSGP_FLAG_LOCAL_SEARCH);
+  const double* ls = scaled ? R.ls + (int64_t)h->gen * h->cfg.pop_size * 2 : nullptr;
+  const int64_t total = n_rows * n_cases;
+  const bool mapped = sizeof(double) * (size_t)total <= h->pinned_bytes;
+  double* to = mapped ? (double*)h->pinned : (double*)R.S[(h->gen & 1) ^ 1];
+  const int64_t most = mapped ? total : (int64_t)(storage_bytes(h->cfg.precision) * h->cfg.pop_size * R.ld / sizeof(double));
+  for (int64_t e = 0; e < total; e += most) {
+    const int64_t count = std::min(most, total - e);
+    HIPCHK(h, launch_fetch_semantics(h->cfg.precision, R, buf, rows, row0, case0, n_cases, e, count, ls, to, h->stream));
+    if (!mapped)
+      HIPCHK(h, hipMemcpyAsync(h_out + e, to, sizeof(double) * count, hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    if (mapped) memcpy(h_out, h->pinned, sizeof(double) * count);
   }
   return GSGP_OK;
-}
-
-// Unpacks a chunk-tiled semantic buffer (see chunk_geom) into FP64 rows of
-// n_train + n_test cases.
-template <typename T>
-void to_f64(const std::vector<char>& raw, int64_t rows, const RunDev& R, double* out) {
-  const T* s = (const T*)raw.data();
-  const int64_t n_all = R.n_train + R.n_test;
-  const int64_t CH = chunk_cases((int)sizeof(T));
-  for (int32_t c = 0; c < R.nch; ++c) {
-    const ChunkGeom g = chunk_geom(R.tr_pad, R.te_pad, R.nch_tr, c, CH);
-    const bool train = c < R.nch_tr;
-    const int64_t first = train ? g.cs : g.cs - R.tr_pad;              // case index in its segment
-    const int64_t real = (train ? R.n_train : R.n_test) - first;      // real cases left in the segment
-    const int64_t used = std::min<int64_t>(g.len, std::max<int64_t>(real, 0));
-    const int64_t out0 = train ? first : R.n_train + first;
-    for (int64_t i = 0; i < rows; ++i) {
-      const T* src = s + rows * g.cs + i * g.len;
-      for (int64_t k = 0; k < used; ++k) out[i * n_all + out0 + k] = (double)src[k];
-    }
-  }
 }
 
 }  // namespace
@@ -491,7 +510,8 @@ gsgp_status gsgp_init(const gsgp_config* cfg, const gsgp_run* runs, int32_t n_ru
   hipError_t e = hipGetDevice(&h->device);
   if (e == hipSuccess) e = resolve_static_scratch(h->device);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipHostMalloc((void**)&h->pinned, sizeof(int32_t) * kStWords * n_runs, hipHostMallocDefault);
+  h->pinned_bytes = std::max(kPinnedBytes, sizeof(int32_t) * kStWords * n_runs);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&h->pinned, h->pinned_bytes, hipHostMallocDefault);
   if (e != hipSuccess) {
     gsgp_status s2 = fail(GSGP_ERR_HIP, "creating handle resources: %s", hipGetErrorString(e));
     gsgp_destroy(h);
@@ -778,7 +798,7 @@ static gsgp_status generation_body(gsgp_handle* h, int32_t n_gens, gsgp_gen_stat
   const int32_t g0 = h->gen;
   st = run_generations(h, n_gens);
   if (st != GSGP_OK) return st;
-  if (h_stats) return copy_stats(h, g0 + 1, n_gens, h_stats, n_gens);
+  if (h_stats) return copy_stats(h, 0, h->n_runs, g0 + 1, n_gens, h_stats);
   return GSGP_OK;
 }
 
@@ -822,7 +842,7 @@ static gsgp_status generation_replay_body(gsgp_handle* h, int32_t n_gens, const 
   HIPCHK(h, launch_set_state(h->runs_d, h->n_runs, kStReplaySelect, 0, h->stream));
   HIPCHK(h, launch_set_state(h->runs_d, h->n_runs, kStReplayElite, 0, h->stream));
   HIPCHK(h, launch_survive(h->runs_d, h->params, h->surv_blocks, kSurvSelectOnly, h->stream));
-  if (h_stats) return copy_stats(h, g0 + 1, n_gens, h_stats, n_gens);
+  if (h_stats) return copy_stats(h, 0, h->n_runs, g0 + 1, n_gens, h_stats);
   return GSGP_OK;
 }
 
@@ -837,9 +857,18 @@ gsgp_status gsgp_current_generation(gsgp_handle* h, int32_t* gen) {
 gsgp_status gsgp_get_fitness(gsgp_handle* h, int32_t run, double* h_train, double* h_test) {
   gsgp_status st = check_run(h, run);
   if (st != GSGP_OK) return st;
-  HIPCHK(h, hipStreamSynchronize(h->stream));
+  const OnDevice here(h);
   const RunDev& R = h->runs_h[run];
   const int cur = h->gen & 1;
+  const size_t bytes = sizeof(double) * h->cfg.pop_size;
+  if (2 * bytes <= h->pinned_bytes) {
+    HIPCHK(h, launch_fetch_pair(R.F[cur], R.Ft[cur], h->cfg.pop_size, (double*)h->pinned, h->stream));
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    if (h_train) memcpy(h_train, h->pinned, bytes);
+    if (h_test) memcpy(h_test, (char*)h->pinned + bytes, bytes);
+    return GSGP_OK;
+  }
+  HIPCHK(h, hipStreamSynchronize(h->stream));
   if (h_train) HIPCHK(h, hipMemcpy(h_train, R.F[cur], 8 * h->cfg.pop_size, hipMemcpyDeviceToHost));
   if (h_test) HIPCHK(h, hipMemcpy(h_test, R.Ft[cur], 8 * h->cfg.pop_size, hipMemcpyDeviceToHost));
   return GSGP_OK;
@@ -854,24 +883,7 @@ gsgp_status gsgp_get_semantics_rows(gsgp_handle* h, int32_t run, int32_t which, 
   const int64_t rows = which == 0 ? h->cfg.pop_size : h->cfg.pool_size;
   if (row0 < 0 || n_rows < 1 || (int64_t)row0 + n_rows > rows)
     return fail(GSGP_ERR_ARG, "rows %d..%d not in [0, %lld)", row0, row0 + n_rows - 1, (long long)rows);
-  HIPCHK(h, hipStreamSynchronize(h->stream));
-  const RunDev& R = h->runs_h[run];
-  const size_t s = storage_bytes(h->cfg.precision);
-  const int64_t CH = chunk_cases((int)s);
-  // gather the rows' part of every chunk block into a tiled buffer of n_rows rows
-  std::vector<char> raw((size_t)n_rows * R.ld * s);
-  const char* from = (const char*)(which == 0 ? R.S[h->gen & 1] : R.sigR);
-  for (int32_t c = 0; c < R.nch; ++c) {
-    const ChunkGeom g = chunk_geom(R.tr_pad, R.te_pad, R.nch_tr, c, CH);
-    HIPCHK(h, hipMemcpy(raw.data() + (size_t)n_rows * g.cs * s, from + (size_t)(rows * g.cs + row0 * g.len) * s,
-                        (size_t)n_rows * g.len * s, hipMemcpyDeviceToHost));
-  }
-  if (s == 8)
-    to_f64<double>(raw, n_rows, R, h_out);
-  else
-    to_f64<float>(raw, n_rows, R, h_out);
-  if (which == 0) return apply_scaling(h, run, row0, n_rows, R.n_train + R.n_test, h_out);
-  return GSGP_OK;
+  return fetch_semantics(h, run, which, row0, n_rows, 0, h->runs_h[run].n_train + h->runs_h[run].n_test, h_out);
 }
 
 gsgp_status gsgp_get_semantics_cases(gsgp_handle* h, int32_t run, int32_t which, int64_t case0, int64_t n_cases,
@@ -885,52 +897,7 @@ gsgp_status gsgp_get_semantics_cases(gsgp_handle* h, int32_t run, int32_t which,
   if (case0 < 0 || n_cases < 1 || case0 + n_cases > n_all)
     return fail(GSGP_ERR_ARG, "cases %lld..%lld not in [0, %lld)", (long long)case0, (long long)(case0 + n_cases - 1),
                 (long long)n_all);
-  HIPCHK(h, hipStreamSynchronize(h->stream));
-  const int64_t rows = which == 0 ? h->cfg.pop_size : h->cfg.pool_size;
-  const size_t s = storage_bytes(h->cfg.precision);
-  const int64_t CH = chunk_cases((int)s);
-  const char* from = (const char*)(which == 0 ? R.S[h->gen & 1] : R.sigR);
-  // the requested cases as padded-column ranges: train part, then test part
-  struct Piece {
-    int64_t col0, col1, out0;
-  };
-  Piece pieces[2];
-  int np = 0;
-  const int64_t c1 = case0 + n_cases;
-  if (case0 < R.n_train) pieces[np++] = Piece{case0, std::min(c1, R.n_train), 0};
-  if (c1 > R.n_train) {
-    const int64_t t0 = std::max(case0, R.n_train) - R.n_train, t1 = c1 - R.n_train;
-    pieces[np++] = Piece{R.tr_pad + t0, R.tr_pad + t1, std::max(case0, R.n_train) - case0};
-  }
-  std::vector<char> buf;
-  for (int q = 0; q < np; ++q) {
-    const Piece& pc = pieces[q];
-    const int32_t first = pc.col0 < R.tr_pad ? (int32_t)(pc.col0 / CH) : R.nch_tr + (int32_t)((pc.col0 - R.tr_pad) / CH);
-    for (int32_t c = first; c < R.nch; ++c) {
-      const ChunkGeom g = chunk_geom(R.tr_pad, R.te_pad, R.nch_tr, c, CH);
-      const int64_t lo = std::max(pc.col0, g.cs), hi = std::min(pc.col1, g.cs + g.len);
-      if (g.cs >= pc.col1) break;
-      if (lo >= hi) continue;
-      // rows x (hi - lo) sub-block of the chunk block: row i at rows * cs + i * len + (lo - cs)
-      const int64_t w = hi - lo;
-      buf.resize((size_t)rows * w * s);
-      HIPCHK(h, hipMemcpy2D(buf.data(), (size_t)w * s, from + (size_t)(rows * g.cs + (lo - g.cs)) * s, (size_t)g.len * s,
-                            (size_t)w * s, (size_t)rows, hipMemcpyDeviceToHost));
-      const int64_t o = pc.out0 + (lo - pc.col0);
-      for (int64_t i = 0; i < rows; ++i) {
-        double* dst = h_out + i * n_cases + o;
-        if (s == 8) {
-          const double* src = (const double*)buf.data() + i * w;
-          for (int64_t k = 0; k < w; ++k) dst[k] = src[k];
-        } else {
-          const float* src = (const float*)buf.data() + i * w;
-          for (int64_t k = 0; k < w; ++k) dst[k] = (double)src[k];
-        }
-      }
-    }
-  }
-  if (which == 0) return apply_scaling(h, run, 0, (int32_t)rows, n_cases, h_out);
-  return GSGP_OK;
+  return fetch_semantics(h, run, which, 0, which == 0 ? h->cfg.pop_size : h->cfg.pool_size, case0, n_cases, h_out);
 }
 
 gsgp_status gsgp_get_semantics(gsgp_handle* h, int32_t run, int32_t which, double* h_out) {
@@ -965,9 +932,7 @@ gsgp_status gsgp_get_stats(gsgp_handle* h, int32_t run, int32_t gen0, int32_t n_
   if (st != GSGP_OK) return st;
   if (!h_out || n_gens < 1 || gen0 < 0 || (int64_t)gen0 + n_gens - 1 > h->gen)
     return fail(GSGP_ERR_ARG, "summaries of generations %d..%d are not available (current %d)", gen0, gen0 + n_gens - 1, h->gen);
-  HIPCHK(h, hipStreamSynchronize(h->stream));
-  HIPCHK(h, hipMemcpy(h_out, h->runs_h[run].stats + gen0, sizeof(gsgp_gen_stats) * n_gens, hipMemcpyDeviceToHost));
-  return GSGP_OK;
+  return copy_stats(h, run, 1, gen0, n_gens, h_out);
 }
 
 gsgp_status gsgp_get_scaling(gsgp_handle* h, int32_t run, int32_t gen0, int32_t n_gens, double* h_out) {
