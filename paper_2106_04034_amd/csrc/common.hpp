@@ -201,6 +201,7 @@ hipError_t launch_prep(const RunDev* d_runs, const Params& p, int64_t total_cols
                        const double* const* Xsrc, const double* const* ysrc, hipStream_t s);
 hipError_t launch_set_state(const RunDev* d_runs, int32_t n_runs, int32_t word, int32_t value,
                             hipStream_t s);
+hipError_t launch_reset_state(const RunDev* d_runs, int32_t n_runs, hipStream_t s);
 hipError_t launch_genome(const RunDev* d_runs, const Params& p, hipStream_t s);
 hipError_t launch_compile(const RunDev* d_runs, const Params& p, hipStream_t s);
 // Interpreter passes: each takes the programs of stack-need list `list` (at

@@ -707,9 +707,7 @@ gsgp_status eval_impl(gsgp_handle* h, const int32_t* h_codes, const double* h_co
     }
   }
   if (ev) HIPCHK(h, hipEventRecord(ev[0], h->stream));
-  for (int32_t w : {kStGen, kStDone, kStReplaySelect, kStReplayElite, kStMaxDepth})
-    HIPCHK(h, launch_set_state(h->runs_d, h->n_runs, w, 0, h->stream));
-  for (int32_t b = 0; b < kLists; ++b) HIPCHK(h, launch_set_state(h->runs_d, h->n_runs, kStList0 + b, 0, h->stream));
+  HIPCHK(h, launch_reset_state(h->runs_d, h->n_runs, h->stream));
   if (h_codes) {
     for (int32_t r = 0; r < h->n_runs; ++r) {
       HIPCHK(h, hipMemcpyAsync(h->runs_h[r].code, h_codes + r * per, 4 * per, hipMemcpyHostToDevice, h->stream));
