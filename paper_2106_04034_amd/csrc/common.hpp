@@ -248,6 +248,14 @@ struct ReplayNode {
   double ms;
   double alpha, beta;  // local search: the offspring is alpha + beta * (operator output)
 };
+// A whole lineage of `gen` generations in one launch: nodes of generation g at
+// begin[g] .. begin[g + 1] - 1 (device array of gen + 2), at most `slots` rows
+// a generation; replay_cases(slots) must not be 0.
+constexpr int64_t kReplayLdsBytes = 128 << 10;
+int replay_cases(int64_t slots);
+hipError_t launch_replay_lineage(const ReplayNode* nodes, const int32_t* begin, int32_t gen, int32_t n0, int32_t np,
+                                 int32_t slots, int64_t total_nodes, int32_t out_slot, const double* first,
+                                 const double* pool, int64_t ld, int64_t n, double* out, hipStream_t s);
 hipError_t launch_replay_nodes(const ReplayNode* nodes, int32_t nnodes, const double* prev,
                                const double* pool, double* next, int64_t ld, int64_t n,
                                hipStream_t s);

@@ -982,6 +982,22 @@ __global__ __launch_bounds__(256) void k_transpose(const double* __restrict__ X,
   for (int f = 0; f < l; ++f) Xfm[(int64_t)f * ld + c] = c < n ? X[c * l + f] : 0.0;
 }
 
+// One recorded step on one case: the parents' values a (and b, crossover) and
+// the squashed pool values r1 (and r2, mutation).
+__device__ __forceinline__ double replay_step(const ReplayNode& nd, double a, double b, double r1, double r2) {
+  double o = a;
+  if (nd.op == 0)
+    o = a + nd.ms * (r1 - r2);
+  else if (nd.op == 1)
+    o = a * r1 + b * (1.0 - r1);
+  // local search: the offspring's recorded scaling (never for copies, and
+  // skipped when it is the identity so that unscaled runs keep their bits)
+  if (nd.op != 2 && (nd.alpha != 0.0 || nd.beta != 1.0)) o = nd.alpha + nd.beta * o;
+  return o;
+}
+
+// One generation of a lineage, rows in global memory (for lineages whose
+// rows of one generation exceed LDS, see k_replay_lineage).
 __global__ __launch_bounds__(256) void k_replay_nodes(const ReplayNode* __restrict__ nodes,
                                                       const double* __restrict__ prev,
                                                       const double* __restrict__ pool,
@@ -990,19 +1006,64 @@ __global__ __launch_bounds__(256) void k_replay_nodes(const ReplayNode* __restri
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n) return;
   const double a = prev[(int64_t)nd.a * ld + c];
-  double o;
-  if (nd.op == 0) {
-    o = a + nd.ms * (pool[(int64_t)nd.r1 * ld + c] - pool[(int64_t)nd.r2 * ld + c]);
-  } else if (nd.op == 1) {
-    const double r = pool[(int64_t)nd.r1 * ld + c];
-    o = a * r + prev[(int64_t)nd.b * ld + c] * (1.0 - r);
-  } else {
-    o = a;
+  const double b = nd.op == 1 ? prev[(int64_t)nd.b * ld + c] : 0.0;
+  const double r1 = nd.op != 2 ? pool[(int64_t)nd.r1 * ld + c] : 0.0;
+  const double r2 = nd.op == 0 ? pool[(int64_t)nd.r2 * ld + c] : 0.0;
+  next[(int64_t)nd.out * ld + c] = replay_step(nd, a, b, r1, r2);
+}
+
+// A whole lineage in one launch.  Cases are independent, so a block takes C
+// of them through every generation with the live rows of two generations
+// (and, when they fit too, the pool rows) in LDS: [slot][C].  Thread t works
+// on case t % C of nodes t / C, t / C + threads / C, ...; the next node is
+// read before the barrier that ends a generation, since nodes depend on no
+// value.  What bounds it is the chain of generations (a barrier, a node read
+// and two LDS round trips each); a launch a generation took 8.5 us for 10,000
+// cases and 2.7 us for 16, plus the gap to the next one.
+template <int C, bool POOL>
+__global__ __launch_bounds__(1024) void k_replay_lineage(const ReplayNode* __restrict__ nodes,
+                                                         const int32_t* __restrict__ begin, int32_t gen, int32_t n0,
+                                                         int32_t np, int32_t slots, int32_t out_slot,
+                                                         const double* __restrict__ first,
+                                                         const double* __restrict__ pool, int64_t ld, int64_t n,
+                                                         double* __restrict__ out) {
+  extern __shared__ double rows[];  // two generations of slots x C, then the pool's np x C
+  const int64_t c0 = (int64_t)blockIdx.x * C;  // ld is a multiple of 64, so c0 + C <= ld
+  const int cl = threadIdx.x % C;
+  const int lane = threadIdx.x / C, lanes = blockDim.x / C;
+  double* cur = rows;
+  double* nxt = rows + (int64_t)slots * C;
+  double* pl = rows + 2 * (int64_t)slots * C;
+  for (int j = lane; j < n0; j += lanes) cur[j * C + cl] = first[(int64_t)j * ld + c0 + cl];
+  if constexpr (POOL)
+    for (int j = lane; j < np; j += lanes) pl[j * C + cl] = pool[(int64_t)j * ld + c0 + cl];
+  auto pool_at = [&](int r) { return POOL ? pl[r * C + cl] : pool[(int64_t)r * ld + c0 + cl]; };
+  int b = begin[1], e = begin[2];
+  ReplayNode nd{};
+  if (b + lane < e) nd = nodes[b + lane];
+  for (int g = 1; g <= gen; ++g) {
+    const int e2 = g < gen ? begin[g + 2] : e;  // end of the next generation's nodes
+    __syncthreads();
+    for (int q = b + lane; q < e; q += lanes) {
+      const ReplayNode now = nd;
+      const int following = q + lanes < e ? q + lanes : e + lane;  // in this generation, or the next one's first
+      if (following < e2) nd = nodes[following];
+      const double a = cur[now.a * C + cl];
+      const double bb = now.op == 1 ? cur[now.b * C + cl] : 0.0;
+      const double r1 = now.op != 2 ? pool_at(now.r1) : 0.0;
+      const double r2 = now.op == 0 ? pool_at(now.r2) : 0.0;
+      nxt[now.out * C + cl] = replay_step(now, a, bb, r1, r2);
+    }
+    // threads without a node in this generation read their next one here
+    if (b + lane >= e && e + lane < e2) nd = nodes[e + lane];
+    b = e;
+    e = e2;
+    double* t = cur;
+    cur = nxt;
+    nxt = t;
   }
-  // local search: the offspring's recorded scaling (never for copies, and
-  // skipped when it is the identity so that unscaled runs keep their bits)
-  if (nd.op != 2 && (nd.alpha != 0.0 || nd.beta != 1.0)) o = nd.alpha + nd.beta * o;
-  next[(int64_t)nd.out * ld + c] = o;
+  __syncthreads();
+  if (lane == 0 && c0 + cl < n) out[c0 + cl] = cur[out_slot * C + cl];
 }
 
 // ---------------------------------------------------------------------------
@@ -1230,6 +1291,50 @@ hipError_t launch_survive(const RunDev* d_runs, const Params& p, int32_t total_b
 hipError_t launch_transpose(const double* X, int64_t n, int32_t l, double* Xfm, int64_t ld,
                             hipStream_t s) {
   hipLaunchKernelGGL(k_transpose, dim3(blocks_for(ld, 256)), dim3(256), 0, s, X, n, l, Xfm, ld);
+  return hipGetLastError();
+}
+
+// Cases per block of k_replay_lineage: the most whose two generations of
+// rows fit in LDS, 0 when not even one case's do.  More cases a block read
+// each node less often, and 8 make a row's segment of a cache line.
+int replay_cases(int64_t slots) {
+  for (int c = 8; c >= 1; c >>= 1)
+    if (2 * slots * c * (int64_t)sizeof(double) <= kReplayLdsBytes) return c;
+  return 0;
+}
+
+template <int C>
+void launch_replay_lineage_as(bool pool_lds, dim3 grid, dim3 block, size_t shmem, hipStream_t s,
+                              const ReplayNode* nodes, const int32_t* begin, int32_t gen, int32_t n0, int32_t np,
+                              int32_t slots, int32_t out_slot, const double* first, const double* pool, int64_t ld,
+                              int64_t n, double* out) {
+  if (pool_lds)
+    hipLaunchKernelGGL((k_replay_lineage<C, true>), grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot,
+                       first, pool, ld, n, out);
+  else
+    hipLaunchKernelGGL((k_replay_lineage<C, false>), grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot,
+                       first, pool, ld, n, out);
+}
+
+hipError_t launch_replay_lineage(const ReplayNode* nodes, const int32_t* begin, int32_t gen, int32_t n0, int32_t np,
+                                 int32_t slots, int64_t total_nodes, int32_t out_slot, const double* first,
+                                 const double* pool, int64_t ld, int64_t n, double* out, hipStream_t s) {
+  const int c = replay_cases(slots);
+  if (c == 0 || gen < 1) return hipErrorInvalidValue;
+  size_t shmem = 2 * (size_t)slots * c * sizeof(double);
+  const size_t pool_bytes = (size_t)np * c * sizeof(double);
+  const bool pool_lds = shmem + pool_bytes <= (size_t)kReplayLdsBytes;
+  if (pool_lds) shmem += pool_bytes;
+  // one sweep of the threads per generation where a block may be that large
+  const int64_t want = (total_nodes + gen - 1) / gen * c;
+  const int threads = (int)(want > 1024 ? 1024 : (want + kWave - 1) / kWave * kWave);
+  const dim3 grid((unsigned)((n + c - 1) / c)), block(threads);
+  switch (c) {
+    case 8: launch_replay_lineage_as<8>(pool_lds, grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot, first, pool, ld, n, out); break;
+    case 4: launch_replay_lineage_as<4>(pool_lds, grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot, first, pool, ld, n, out); break;
+    case 2: launch_replay_lineage_as<2>(pool_lds, grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot, first, pool, ld, n, out); break;
+    default: launch_replay_lineage_as<1>(pool_lds, grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot, first, pool, ld, n, out); break;
+  }
   return hipGetLastError();
 }
 
