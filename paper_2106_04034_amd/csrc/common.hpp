@@ -96,6 +96,14 @@ enum StateWord : int {
   kStWords = 12
 };
 
+// Best and worst train fitness of kFitGroup consecutive individuals (lowest
+// index on ties): the fitness kernel leaves one per group for survival.
+constexpr int kFitGroup = 16;
+struct Extremes {
+  double min, max;
+  int32_t min_i, max_i;
+};
+
 // Everything a kernel needs to know about one run; lives in the workspace.
 struct RunDev {
   void* S[2];               // population semantics ping-pong, [m][ld], storage type
@@ -106,6 +114,7 @@ struct RunDev {
                             // search the generation's sums of o, o^2 and o * t, [nch][3][m]
   double* F[2];             // train RMSE ping-pong, [m]
   double* Ft[2];            // test RMSE ping-pong, [m]
+  Extremes* extremes;       // of the newest fitness, [ceil(m / kFitGroup)]
   gsgp_record* rec;         // variation draws, [gmax][m]; generation g at g - 1
   gsgp_gen_stats* stats;    // [gmax + 1]
   gsgp_gen_stats* elite_in; // supplied survival decisions, [gmax]

@@ -526,56 +526,104 @@ __global__ __launch_bounds__(512) void k_vary(const RunDev* __restrict__ runs, P
 // (the generation-0 partial sums never scale: every individual starts with
 // alpha = 0, beta = 1)
 
-// ComputeFitness (Section 2.2 "Fitness computation"): a block takes 64
-// individuals of one run (lane = individual, so the chunk-major partial sums
-// are read with coalesced loads); its kFitWaves waves split each segment's
-// chunks into contiguous ranges, sum them in chunk order, and the ranges are
-// added in wave order in FP64.  Then the root mean.
-constexpr int kFitWaves = 16;
+// A value and the individual it belongs to; the lowest index wins ties, as
+// the first extremum that I?AMIN / I?AMAX return.
+struct ValIdx {
+  double v;
+  int i;
+};
 
-__device__ __forceinline__ double sum_range(const double* __restrict__ part, int64_t m, int i, int c0, int c1) {
+__device__ __forceinline__ ValIdx pick_min(ValIdx a, ValIdx b) {
+  return (b.v < a.v || (b.v == a.v && b.i < a.i)) ? b : a;
+}
+__device__ __forceinline__ ValIdx pick_max(ValIdx a, ValIdx b) {
+  return (b.v > a.v || (b.v == a.v && b.i < a.i)) ? b : a;
+}
+
+// Extrema over groups of W neighbouring lanes (a power of two).
+template <int W>
+__device__ __forceinline__ void lane_extrema(ValIdx& lo, ValIdx& hi) {
+#pragma unroll
+  for (int o = W / 2; o >= 1; o >>= 1) {
+    lo = pick_min(lo, ValIdx{__shfl_xor(lo.v, o, kWave), __shfl_xor(lo.i, o, kWave)});
+    hi = pick_max(hi, ValIdx{__shfl_xor(hi.v, o, kWave), __shfl_xor(hi.i, o, kWave)});
+  }
+}
+
+// ComputeFitness (Section 2.2 "Fitness computation"): a block takes
+// kFitGroup individuals of one run; its threads split each segment's chunks
+// into kFitRanges contiguous ranges per individual, sum them in chunk order,
+// and the ranges are added in range order in FP64.  Then the root mean, and
+// the group's best and worst train fitness for the survival kernel.
+// What bounds it is the latency of the chunk sums (8 B per individual and
+// chunk, read once): kFitUnroll of them are in flight per thread.  16
+// individuals a block (128-byte segments) put four times as many CUs to work
+// as 64: 1,024 individuals on 2,442 chunks 30.4 -> 13.6 us, on 245 chunks
+// 6.9 -> 5.5 us; on 13 chunks, where the launch is all of it, 4.6 -> 4.8 us.
+constexpr int kFitRanges = 16;
+constexpr int kFitUnroll = 16;
+
+__device__ __forceinline__ double sum_range(const double* __restrict__ part, int64_t stride, int c0, int c1) {
   double s = 0.0;
   int c = c0;
-  for (; c + 4 <= c1; c += 4) {
-    const double a = part[(int64_t)c * m + i];
-    const double b = part[(int64_t)(c + 1) * m + i];
-    const double d = part[(int64_t)(c + 2) * m + i];
-    const double e = part[(int64_t)(c + 3) * m + i];
-    s += a;
-    s += b;
-    s += d;
-    s += e;
+  for (; c + kFitUnroll <= c1; c += kFitUnroll) {
+    double v[kFitUnroll];
+#pragma unroll
+    for (int u = 0; u < kFitUnroll; ++u) v[u] = part[(int64_t)(c + u) * stride];
+#pragma unroll
+    for (int u = 0; u < kFitUnroll; ++u) s += v[u];
   }
-  for (; c < c1; ++c) s += part[(int64_t)c * m + i];
+  if (c < c1) {
+    double v[kFitUnroll];
+#pragma unroll
+    for (int u = 0; u < kFitUnroll; ++u) v[u] = c + u < c1 ? part[(int64_t)(c + u) * stride] : 0.0;
+#pragma unroll
+    for (int u = 0; u < kFitUnroll; ++u)
+      if (c + u < c1) s += v[u];
+  }
   return s;
 }
 
-__global__ __launch_bounds__(kFitWaves * 64) void k_fitness(const RunDev* __restrict__ runs, Params p,
-                                                             int32_t blocks_per_run, int init) {
-  __shared__ double sh_tr[kFitWaves][kWave];
-  __shared__ double sh_te[kFitWaves][kWave];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+// Writes the extremes of a group's fitness (threads 0 .. kFitGroup - 1 hold
+// the individuals' values).
+__device__ __forceinline__ void store_extremes(const RunDev& R, int group, bool live, double f, int i) {
+  ValIdx lo{live ? f : INFINITY, live ? i : 0x7fffffff}, hi{live ? f : -INFINITY, live ? i : 0x7fffffff};
+  lane_extrema<kFitGroup>(lo, hi);
+  if (threadIdx.x == 0) R.extremes[group] = Extremes{lo.v, hi.v, lo.i, hi.i};
+}
+
+__global__ __launch_bounds__(kFitRanges * kFitGroup) void k_fitness(const RunDev* __restrict__ runs, Params p,
+                                                                     int32_t blocks_per_run, int init) {
+  __shared__ double sh_tr[kFitRanges][kFitGroup];
+  __shared__ double sh_te[kFitRanges][kFitGroup];
+  const int l = threadIdx.x % kFitGroup;
+  const int w = threadIdx.x / kFitGroup;
   const int run = blockIdx.x / blocks_per_run;
-  const int i = (blockIdx.x - run * blocks_per_run) * kWave + lane;
+  const int group = blockIdx.x - run * blocks_per_run;
+  const int i = group * kFitGroup + l;
   const RunDev& R = runs[run];
   const bool live = i < p.m;
-  const int ii = live ? i : 0;
+  const double* part = R.part + (live ? i : 0);
   const int nt = R.nch_tr, ne = R.nch - R.nch_tr;
-  const int a0 = (int)((int64_t)nt * wave / kFitWaves), a1 = (int)((int64_t)nt * (wave + 1) / kFitWaves);
-  const int b0 = nt + (int)((int64_t)ne * wave / kFitWaves), b1 = nt + (int)((int64_t)ne * (wave + 1) / kFitWaves);
-  sh_tr[wave][lane] = sum_range(R.part, p.m, ii, a0, a1);
-  sh_te[wave][lane] = sum_range(R.part, p.m, ii, b0, b1);
+  const int a0 = (int)((int64_t)nt * w / kFitRanges), a1 = (int)((int64_t)nt * (w + 1) / kFitRanges);
+  const int b0 = nt + (int)((int64_t)ne * w / kFitRanges), b1 = nt + (int)((int64_t)ne * (w + 1) / kFitRanges);
+  sh_tr[w][l] = sum_range(part, p.m, a0, a1);
+  sh_te[w][l] = sum_range(part, p.m, b0, b1);
   __syncthreads();
-  if (wave == 0 && live) {
-    double s = sh_tr[0][lane], st = sh_te[0][lane];
-    for (int w = 1; w < kFitWaves; ++w) {
-      s += sh_tr[w][lane];
-      st += sh_te[w][lane];
+  if (threadIdx.x < kFitGroup) {
+    double s = sh_tr[0][l], st = sh_te[0][l];
+#pragma unroll
+    for (int q = 1; q < kFitRanges; ++q) {
+      s += sh_tr[q][l];
+      st += sh_te[q][l];
     }
     const int dst = init ? 0 : ((R.state[kStGen] + 1) & 1);
-    R.F[dst][i] = sqrt(s / (double)R.n_train);
-    R.Ft[dst][i] = R.n_test > 0 ? sqrt(st / (double)R.n_test) : 0.0;
+    const double f = sqrt(s / (double)R.n_train);
+    if (live) {
+      R.F[dst][i] = f;
+      R.Ft[dst][i] = R.n_test > 0 ? sqrt(st / (double)R.n_test) : 0.0;
+    }
+    store_extremes(R, group, live, f, i);
   }
 }
 
@@ -590,33 +638,31 @@ __global__ __launch_bounds__(kFitWaves * 64) void k_fitness(const RunDev* __rest
 // A numerically constant offspring (D <= 1e-10 * So2) keeps alpha = 0,
 // beta = 1 and SSE = So2 - 2 Sot + Stt.  Chunk sums combine as in k_fitness.
 // The scaling goes to the table row of the offspring generation.
-__global__ __launch_bounds__(kFitWaves * 64) void k_fitness_ls(const RunDev* __restrict__ runs, Params p,
-                                                                int32_t blocks_per_run) {
-  __shared__ double sh[6][kFitWaves][kWave];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+__global__ __launch_bounds__(kFitRanges * kFitGroup) void k_fitness_ls(const RunDev* __restrict__ runs, Params p,
+                                                                        int32_t blocks_per_run) {
+  __shared__ double sh[6][kFitRanges][kFitGroup];
+  const int l = threadIdx.x % kFitGroup;
+  const int w = threadIdx.x / kFitGroup;
   const int run = blockIdx.x / blocks_per_run;
-  const int i = (blockIdx.x - run * blocks_per_run) * kWave + lane;
+  const int group = blockIdx.x - run * blocks_per_run;
+  const int i = group * kFitGroup + l;
   const RunDev& R = runs[run];
   const bool live = i < p.m;
-  const int ii = live ? i : 0;
   const int64_t m = p.m;
+  const double* part = R.part + (live ? i : 0);
   const int nt = R.nch_tr, ne = R.nch - R.nch_tr;
-  const int a0 = (int)((int64_t)nt * wave / kFitWaves), a1 = (int)((int64_t)nt * (wave + 1) / kFitWaves);
-  const int b0 = nt + (int)((int64_t)ne * wave / kFitWaves), b1 = nt + (int)((int64_t)ne * (wave + 1) / kFitWaves);
+  const int a0 = (int)((int64_t)nt * w / kFitRanges), a1 = (int)((int64_t)nt * (w + 1) / kFitRanges);
+  const int b0 = nt + (int)((int64_t)ne * w / kFitRanges), b1 = nt + (int)((int64_t)ne * (w + 1) / kFitRanges);
   for (int q = 0; q < 3; ++q) {
-    double s = 0.0, st = 0.0;
-    for (int c = a0; c < a1; ++c) s += R.part[((int64_t)c * 3 + q) * m + ii];
-    for (int c = b0; c < b1; ++c) st += R.part[((int64_t)c * 3 + q) * m + ii];
-    sh[q][wave][lane] = s;
-    sh[3 + q][wave][lane] = st;
+    sh[q][w][l] = sum_range(part + q * m, 3 * m, a0, a1);
+    sh[3 + q][w][l] = sum_range(part + q * m, 3 * m, b0, b1);
   }
   __syncthreads();
-  if (wave == 0 && live) {
+  if (threadIdx.x < kFitGroup) {
     double v[6];
     for (int q = 0; q < 6; ++q) {
-      v[q] = sh[q][0][lane];
-      for (int w = 1; w < kFitWaves; ++w) v[q] += sh[q][w][lane];
+      v[q] = sh[q][0][l];
+      for (int r = 1; r < kFitRanges; ++r) v[q] += sh[q][r][l];
     }
     const double n = (double)R.n_train, So = v[0], Soo = v[1], Sot = v[2];
     const double St = R.tsum[0], Stt = R.tsum[1];
@@ -642,10 +688,14 @@ __global__ __launch_bounds__(kFitWaves * 64) void k_fitness_ls(const RunDev* __r
     }
     const int g1 = R.state[kStGen] + 1;
     const int dst = g1 & 1;
-    R.F[dst][i] = sqrt(sse / n);
-    R.Ft[dst][i] = R.n_test > 0 ? sqrt(sse_te / (double)R.n_test) : 0.0;
-    R.ls[((int64_t)g1 * m + i) * 2] = alpha;
-    R.ls[((int64_t)g1 * m + i) * 2 + 1] = beta;
+    const double f = sqrt(sse / n);
+    if (live) {
+      R.F[dst][i] = f;
+      R.Ft[dst][i] = R.n_test > 0 ? sqrt(sse_te / (double)R.n_test) : 0.0;
+      R.ls[((int64_t)g1 * m + i) * 2] = alpha;
+      R.ls[((int64_t)g1 * m + i) * 2 + 1] = beta;
+    }
+    store_extremes(R, group, live, f, i);
   }
 }
 
@@ -688,18 +738,6 @@ __global__ __launch_bounds__(256) void k_target_sums(const RunDev* __restrict__ 
 
 // ---------------------------------------------------------------------------
 // Survival, summary and the next generation's variation draws.
-struct ValIdx {
-  double v;
-  int i;
-};
-
-__device__ __forceinline__ ValIdx pick_min(ValIdx a, ValIdx b) {
-  return (b.v < a.v || (b.v == a.v && b.i < a.i)) ? b : a;
-}
-__device__ __forceinline__ ValIdx pick_max(ValIdx a, ValIdx b) {
-  return (b.v > a.v || (b.v == a.v && b.i < a.i)) ? b : a;
-}
-
 template <bool MAX, typename View>
 __device__ ValIdx block_arg(int m, View F, ValIdx* sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
@@ -780,60 +818,42 @@ __device__ gsgp_record draw_record(const Params& p, uint32_t run_id, int gen_dra
   return rc;
 }
 
-// Block-wide reduction of three extrema in one pass: argmin of a, argmin of
-// b, argmax of b (lowest index on ties).
-template <typename A, typename B>
-__device__ void block_arg3(int m, A fa, B fb, ValIdx* sh, ValIdx& min_a, ValIdx& min_b, ValIdx& max_b) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  ValIdx x{INFINITY, 0x7fffffff}, y{INFINITY, 0x7fffffff}, z{-INFINITY, 0x7fffffff};
-  for (int i = threadIdx.x; i < m; i += blockDim.x) {
-    const double va = fa(i), vb = fb(i);
-    x = pick_min(x, ValIdx{va, i});
-    y = pick_min(y, ValIdx{vb, i});
-    z = pick_max(z, ValIdx{vb, i});
+// Best and worst of a run's fitness from its groups' extremes: every wave
+// reduces them for itself, so no barrier is needed.
+__device__ __forceinline__ void run_extrema(const RunDev& R, int m, ValIdx& lo, ValIdx& hi) {
+  const int groups = (m + kFitGroup - 1) / kFitGroup;
+  lo = ValIdx{INFINITY, 0x7fffffff};
+  hi = ValIdx{-INFINITY, 0x7fffffff};
+  for (int g = threadIdx.x & 63; g < groups; g += kWave) {
+    const Extremes e = R.extremes[g];
+    lo = pick_min(lo, ValIdx{e.min, e.min_i});
+    hi = pick_max(hi, ValIdx{e.max, e.max_i});
   }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    x = pick_min(x, ValIdx{__shfl_xor(x.v, o, kWave), __shfl_xor(x.i, o, kWave)});
-    y = pick_min(y, ValIdx{__shfl_xor(y.v, o, kWave), __shfl_xor(y.i, o, kWave)});
-    z = pick_max(z, ValIdx{__shfl_xor(z.v, o, kWave), __shfl_xor(z.i, o, kWave)});
-  }
-  if (lane == 0) {
-    sh[wave] = x;
-    sh[8 + wave] = y;
-    sh[16 + wave] = z;
-  }
-  __syncthreads();
-  min_a = sh[0];
-  min_b = sh[8];
-  max_b = sh[16];
-  for (int w = 1; w < nw; ++w) {
-    min_a = pick_min(min_a, sh[w]);
-    min_b = pick_min(min_b, sh[8 + w]);
-    max_b = pick_max(max_b, sh[16 + w]);
-  }
-  __syncthreads();
+  lane_extrema<kWave>(lo, hi);
   // fitness is always finite; keep indices in range regardless
-  if (min_a.i < 0 || min_a.i >= m) min_a.i = 0;
-  if (min_b.i < 0 || min_b.i >= m) min_b.i = 0;
-  if (max_b.i < 0 || max_b.i >= m) max_b.i = 0;
+  if (lo.i < 0 || lo.i >= m) lo.i = 0;
+  if (hi.i < 0 || hi.i >= m) hi.i = 0;
 }
-
-constexpr int kSurvLdsMaxM = 4096;  // parents + offspring fitness staged in LDS up to this m
 
 // Survival with elitism (Section 2.2 "Survival"; Algorithm 1): offspring
 // replace parents; when the best parent is strictly better than the best
 // offspring it overwrites the worst offspring (lowest index on ties, as the
 // first extremum that I?AMIN / I?AMAX return).  Then the summary and the next
-// generation's draws.  surv_blks blocks per run share the elite row copy and
-// the draws; each block stages the fitness arrays in LDS (LDS = true) and
-// takes the survival decision redundantly; the last block to arrive
-// publishes the elite fitness and advances the generation counter.
-template <typename T, bool LDS>
+// generation's draws.  The best parent is in its generation's summary, the
+// best and worst offspring come from the fitness kernel's groups, so a block
+// reads m / 16 entries where it read and reduced 2 m values; surv_blks blocks
+// per run take the decision redundantly and share the elite row copy (16 KiB
+// a block) and the draws (64 a block: with the copy going on, one wave takes
+// them; a row of a few cases gave two blocks, whose one wave each drew 512).
+// The last block to arrive publishes the elite fitness and advances the
+// generation counter.  Bound by latency (the chain of counter, extremes,
+// decision, draws, arrival): 1,024 individuals on 5,000 cases 14.2 -> 7.5 us,
+// on 100,000 11.0 -> 8.1 us, 10,240 on 102,400 26.1 -> 9.5 us, 64 runs of 256
+// 15.7 -> 10.3 us.
+template <typename T>
 __global__ __launch_bounds__(256) void k_survive(const RunDev* __restrict__ runs, Params p,
                                                  int32_t total, int mode) {
-  extern __shared__ double fit[];  // [2 m] when LDS: parents, then offspring
-  __shared__ ValIdx sh[24];
+  __shared__ ValIdx sh[8];
   __shared__ int is_last;
   const int run = find_run(p.n_runs, (int64_t)blockIdx.x, [&](int r) { return (int64_t)runs[r].surv_blk0; });
   const RunDev& R = runs[run];
@@ -849,27 +869,18 @@ __global__ __launch_bounds__(256) void k_survive(const RunDev* __restrict__ runs
   double* FO = R.F[nxt];
   double* FtO = R.Ft[nxt];
   const bool gen_mode = mode == kSurvGen;
-  if constexpr (LDS) {
-    for (int i = threadIdx.x; i < m; i += blockDim.x) {
-      fit[i] = FP[i];
-      if (gen_mode) fit[m + i] = FO[i];
-    }
-    __syncthreads();
-  }
-  const double* fP = LDS ? fit : FP;
-  const double* fO = LDS ? fit + m : FO;
   int copied = 0, src = -1, dst = -1;
-  ValIdx bp, bo, wo;
-  block_arg3(m, [&](int i) { return fP[i]; }, [&](int i) { return gen_mode ? fO[i] : fP[i]; }, sh, bp, bo, wo);
+  ValIdx bo{0.0, 0}, wo{0.0, 0};
+  if (mode != kSurvSelectOnly) run_extrema(R, m, bo, wo);  // of the offspring, or of generation 0
   if (gen_mode) {
     if (replay_elite) {
       const gsgp_gen_stats e = R.elite_in[gen];
       copied = e.elite_copied;
       src = e.elite_src;
       dst = e.elite_dst;
-    } else if (bp.v < bo.v) {
+    } else if (R.stats[gen].best_train_rmse < bo.v) {
       copied = 1;
-      src = bp.i;
+      src = R.stats[gen].best_index;
       dst = wo.i;
     }
     if (copied) {
@@ -910,22 +921,21 @@ __global__ __launch_bounds__(256) void k_survive(const RunDev* __restrict__ runs
       }
     }
   }
+  const double f_src = copied ? FP[src] : 0.0;
   // when the other waves copied the elite row, wave 0 alone takes the draws
   const bool draw_split = copied && blockDim.x > kWave;
   // fitness of the individuals the next draw selects from
-  auto view_new = [&](int i) { return (copied && i == dst) ? fP[src] : fO[i]; };
-  auto view_cur = [&](int i) { return fP[i]; };
+  auto view_new = [&](int i) { return (copied && i == dst) ? f_src : FO[i]; };
+  auto view_cur = [&](int i) { return FP[i]; };
   if (bl == 0 && mode != kSurvSelectOnly) {
-    ValIdx b;
+    ValIdx b = bo;
     if (gen_mode) {
       if (replay_elite) {
         b = block_arg<false>(m, view_new, sh);
-      } else {
+      } else if (copied) {
         // an elite copy is strictly better than every offspring
-        b = copied ? ValIdx{fP[src], dst} : bo;
+        b = ValIdx{f_src, dst};
       }
-    } else {
-      b = bp;
     }
     if (threadIdx.x == 0) {
       gsgp_gen_stats st;
@@ -1251,13 +1261,12 @@ hipError_t launch_vary(const RunDev* d_runs, const Params& p, const VaryLaunch& 
 }
 
 hipError_t launch_fitness(const RunDev* d_runs, const Params& p, bool init, hipStream_t s) {
-  const int32_t per_run = (p.m + kWave - 1) / kWave;
+  const int32_t per_run = (p.m + kFitGroup - 1) / kFitGroup;
+  const dim3 grid((unsigned)(per_run * p.n_runs)), block(kFitRanges * kFitGroup);
   if (p.ls && !init)
-    hipLaunchKernelGGL(k_fitness_ls, dim3((unsigned)(per_run * p.n_runs)), dim3(kFitWaves * kWave), 0, s, d_runs,
-                       p, per_run);
+    hipLaunchKernelGGL(k_fitness_ls, grid, block, 0, s, d_runs, p, per_run);
   else
-    hipLaunchKernelGGL(k_fitness, dim3((unsigned)(per_run * p.n_runs)), dim3(kFitWaves * kWave), 0, s, d_runs, p,
-                       per_run, init ? 1 : 0);
+    hipLaunchKernelGGL(k_fitness, grid, block, 0, s, d_runs, p, per_run, init ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -1271,20 +1280,11 @@ hipError_t launch_target_sums(const RunDev* d_runs, const Params& p, hipStream_t
 
 hipError_t launch_survive(const RunDev* d_runs, const Params& p, int32_t total_blocks, int mode,
                           hipStream_t s) {
-  const bool lds = p.m <= kSurvLdsMaxM;
-  const size_t shmem = lds ? (size_t)2 * p.m * sizeof(double) : 0;
   const dim3 grid(total_blocks), block(256);
-  if (p.precision == GSGP_FP64) {
-    if (lds)
-      hipLaunchKernelGGL((k_survive<double, true>), grid, block, shmem, s, d_runs, p, total_blocks, mode);
-    else
-      hipLaunchKernelGGL((k_survive<double, false>), grid, block, 0, s, d_runs, p, total_blocks, mode);
-  } else {
-    if (lds)
-      hipLaunchKernelGGL((k_survive<float, true>), grid, block, shmem, s, d_runs, p, total_blocks, mode);
-    else
-      hipLaunchKernelGGL((k_survive<float, false>), grid, block, 0, s, d_runs, p, total_blocks, mode);
-  }
+  if (p.precision == GSGP_FP64)
+    hipLaunchKernelGGL(k_survive<double>, grid, block, 0, s, d_runs, p, total_blocks, mode);
+  else
+    hipLaunchKernelGGL(k_survive<float>, grid, block, 0, s, d_runs, p, total_blocks, mode);
   return hipGetLastError();
 }
 

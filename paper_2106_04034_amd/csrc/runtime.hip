@@ -66,6 +66,8 @@ gsgp_status fail(gsgp_status s, const char* fmt, ...) {
 // (larger ones are copied from device memory).
 constexpr size_t kPinnedBytes = (size_t)256 << 10;
 
+constexpr int64_t kSurvBlocks = 64;
+
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v, size_t a = kAlign) { return (v + a - 1) / a * a; }
 inline int64_t pad_to(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
@@ -82,7 +84,7 @@ size_t storage_bytes(int32_t precision) { return precision == GSGP_FP64 ? 8 : 4;
 struct RunPlan {
   int64_t n_train, n_test, tr_pad, te_pad, ld;
   int32_t l, nch_tr, nch_te;
-  size_t X, y, S0, S1, sigR, part, F0, F1, Ft0, Ft1, rec, stats, elite_in, code, cval, ops, opv, opy, nops, need, lists;
+  size_t X, y, S0, S1, sigR, part, F0, F1, Ft0, Ft1, extremes, rec, stats, elite_in, code, cval, ops, opv, opy, nops, need, lists;
   size_t ls, tsum;
   size_t end;
 };
@@ -193,7 +195,9 @@ gsgp_status make_plan(const gsgp_config* c, const gsgp_run* runs, int32_t n_runs
     p.F0 = take_at(8 * m, i, "F[0]");
     p.F1 = take_at(8 * m, i, "F[1]");
     p.Ft0 = take_at(8 * m, i, "Ft[0]");
-    p.Ft1 = take_at(8 * m, i, "Ft[1]");
+    // Ft[1] and, behind it, the fitness extremes of every group
+    p.Ft1 = take_at(8 * m + sizeof(Extremes) * ((m + kFitGroup - 1) / kFitGroup), i, "Ft[1]");
+    p.extremes = p.Ft1 + 8 * m;
     p.rec = take_at(sizeof(gsgp_record) * G * m, i, "variation records");
     p.stats = take_at(sizeof(gsgp_gen_stats) * (G + 1), i, "summaries");
     p.elite_in = take_at(sizeof(gsgp_gen_stats) * G, i, "supplied survival decisions");
@@ -556,6 +560,7 @@ gsgp_status gsgp_init(const gsgp_config* cfg, const gsgp_run* runs, int32_t n_ru
     R.F[1] = (double*)(ws + q.F1);
     R.Ft[0] = (double*)(ws + q.Ft0);
     R.Ft[1] = (double*)(ws + q.Ft1);
+    R.extremes = (Extremes*)(ws + q.extremes);
     R.rec = (gsgp_record*)(ws + q.rec);
     R.stats = (gsgp_gen_stats*)(ws + q.stats);
     R.elite_in = (gsgp_gen_stats*)(ws + q.elite_in);
@@ -587,9 +592,11 @@ gsgp_status gsgp_init(const gsgp_config* cfg, const gsgp_run* runs, int32_t n_ru
     R.cblk0w = itask_w;
     itask_w += (q.ld + 4 * kWave - 1) / (4 * kWave);
     R.surv_blk0 = sblk;
-    // survival blocks per run: each copies about 16 KiB of an elite row
-    const int64_t nb = ((int64_t)storage_bytes(cfg->precision) * q.ld + 16383) / 16384;
-    R.surv_blks = (int32_t)std::max<int64_t>(1, std::min<int64_t>(nb, 64));
+    // survival blocks per run: each copies about 16 KiB of an elite row and
+    // draws for at least 64 offspring, up to kSurvBlocks
+    const int64_t nb = std::max(((int64_t)storage_bytes(cfg->precision) * q.ld + 16383) / 16384,
+                                ((int64_t)cfg->pop_size + 63) / 64);
+    R.surv_blks = (int32_t)std::max<int64_t>(1, std::min<int64_t>(nb, kSurvBlocks));
     sblk += R.surv_blks;
   }
   h->interp_tasks = itask;
