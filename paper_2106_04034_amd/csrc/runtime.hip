@@ -353,6 +353,28 @@ void plan_rows(gsgp_handle* h) {
   h->rows.grid = h->vary.total_tasks;
 }
 
+// The shape a handle starts with (gsgp_set_launch and gsgp_autotune change
+// it; results never depend on it).  One offspring a wave, four waves a block:
+// with four offspring a wave the small launches leave the chip idle (128
+// individuals on 700 FP64 cases: 10.1 against 6.8 us) and the large ones lose
+// a few percent (1,024 on 125,000 FP32 cases 235 against 227 us).  Block
+// order: the XCDs take neighbouring chunks side by side (2) when there are
+// enough chunks to even out the windows of eight and a chunk's population
+// rows take at most 2 MiB of an XCD's 4 MiB L2 (125,000 FP32 cases 223 against
+// 227 us; 64 runs of 256 individuals 317 against 330 us); otherwise each XCD
+// takes a contiguous range (1) (13 chunks 18.0 against 18.9 us, 50 chunks 30.7
+// against 31.8 us, 2,048 individuals on 391 chunks 717 against 723 us).
+constexpr int64_t kSideBySideChunks = 128;
+constexpr int64_t kSideBySideRows = 1024;
+
+void plan_default(gsgp_handle* h) {
+  int64_t chunks = 0;
+  for (const RunDev& R : h->runs_h) chunks += R.nch;
+  const bool side_by_side = chunks >= kSideBySideChunks && h->cfg.pop_size <= kSideBySideRows;
+  plan_vary(h, 4, 4, side_by_side ? 2 : 1, 0);
+  plan_rows(h);
+}
+
 hipError_t upload_runs(gsgp_handle* h) {
   return hipMemcpyAsync(h->runs_d, h->runs_h.data(), sizeof(RunDev) * h->n_runs, hipMemcpyHostToDevice,
                         h->stream);
@@ -602,8 +624,7 @@ gsgp_status gsgp_init(const gsgp_config* cfg, const gsgp_run* runs, int32_t n_ru
   h->interp_tasks = itask;
   h->interp_tasks_w = itask_w;
   h->surv_blocks = sblk;
-  plan_vary(h, 4, 16, 1, 0);
-  plan_rows(h);
+  plan_default(h);
 
   std::vector<const double*> src(4 * (size_t)n_runs);
   for (int32_t i = 0; i < n_runs; ++i) {
