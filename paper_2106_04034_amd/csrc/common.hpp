@@ -104,6 +104,22 @@ struct Extremes {
   int32_t min_i, max_i;
 };
 
+// The loop without selection (tournament_size 0, no local search) runs up to
+// kBlockGens generations at a time (see k_mutate_block).  A copy of the best
+// parent over the worst offspring makes that individual leave its own line:
+// its values are then those of generation-0-of-the-block individual `root`,
+// taken through the recorded mutations of individual by[s] at step s (-1: the
+// copy itself, nothing applied).
+constexpr int kBlockGens = 7;
+struct BlockState {
+  int32_t base;                  // generation the block started from
+  int32_t n;                     // individuals that have left their line
+  int32_t dst;                   // the one the last step's copy overwrote, -1: no copy
+  int32_t who[kBlockGens];       // [n]
+  int32_t root[kBlockGens];
+  int32_t by[kBlockGens][kBlockGens + 1];
+};
+
 // Everything a kernel needs to know about one run; lives in the workspace.
 struct RunDev {
   void* S[2];               // population semantics ping-pong, [m][ld], storage type
@@ -111,10 +127,13 @@ struct RunDev {
   void* y;                  // target, [ld], storage type, zero pads
   double* X;                // features in case tiles, [ceil(ld / kXTile)][l][kXTile], zero pads
   double* part;             // chunk partial sums of squared residuals, [nch][m]; with local
-                            // search the generation's sums of o, o^2 and o * t, [nch][3][m]
+                            // search the generation's sums of o, o^2 and o * t, [nch][3][m];
+                            // for blocks of generations [kBlockGens][nch][m]
   double* F[2];             // train RMSE ping-pong, [m]
   double* Ft[2];            // test RMSE ping-pong, [m]
   Extremes* extremes;       // of the newest fitness, [ceil(m / kFitGroup)]
+  double* block_F;          // blocks of generations: train, then test RMSE of steps 1 .. kBlockGens - 1, [2][kBlockGens - 1][m]
+  BlockState* block;        // blocks of generations, else NULL
   gsgp_record* rec;         // variation draws, [gmax][m]; generation g at g - 1
   gsgp_gen_stats* stats;    // [gmax + 1]
   gsgp_gen_stats* elite_in; // supplied survival decisions, [gmax]
@@ -137,6 +156,7 @@ struct RunDev {
   uint32_t run_id;
   int32_t surv_blk0, surv_blks; // survival kernel blocks of this run
   int32_t x_big;            // X holds a value beyond 2^128 in magnitude (no short division by features)
+  int32_t row_blk0;         // first block of this run in the row kernel of a block of generations
   int64_t vary_task0;       // first task of this run in the variation launch
   int64_t cblk0;            // first 128-case block of this run (interpreter)
   int64_t cblk0w;           // first 256-case block of this run (wide interpreter)
@@ -231,6 +251,9 @@ hipError_t launch_interpret_spill(const RunDev* d_runs, const Params& p, double*
 hipError_t launch_vary(const RunDev* d_runs, const Params& p, const VaryLaunch& lc, bool rows_only,
                        hipStream_t s);
 hipError_t launch_fitness(const RunDev* d_runs, const Params& p, bool init, hipStream_t s);
+// `gens` (odd, at most kBlockGens) generations of the loop without selection.
+hipError_t launch_block(const RunDev* d_runs, const Params& p, const VaryLaunch& lc, int32_t gens,
+                        int32_t row_blocks, hipStream_t s);
 // Local search: sums of the stored target over each run's train and test cases.
 hipError_t launch_target_sums(const RunDev* d_runs, const Params& p, hipStream_t s);
 hipError_t launch_survive(const RunDev* d_runs, const Params& p, int32_t total_blocks, int mode,

@@ -984,6 +984,348 @@ __global__ __launch_bounds__(256) void k_survive(const RunDev* __restrict__ runs
 }
 
 // ---------------------------------------------------------------------------
+// Blocks of generations of the loop without selection (the paper's own loop:
+// every individual is mutated once a generation, Section 2.1 stage 5).
+//
+// Without tournaments the draws do not depend on the fitness, and an
+// individual's line crosses another one only where the elite copy overwrites
+// it.  So a wave takes one individual's chunk through all generations of a
+// block in registers (k_mutate_block), each generation's squared error sums
+// are combined for all of them (k_block_fitness), and the elite decisions are
+// then made step by step (k_block_elite): a copy gives individual dst another
+// line, which k_block_row follows through the rest of the block for that one
+// row, correcting its sums and its final values.  Values and sums are formed
+// by the operations, and in the order, of one generation at a time.
+//
+// What a generation must read and write falls from a parent, two pool rows
+// and an offspring row to the two pool rows, plus 1 / kBlockGens of the other
+// two: @BLOCK@.
+
+// One block step's fitness arrays: the table for steps inside the block, the
+// run's own arrays for its last one (and its start, step 0).
+__device__ __forceinline__ double* step_F(const RunDev& R, int m, int base, int gens, int step, bool test) {
+  if (step == 0 || step == gens) {
+    const int at = (base + step) & 1;
+    return test ? R.Ft[at] : R.F[at];
+  }
+  return R.block_F + ((int64_t)(test ? kBlockGens - 1 : 0) + (step - 1)) * m;
+}
+
+// The draws of steps 2 .. gens + 1 (step 1's were made with the generation
+// before it): what k_survive draws, one thread a record.
+__global__ __launch_bounds__(256) void k_block_draws(const RunDev* __restrict__ runs, Params p, int32_t gens,
+                                                     int64_t total) {
+  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= total) return;
+  const int64_t per_run = (int64_t)gens * p.m;
+  const int run = (int)(q / per_run);
+  const int64_t local = q - run * per_run;
+  const RunDev& R = runs[run];
+  const int g = R.state[kStGen] + 2 + (int)(local / p.m);
+  const int i = (int)(local % p.m);
+  if (local == 0) {
+    R.block->base = R.state[kStGen];
+    R.block->n = 0;
+    R.block->dst = -1;
+  }
+  if (g <= p.gmax)
+    R.rec[(int64_t)(g - 1) * p.m + i] = draw_record(p, R.run_id, g, i, [](int) { return 0.0; });
+}
+
+template <typename T, int PREC, bool FULL>
+__device__ __forceinline__ void mutate_block_task(const RunDev& R, const Params& p, const VaryLaunch& lc, int gens,
+                                                  int chunk, int grp, int lane, int wave) {
+  typedef typename VecOf<T>::type VT;
+  constexpr int N = VecOf<T>::N;
+  constexpr int kChunk = chunk_cases(sizeof(T));
+  constexpr int NJ = kChunk / (kWave * N);
+  const ChunkGeom g = chunk_geom(R.tr_pad, R.te_pad, R.nch_tr, chunk, kChunk);
+  const int64_t len = FULL ? (int64_t)kChunk : g.len;
+  const int gen = uni(cload(&R.state[kStGen]));
+  const int cur = gen & 1;
+  const T* Sc = (const T*)R.S[cur] + (int64_t)p.m * g.cs;
+  T* Oc = (T*)R.S[cur ^ 1] + (int64_t)p.m * g.cs;  // gens is odd
+  const T* gc = (const T*)R.sigR + (int64_t)p.r * g.cs;
+  const T* yv = (const T*)R.y + g.cs;
+  VT t[NJ];
+  bool ok[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int e = j * kWave * N + lane * N;
+    ok[j] = FULL || e < len;
+    t[j] = ok[j] ? gload<VT>(yv + e) : VT(0);
+  }
+  int i_end = (grp + 1) * lc.opb;
+  i_end = i_end < p.m ? i_end : p.m;
+  for (int i = grp * lc.opb + wave; i < i_end; i += lc.waves) {
+    VT x[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) x[j] = ok[j] ? gload<VT>(Sc + (int64_t)i * len + j * kWave * N + lane * N) : VT(0);
+    // a step's pool rows are read while the step before is worked on
+    auto read = [&](int s, T& ms, VT (&a)[NJ], VT (&b)[NJ]) {
+      const gsgp_record* rc = R.rec + (int64_t)(gen + s) * p.m + i;
+      const T* A = gc + (int64_t)uni(cload(&rc->r1)) * len;
+      const T* B = gc + (int64_t)uni(cload(&rc->r2)) * len;
+      ms = (T)cload(&rc->ms);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int e = j * kWave * N + lane * N;
+        a[j] = ok[j] ? gload<VT>(A + e) : VT(0);
+        b[j] = ok[j] ? gload<VT>(B + e) : VT(0);
+      }
+    };
+    auto step = [&](int s, T ms, const VT (&a)[NJ], const VT (&b)[NJ]) {
+      LaneSse<T, PREC> acc;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        VT v = x[j] + ms * (a[j] - b[j]);
+        if constexpr (PREC != GSGP_FP64) {
+#pragma unroll
+          for (int c = 0; c < N; ++c) v[c] = __builtin_amdgcn_fmed3f(v[c], (T)-kFltMax, (T)kFltMax);
+        }
+        x[j] = v;
+        if (ok[j]) acc.add(v, t[j]);
+      }
+      const double sse = sse_finish<T, PREC, NJ>(acc, ok, x, yv, lane);
+      if (lane == 0) R.part[((int64_t)s * R.nch + chunk) * p.m + i] = sse;
+    };
+    T ms0, ms1;
+    VT a0[NJ], b0[NJ], a1[NJ], b1[NJ];
+    read(0, ms0, a0, b0);
+    for (int s = 0;;) {
+      if (s + 1 < gens) read(s + 1, ms1, a1, b1);
+      step(s, ms0, a0, b0);
+      if (++s >= gens) break;
+      if (s + 1 < gens) read(s + 1, ms0, a0, b0);
+      step(s, ms1, a1, b1);
+      if (++s >= gens) break;
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      if (ok[j]) gstore_nt<VT>(x[j], Oc + (int64_t)i * len + j * kWave * N + lane * N);
+  }
+}
+
+// Task = (run, chunk, group of offspring) as in k_vary, same block order.
+template <typename T, int PREC>
+__global__ __launch_bounds__(512) void k_mutate_block(const RunDev* __restrict__ runs, Params p, VaryLaunch lc,
+                                                      int32_t gens) {
+  constexpr int kChunk = chunk_cases(sizeof(T));
+  const int lane = threadIdx.x & 63;
+  const int wave = uni(threadIdx.x >> 6);
+  const int64_t xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, per = lc.grid >> 3;
+  const int64_t task = lc.remap ? xcd * per + slot : (int64_t)blockIdx.x;
+  if (task >= lc.total_tasks) return;
+  const int run = find_run(p.n_runs, task, [&](int r) { return runs[r].vary_task0; });
+  const RunDev& R = runs[run];
+  const int64_t local = task - R.vary_task0;
+  const int chunk = (int)(local / lc.ogroups);
+  const int grp = (int)(local - (int64_t)chunk * lc.ogroups);
+  const ChunkGeom g = chunk_geom(R.tr_pad, R.te_pad, R.nch_tr, chunk, kChunk);
+  if (g.len == kChunk)
+    mutate_block_task<T, PREC, true>(R, p, lc, gens, chunk, grp, lane, wave);
+  else
+    mutate_block_task<T, PREC, false>(R, p, lc, gens, chunk, grp, lane, wave);
+}
+
+// k_fitness for every step of a block (grid.y), without the extremes.
+__global__ __launch_bounds__(kFitRanges * kFitGroup) void k_block_fitness(const RunDev* __restrict__ runs, Params p,
+                                                                           int32_t blocks_per_run, int32_t gens) {
+  __shared__ double sh_tr[kFitRanges][kFitGroup];
+  __shared__ double sh_te[kFitRanges][kFitGroup];
+  const int l = threadIdx.x % kFitGroup;
+  const int w = threadIdx.x / kFitGroup;
+  const int run = blockIdx.x / blocks_per_run;
+  const int i = (blockIdx.x - run * blocks_per_run) * kFitGroup + l;
+  const int step = blockIdx.y + 1;
+  const RunDev& R = runs[run];
+  const bool live = i < p.m;
+  const double* part = R.part + (int64_t)(step - 1) * R.nch * p.m + (live ? i : 0);
+  const int nt = R.nch_tr, ne = R.nch - R.nch_tr;
+  const int a0 = (int)((int64_t)nt * w / kFitRanges), a1 = (int)((int64_t)nt * (w + 1) / kFitRanges);
+  const int b0 = nt + (int)((int64_t)ne * w / kFitRanges), b1 = nt + (int)((int64_t)ne * (w + 1) / kFitRanges);
+  sh_tr[w][l] = sum_range(part, p.m, a0, a1);
+  sh_te[w][l] = sum_range(part, p.m, b0, b1);
+  __syncthreads();
+  if (threadIdx.x < kFitGroup && live) {
+    double s = sh_tr[0][l], st = sh_te[0][l];
+#pragma unroll
+    for (int q = 1; q < kFitRanges; ++q) {
+      s += sh_tr[q][l];
+      st += sh_te[q][l];
+    }
+    const int base = R.state[kStGen];
+    step_F(R, p.m, base, gens, step, false)[i] = sqrt(s / (double)R.n_train);
+    step_F(R, p.m, base, gens, step, true)[i] = R.n_test > 0 ? sqrt(st / (double)R.n_test) : 0.0;
+  }
+}
+
+// Survival of one step (k_survive's decision and summary), one block per run.
+// Fitness of the individuals that have left their line is formed again from
+// their corrected sums first, in k_fitness's order: a wave an individual,
+// lanes 0 .. 15 the ranges of the train chunks, 16 .. 31 of the test chunks.
+__global__ __launch_bounds__(1024) void k_block_elite(const RunDev* __restrict__ runs, Params p, int32_t gens,
+                                                      int32_t step) {
+  static_assert(kBlockGens <= 8, "a wave of the smallest block per individual that has left its line");
+  __shared__ ValIdx sh_lo[16], sh_hi[16];
+  const RunDev& R = runs[blockIdx.x];
+  BlockState& B = *R.block;
+  const int m = p.m, base = B.base, n = B.n;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double* F = step_F(R, m, base, gens, step, false);
+  double* Ft = step_F(R, m, base, gens, step, true);
+  if (wave < n) {
+    const int i = B.who[wave];
+    const double* part = R.part + (int64_t)(step - 1) * R.nch * m + i;
+    const int w = lane & 15;
+    const bool test = lane >= 16;
+    const int c0 = test ? R.nch_tr : 0, nc = test ? R.nch - R.nch_tr : R.nch_tr;
+    double s = 0.0;
+    if (lane < 32)
+      s = sum_range(part, m, c0 + (int)((int64_t)nc * w / kFitRanges), c0 + (int)((int64_t)nc * (w + 1) / kFitRanges));
+    double tr = __shfl(s, 0, kWave), te = __shfl(s, 16, kWave);
+    for (int q = 1; q < kFitRanges; ++q) {
+      tr += __shfl(s, q, kWave);
+      te += __shfl(s, 16 + q, kWave);
+    }
+    if (lane == 0) {
+      F[i] = sqrt(tr / (double)R.n_train);
+      Ft[i] = R.n_test > 0 ? sqrt(te / (double)R.n_test) : 0.0;
+    }
+  }
+  __syncthreads();
+  ValIdx lo{INFINITY, 0x7fffffff}, hi{-INFINITY, 0x7fffffff};
+  for (int i = threadIdx.x; i < m; i += blockDim.x) {
+    const ValIdx y{F[i], i};
+    lo = pick_min(lo, y);
+    hi = pick_max(hi, y);
+  }
+  lane_extrema<kWave>(lo, hi);
+  if (lane == 0) {
+    sh_lo[wave] = lo;
+    sh_hi[wave] = hi;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
+    lo = pick_min(lo, sh_lo[w]);
+    hi = pick_max(hi, sh_hi[w]);
+  }
+  // fitness is always finite; keep indices in range regardless
+  if (lo.i < 0 || lo.i >= m) lo.i = 0;
+  if (hi.i < 0 || hi.i >= m) hi.i = 0;
+  const gsgp_gen_stats before = R.stats[base + step - 1];
+  gsgp_gen_stats st;
+  st.elite_copied = before.best_train_rmse < lo.v;
+  st.elite_src = st.elite_copied ? before.best_index : -1;
+  st.elite_dst = st.elite_copied ? hi.i : -1;
+  if (st.elite_copied) {
+    const int src = st.elite_src, dst = st.elite_dst;
+    const double f = step_F(R, m, base, gens, step - 1, false)[src], ft = step_F(R, m, base, gens, step - 1, true)[src];
+    F[dst] = f;
+    Ft[dst] = ft;
+    st.best_train_rmse = f;
+    st.best_test_rmse = ft;
+    st.best_index = dst;
+    // dst's line from here on: src's up to the step before, the copy, its own
+    int from = -1, at = n;
+    for (int j = 0; j < n; ++j) {
+      if (B.who[j] == src) from = j;
+      if (B.who[j] == dst) at = j;
+    }
+    int line[kBlockGens + 1];
+    for (int s = 1; s < step; ++s) line[s] = from >= 0 ? B.by[from][s] : src;
+    const int root = from >= 0 ? B.root[from] : src;
+    for (int s = 1; s <= kBlockGens; ++s) B.by[at][s] = s < step ? line[s] : s == step ? -1 : dst;
+    B.root[at] = root;
+    B.who[at] = dst;
+    if (at == n) B.n = n + 1;
+    B.dst = at;
+  } else {
+    st.best_train_rmse = lo.v;
+    st.best_test_rmse = Ft[lo.i];
+    st.best_index = lo.i;
+    B.dst = -1;
+  }
+  R.stats[base + step] = st;
+  if (step == gens) R.state[kStGen] = base + gens;
+}
+
+// The rest of the block for the row that the step's copy overwrote: one wave
+// a chunk forms its values along its line, the squared error sums of the
+// steps after the copy, and its values at the end of the block.
+template <typename T, int PREC, bool FULL>
+__device__ __forceinline__ void block_row_chunk(const RunDev& R, const Params& p, int gens, int step, int chunk, int at,
+                                                int lane) {
+  typedef typename VecOf<T>::type VT;
+  constexpr int N = VecOf<T>::N;
+  constexpr int kChunk = chunk_cases(sizeof(T));
+  constexpr int NJ = kChunk / (kWave * N);
+  const BlockState& B = *R.block;
+  const int base = uni(B.base), dst = uni(B.who[at]), root = uni(B.root[at]);
+  const ChunkGeom g = chunk_geom(R.tr_pad, R.te_pad, R.nch_tr, chunk, kChunk);
+  const int64_t len = FULL ? (int64_t)kChunk : g.len;
+  const T* Sc = (const T*)R.S[base & 1] + (int64_t)p.m * g.cs + (int64_t)root * len;
+  T* Oc = (T*)R.S[(base & 1) ^ 1] + (int64_t)p.m * g.cs + (int64_t)dst * len;
+  const T* gc = (const T*)R.sigR + (int64_t)p.r * g.cs;
+  const T* yv = (const T*)R.y + g.cs;
+  VT x[NJ], t[NJ];
+  bool ok[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int e = j * kWave * N + lane * N;
+    ok[j] = FULL || e < len;
+    x[j] = ok[j] ? gload<VT>(Sc + e) : VT(0);
+    t[j] = ok[j] ? gload<VT>(yv + e) : VT(0);
+  }
+  for (int s = 1; s <= gens; ++s) {
+    const int by = uni(B.by[at][s]);
+    if (by < 0) continue;
+    const gsgp_record* rc = R.rec + (int64_t)(base + s - 1) * p.m + by;
+    const T* A = gc + (int64_t)uni(cload(&rc->r1)) * len;
+    const T* C = gc + (int64_t)uni(cload(&rc->r2)) * len;
+    const T ms = (T)cload(&rc->ms);
+    LaneSse<T, PREC> acc;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int e = j * kWave * N + lane * N;
+      const VT a = ok[j] ? gload<VT>(A + e) : VT(0), c = ok[j] ? gload<VT>(C + e) : VT(0);
+      VT v = x[j] + ms * (a - c);
+      if constexpr (PREC != GSGP_FP64) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) v[k] = __builtin_amdgcn_fmed3f(v[k], (T)-kFltMax, (T)kFltMax);
+      }
+      x[j] = v;
+      if (ok[j]) acc.add(v, t[j]);
+    }
+    if (s > step) {
+      const double sse = sse_finish<T, PREC, NJ>(acc, ok, x, yv, lane);
+      if (lane == 0) R.part[((int64_t)(s - 1) * R.nch + chunk) * p.m + dst] = sse;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+    if (ok[j]) gstore_nt<VT>(x[j], Oc + j * kWave * N + lane * N);
+}
+
+constexpr int kRowWaves = 4;
+
+template <typename T, int PREC>
+__global__ __launch_bounds__(kRowWaves * kWave) void k_block_row(const RunDev* __restrict__ runs, Params p, int32_t gens,
+                                                                  int32_t step) {
+  const int run = find_run(p.n_runs, (int64_t)blockIdx.x, [&](int r) { return (int64_t)runs[r].row_blk0; });
+  const RunDev& R = runs[run];
+  const int at = uni(R.block->dst);
+  const int chunk = (blockIdx.x - R.row_blk0) * kRowWaves + uni(threadIdx.x >> 6);
+  if (at < 0 || chunk >= R.nch) return;
+  const ChunkGeom g = chunk_geom(R.tr_pad, R.te_pad, R.nch_tr, chunk, chunk_cases(sizeof(T)));
+  if (g.len == chunk_cases(sizeof(T)))
+    block_row_chunk<T, PREC, true>(R, p, gens, step, chunk, at, threadIdx.x & 63);
+  else
+    block_row_chunk<T, PREC, false>(R, p, gens, step, chunk, at, threadIdx.x & 63);
+}
+
+// ---------------------------------------------------------------------------
 // Lineage reconstruction helpers (all FP64).
 __global__ __launch_bounds__(256) void k_transpose(const double* __restrict__ X, int64_t n, int32_t l,
                                                    double* __restrict__ Xfm, int64_t ld) {
@@ -1268,6 +1610,34 @@ hipError_t launch_fitness(const RunDev* d_runs, const Params& p, bool init, hipS
   else
     hipLaunchKernelGGL(k_fitness, grid, block, 0, s, d_runs, p, per_run, init ? 1 : 0);
   return hipGetLastError();
+}
+
+template <typename T, int PREC>
+hipError_t launch_block_as(const RunDev* d_runs, const Params& p, const VaryLaunch& lc, int32_t gens,
+                           int32_t row_blocks, hipStream_t s) {
+  const int64_t draws = (int64_t)p.n_runs * gens * p.m;
+  hipLaunchKernelGGL(k_block_draws, dim3(blocks_for(draws, 256)), dim3(256), 0, s, d_runs, p, gens, draws);
+  hipLaunchKernelGGL((k_mutate_block<T, PREC>), dim3((unsigned)lc.grid), dim3(lc.waves * kWave), 0, s, d_runs, p, lc, gens);
+  const int32_t per_run = (p.m + kFitGroup - 1) / kFitGroup;
+  hipLaunchKernelGGL(k_block_fitness, dim3((unsigned)(per_run * p.n_runs), (unsigned)gens), dim3(kFitRanges * kFitGroup),
+                     0, s, d_runs, p, per_run, gens);
+  hipError_t e = hipGetLastError();
+  for (int32_t step = 1; step <= gens && e == hipSuccess; ++step) {
+    hipLaunchKernelGGL(k_block_elite, dim3((unsigned)p.n_runs), dim3(p.m <= 2048 ? 512 : 1024), 0, s, d_runs, p, gens, step);
+    hipLaunchKernelGGL((k_block_row<T, PREC>), dim3((unsigned)row_blocks), dim3(kRowWaves * kWave), 0, s, d_runs, p, gens, step);
+    e = hipGetLastError();
+  }
+  return e;
+}
+
+hipError_t launch_block(const RunDev* d_runs, const Params& p, const VaryLaunch& lc, int32_t gens,
+                        int32_t row_blocks, hipStream_t s) {
+  if (gens < 1 || gens > kBlockGens || gens % 2 == 0) return hipErrorInvalidValue;
+  switch (p.precision) {
+    case GSGP_FP64: return launch_block_as<double, GSGP_FP64>(d_runs, p, lc, gens, row_blocks, s);
+    case GSGP_FP32: return launch_block_as<float, GSGP_FP32>(d_runs, p, lc, gens, row_blocks, s);
+    default: return launch_block_as<float, GSGP_FP32_KAHAN>(d_runs, p, lc, gens, row_blocks, s);
+  }
 }
 
 hipError_t launch_target_sums(const RunDev* d_runs, const Params& p, hipStream_t s) {

@@ -84,7 +84,7 @@ size_t storage_bytes(int32_t precision) { return precision == GSGP_FP64 ? 8 : 4;
 struct RunPlan {
   int64_t n_train, n_test, tr_pad, te_pad, ld;
   int32_t l, nch_tr, nch_te;
-  size_t X, y, S0, S1, sigR, part, F0, F1, Ft0, Ft1, extremes, rec, stats, elite_in, code, cval, ops, opv, opy, nops, need, lists;
+  size_t X, y, S0, S1, sigR, part, block_F, block, F0, F1, Ft0, Ft1, extremes, rec, stats, elite_in, code, cval, ops, opv, opy, nops, need, lists;
   size_t ls, tsum;
   size_t end;
 };
@@ -108,6 +108,13 @@ struct Plan {
 
 // Flags that change what a run computes (the others change only how).
 constexpr uint32_t kResultFlags = GSGP_FLAG_LOCAL_SEARCH;
+
+// Whether free runs of this configuration take blocks of generations (see
+// k_mutate_block): no selection, no scaling by the fit, and a population
+// whose fitness one block of threads scans in a few microseconds a step.
+bool in_blocks(const gsgp_config& c) {
+  return c.tournament_size == 0 && !(c.flags & GSGP_FLAG_LOCAL_SEARCH) && c.pop_size <= 65536;
+}
 
 gsgp_status validate_config(const gsgp_config* c) {
   if (!c) return fail(GSGP_ERR_ARG, "config is NULL");
@@ -190,8 +197,14 @@ gsgp_status make_plan(const gsgp_config* c, const gsgp_run* runs, int32_t n_runs
     p.S0 = take_at(s * m * p.ld, i, "S[0]");
     p.S1 = take_at(s * m * p.ld, i, "S[1]");
     p.sigR = take_at(s * r * p.ld, i, "sigmoid(S_R)");
-    // chunk partial sums: one per individual, three with local search
-    p.part = take_at(sizeof(double) * (p.nch_tr + p.nch_te) * m * (ls ? 3 : 1), i, "chunk partial sums");
+    // chunk partial sums: one per individual, three with local search, one a
+    // generation for blocks of generations, which keep their fitness table
+    // and state behind them
+    const size_t sums = sizeof(double) * (p.nch_tr + p.nch_te) * m * (ls ? 3 : in_blocks(*c) ? kBlockGens : 1);
+    const size_t table = in_blocks(*c) ? sizeof(double) * 2 * (kBlockGens - 1) * m : 0;
+    p.part = take_at(sums + table + (in_blocks(*c) ? sizeof(BlockState) : 0), i, "chunk partial sums");
+    p.block_F = p.part + sums;
+    p.block = p.block_F + table;
     p.F0 = take_at(8 * m, i, "F[0]");
     p.F1 = take_at(8 * m, i, "F[1]");
     p.Ft0 = take_at(8 * m, i, "Ft[0]");
@@ -234,6 +247,7 @@ struct gsgp_handle {
   int64_t interp_tasks = 0;  // interpreter case blocks over all runs
   int64_t interp_tasks_w = 0;  // wide interpreter case blocks over all runs
   int32_t surv_blocks = 0;
+  int32_t row_blocks = 0;      // blocks of the row kernel (four chunks each) over all runs
   int32_t slots = 1;         // interpreter stack values per lane in LDS
   int32_t max_blocks = 0;
   int32_t gen = 0;
@@ -243,6 +257,8 @@ struct gsgp_handle {
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph_k = nullptr;     // kGraphGens generations back to back
   hipGraphExec_t exec_k = nullptr;
+  hipGraph_t graph_b = nullptr;     // one block of kBlockGens generations
+  hipGraphExec_t exec_b = nullptr;
   int32_t* pinned = nullptr;  // read-back in mapped host memory: state words [n_runs][kStWords], or what a getter returns
   size_t pinned_bytes = 0;
   int device = 0;
@@ -315,6 +331,10 @@ void drop_graph(gsgp_handle* h) {
   if (h->graph) (void)hipGraphDestroy(h->graph);
   if (h->exec_k) (void)hipGraphExecDestroy(h->exec_k);
   if (h->graph_k) (void)hipGraphDestroy(h->graph_k);
+  if (h->exec_b) (void)hipGraphExecDestroy(h->exec_b);
+  if (h->graph_b) (void)hipGraphDestroy(h->graph_b);
+  h->exec_b = nullptr;
+  h->graph_b = nullptr;
   h->exec = nullptr;
   h->graph = nullptr;
   h->exec_k = nullptr;
@@ -396,10 +416,21 @@ hipError_t enqueue_generation(gsgp_handle* h, hipStream_t s) {
 // graph and 242.9 / 242.1 / 241.9 / 241.8 ms with 4 / 8 / 16 / 32.
 constexpr int32_t kGraphGens = 16;
 
-gsgp_status capture(gsgp_handle* h, int32_t n, hipGraph_t* graph, hipGraphExec_t* exec) {
+// A block of `gens` generations without selection, in the variation launch's
+// shape.
+hipError_t enqueue_block(gsgp_handle* h, int32_t gens, hipStream_t s) {
+  VaryLaunch lc = h->vary;
+  lc.remap = lc.remap ? 1 : 0;
+  lc.grid = lc.remap ? pad_to(lc.total_tasks, 8) : lc.total_tasks;
+  return launch_block(h->runs_d, h->params, lc, gens, h->row_blocks, s);
+}
+
+// Captures what `enqueue` launches, once.
+template <typename Enqueue>
+gsgp_status capture(gsgp_handle* h, hipGraph_t* graph, hipGraphExec_t* exec, Enqueue enqueue) {
+  if (*exec) return GSGP_OK;
   HIPCHK(h, hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
-  hipError_t e = hipSuccess;
-  for (int32_t i = 0; i < n && e == hipSuccess; ++i) e = enqueue_generation(h, h->cap_stream);
+  const hipError_t e = enqueue(h->cap_stream);
   hipGraph_t g = nullptr;
   hipError_t e2 = hipStreamEndCapture(h->cap_stream, &g);
   if (e != hipSuccess) return hip_fail(h, e, "capturing generations");
@@ -409,25 +440,38 @@ gsgp_status capture(gsgp_handle* h, int32_t n, hipGraph_t* graph, hipGraphExec_t
   return GSGP_OK;
 }
 
-gsgp_status ensure_graph(gsgp_handle* h) {
-  if (!h->exec) {
-    gsgp_status st = capture(h, 1, &h->graph, &h->exec);
-    if (st != GSGP_OK) return st;
-  }
-  if (!h->exec_k) return capture(h, kGraphGens, &h->graph_k, &h->exec_k);
-  return GSGP_OK;
-}
-
-gsgp_status run_generations(gsgp_handle* h, int32_t n_gens) {
+// n_gens generations; free_run: the draws and decisions are the device's own.
+gsgp_status run_generations(gsgp_handle* h, int32_t n_gens, bool free_run) {
   const bool graph = !(h->cfg.flags & GSGP_FLAG_NO_GRAPH);
+  int32_t left = n_gens;
+  // without selection: whole blocks, then an odd number (a block ends in the
+  // other population buffer), at most one generation by itself
+  while (free_run && in_blocks(h->cfg) && left >= 3) {
+    const int32_t gens = std::min(kBlockGens, left - (left % 2 == 0 ? 1 : 0));
+    if (graph && gens == kBlockGens) {
+      gsgp_status st = capture(h, &h->graph_b, &h->exec_b, [&](hipStream_t s) { return enqueue_block(h, kBlockGens, s); });
+      if (st != GSGP_OK) return st;
+      HIPCHK(h, hipGraphLaunch(h->exec_b, h->stream));
+    } else {
+      HIPCHK(h, enqueue_block(h, gens, h->stream));
+    }
+    left -= gens;
+  }
   if (graph) {
-    gsgp_status st = ensure_graph(h);
+    gsgp_status st = GSGP_OK;
+    if (left >= kGraphGens)
+      st = capture(h, &h->graph_k, &h->exec_k, [&](hipStream_t s) {
+        hipError_t e = hipSuccess;
+        for (int32_t i = 0; i < kGraphGens && e == hipSuccess; ++i) e = enqueue_generation(h, s);
+        return e;
+      });
+    if (st == GSGP_OK && left % kGraphGens)
+      st = capture(h, &h->graph, &h->exec, [&](hipStream_t s) { return enqueue_generation(h, s); });
     if (st != GSGP_OK) return st;
-    int32_t g = 0;
-    for (; g + kGraphGens <= n_gens; g += kGraphGens) HIPCHK(h, hipGraphLaunch(h->exec_k, h->stream));
-    for (; g < n_gens; ++g) HIPCHK(h, hipGraphLaunch(h->exec, h->stream));
+    for (; left >= kGraphGens; left -= kGraphGens) HIPCHK(h, hipGraphLaunch(h->exec_k, h->stream));
+    for (; left > 0; --left) HIPCHK(h, hipGraphLaunch(h->exec, h->stream));
   } else {
-    for (int32_t g = 0; g < n_gens; ++g) HIPCHK(h, enqueue_generation(h, h->stream));
+    for (; left > 0; --left) HIPCHK(h, enqueue_generation(h, h->stream));
   }
   h->gen += n_gens;
   return GSGP_OK;
@@ -578,6 +622,8 @@ gsgp_status gsgp_init(const gsgp_config* cfg, const gsgp_run* runs, int32_t n_ru
     R.y = ws + q.y;
     R.X = (double*)(ws + q.X);
     R.part = (double*)(ws + q.part);
+    R.block_F = (double*)(ws + q.block_F);
+    R.block = in_blocks(*cfg) ? (BlockState*)(ws + q.block) : nullptr;
     R.F[0] = (double*)(ws + q.F0);
     R.F[1] = (double*)(ws + q.F1);
     R.Ft[0] = (double*)(ws + q.Ft0);
@@ -613,6 +659,8 @@ gsgp_status gsgp_init(const gsgp_config* cfg, const gsgp_run* runs, int32_t n_ru
     itask += (q.ld + kInterpCases - 1) / kInterpCases;
     R.cblk0w = itask_w;
     itask_w += (q.ld + 4 * kWave - 1) / (4 * kWave);
+    R.row_blk0 = h->row_blocks;
+    h->row_blocks += (R.nch + 3) / 4;
     R.surv_blk0 = sblk;
     // survival blocks per run: each copies about 16 KiB of an elite row and
     // draws for at least 64 offspring, up to kSurvBlocks
@@ -821,7 +869,7 @@ static gsgp_status generation_body(gsgp_handle* h, int32_t n_gens, gsgp_gen_stat
   if ((int64_t)h->gen + n_gens > h->cfg.n_generations_max)
     return fail(GSGP_ERR_ARG, "generation %d + %d exceeds n_generations_max %d", h->gen, n_gens, h->cfg.n_generations_max);
   const int32_t g0 = h->gen;
-  st = run_generations(h, n_gens);
+  st = run_generations(h, n_gens, true);
   if (st != GSGP_OK) return st;
   if (h_stats) return copy_stats(h, 0, h->n_runs, g0 + 1, n_gens, h_stats);
   return GSGP_OK;
@@ -862,7 +910,7 @@ static gsgp_status generation_replay_body(gsgp_handle* h, int32_t n_gens, const 
   HIPCHK(h, hipStreamSynchronize(h->stream));
   HIPCHK(h, launch_set_state(h->runs_d, h->n_runs, kStReplaySelect, 1, h->stream));
   HIPCHK(h, launch_set_state(h->runs_d, h->n_runs, kStReplayElite, h_elite ? 1 : 0, h->stream));
-  st = run_generations(h, n_gens);
+  st = run_generations(h, n_gens, false);
   if (st != GSGP_OK) return st;
   HIPCHK(h, launch_set_state(h->runs_d, h->n_runs, kStReplaySelect, 0, h->stream));
   HIPCHK(h, launch_set_state(h->runs_d, h->n_runs, kStReplayElite, 0, h->stream));
