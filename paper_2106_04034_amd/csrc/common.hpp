@@ -110,7 +110,7 @@ struct Extremes {
 // its values are then those of generation-0-of-the-block individual `root`,
 // taken through the recorded mutations of individual by[s] at step s (-1: the
 // copy itself, nothing applied).
-constexpr int kBlockGens = 7;
+constexpr int kBlockGens = 15;
 struct BlockState {
   int32_t base;                  // generation the block started from
   int32_t n;                     // individuals that have left their line
@@ -128,7 +128,7 @@ struct RunDev {
   double* X;                // features in case tiles, [ceil(ld / kXTile)][l][kXTile], zero pads
   double* part;             // chunk partial sums of squared residuals, [nch][m]; with local
                             // search the generation's sums of o, o^2 and o * t, [nch][3][m];
-                            // for blocks of generations [kBlockGens][nch][m]
+                            // for blocks of generations [generations a block][nch][m]
   double* F[2];             // train RMSE ping-pong, [m]
   double* Ft[2];            // test RMSE ping-pong, [m]
   Extremes* extremes;       // of the newest fitness, [ceil(m / kFitGroup)]

@@ -997,9 +997,20 @@ __global__ __launch_bounds__(256) void k_survive(const RunDev* __restrict__ runs
 // row, correcting its sums and its final values.  Values and sums are formed
 // by the operations, and in the order, of one generation at a time.
 //
-// What a generation must read and write falls from a parent, two pool rows
-// and an offspring row to the two pool rows, plus 1 / kBlockGens of the other
-// two: @BLOCK@.
+// What a generation reads and writes falls from a parent, two pool rows and an
+// offspring row to the two pool rows, which mostly come from the caches, plus
+// one in 7 or 15 of the other two.  Per generation, one at a time -> 7 -> 15 a
+// block: 10,240 individuals on 102,400 FP32 cases 2,233 -> 1,104 -> 1,006 us (a
+// chunk's pool column is 20 MB, so most of its reads leave the XCD's L2: 8.3
+// TB/s of pool rows); 4,000 on 30,000 185 -> 104 -> 93 us; 2,048 on 10,240
+// 58 -> 25.8 -> 25.4 us; 600 on 2,000 23 -> 11.9 -> 13.8 us; 128 on 500 (FP64)
+// 23 -> 11.0 -> 12.6 us.
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const int64_t b = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
 
 // One block step's fitness arrays: the table for steps inside the block, the
 // run's own arrays for its last one (and its start, step 0).
@@ -1166,7 +1177,6 @@ __global__ __launch_bounds__(kFitRanges * kFitGroup) void k_block_fitness(const 
 // lanes 0 .. 15 the ranges of the train chunks, 16 .. 31 of the test chunks.
 __global__ __launch_bounds__(1024) void k_block_elite(const RunDev* __restrict__ runs, Params p, int32_t gens,
                                                       int32_t step) {
-  static_assert(kBlockGens <= 8, "a wave of the smallest block per individual that has left its line");
   __shared__ ValIdx sh_lo[16], sh_hi[16];
   const RunDev& R = runs[blockIdx.x];
   BlockState& B = *R.block;
@@ -1174,8 +1184,8 @@ __global__ __launch_bounds__(1024) void k_block_elite(const RunDev* __restrict__
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double* F = step_F(R, m, base, gens, step, false);
   double* Ft = step_F(R, m, base, gens, step, true);
-  if (wave < n) {
-    const int i = B.who[wave];
+  for (int j = wave; j < n; j += (int)(blockDim.x >> 6)) {
+    const int i = B.who[j];
     const double* part = R.part + (int64_t)(step - 1) * R.nch * m + i;
     const int w = lane & 15;
     const bool test = lane >= 16;
@@ -1183,10 +1193,11 @@ __global__ __launch_bounds__(1024) void k_block_elite(const RunDev* __restrict__
     double s = 0.0;
     if (lane < 32)
       s = sum_range(part, m, c0 + (int)((int64_t)nc * w / kFitRanges), c0 + (int)((int64_t)nc * (w + 1) / kFitRanges));
-    double tr = __shfl(s, 0, kWave), te = __shfl(s, 16, kWave);
+    double tr = lane_value(s, 0), te = lane_value(s, 16);
+#pragma unroll
     for (int q = 1; q < kFitRanges; ++q) {
-      tr += __shfl(s, q, kWave);
-      te += __shfl(s, 16 + q, kWave);
+      tr += lane_value(s, q);
+      te += lane_value(s, 16 + q);
     }
     if (lane == 0) {
       F[i] = sqrt(tr / (double)R.n_train);
@@ -1206,49 +1217,48 @@ __global__ __launch_bounds__(1024) void k_block_elite(const RunDev* __restrict__
     sh_hi[wave] = hi;
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
-    lo = pick_min(lo, sh_lo[w]);
-    hi = pick_max(hi, sh_hi[w]);
+  if (wave != 0) return;
+  const int q = lane & 15;
+  if (q < (int)(blockDim.x >> 6)) {
+    lo = sh_lo[q];
+    hi = sh_hi[q];
   }
+  lane_extrema<16>(lo, hi);  // idle lanes hold wave 0's own
   // fitness is always finite; keep indices in range regardless
   if (lo.i < 0 || lo.i >= m) lo.i = 0;
   if (hi.i < 0 || hi.i >= m) hi.i = 0;
   const gsgp_gen_stats before = R.stats[base + step - 1];
-  gsgp_gen_stats st;
-  st.elite_copied = before.best_train_rmse < lo.v;
-  st.elite_src = st.elite_copied ? before.best_index : -1;
-  st.elite_dst = st.elite_copied ? hi.i : -1;
-  if (st.elite_copied) {
-    const int src = st.elite_src, dst = st.elite_dst;
-    const double f = step_F(R, m, base, gens, step - 1, false)[src], ft = step_F(R, m, base, gens, step - 1, true)[src];
-    F[dst] = f;
-    Ft[dst] = ft;
-    st.best_train_rmse = f;
-    st.best_test_rmse = ft;
+  const int src = uni(before.best_index), dst = uni(hi.i);
+  const bool copied = before.best_train_rmse < lo.v;
+  gsgp_gen_stats st{lo.v, 0.0, lo.i, copied, copied ? src : -1, copied ? dst : -1};
+  int at = -1;
+  if (copied) {
+    st.best_train_rmse = step_F(R, m, base, gens, step - 1, false)[src];
+    st.best_test_rmse = step_F(R, m, base, gens, step - 1, true)[src];
     st.best_index = dst;
     // dst's line from here on: src's up to the step before, the copy, its own
-    int from = -1, at = n;
-    for (int j = 0; j < n; ++j) {
-      if (B.who[j] == src) from = j;
-      if (B.who[j] == dst) at = j;
-    }
-    int line[kBlockGens + 1];
-    for (int s = 1; s < step; ++s) line[s] = from >= 0 ? B.by[from][s] : src;
+    const int who = lane < n ? B.who[lane] : -1;
+    const uint64_t is_src = __builtin_amdgcn_ballot_w64(who == src), is_dst = __builtin_amdgcn_ballot_w64(who == dst);
+    const int from = is_src ? __builtin_ctzll(is_src) : -1;
+    at = is_dst ? __builtin_ctzll(is_dst) : n;
     const int root = from >= 0 ? B.root[from] : src;
-    for (int s = 1; s <= kBlockGens; ++s) B.by[at][s] = s < step ? line[s] : s == step ? -1 : dst;
-    B.root[at] = root;
-    B.who[at] = dst;
-    if (at == n) B.n = n + 1;
-    B.dst = at;
+    if (lane >= 1 && lane <= kBlockGens)
+      B.by[at][lane] = lane < step ? (from >= 0 ? B.by[from][lane] : src) : lane == step ? -1 : dst;
+    if (lane == 0) {
+      F[dst] = st.best_train_rmse;
+      Ft[dst] = st.best_test_rmse;
+      B.root[at] = root;
+      B.who[at] = dst;
+      if (at == n) B.n = n + 1;
+    }
   } else {
-    st.best_train_rmse = lo.v;
     st.best_test_rmse = Ft[lo.i];
-    st.best_index = lo.i;
-    B.dst = -1;
   }
-  R.stats[base + step] = st;
-  if (step == gens) R.state[kStGen] = base + gens;
+  if (lane == 0) {
+    B.dst = at;
+    R.stats[base + step] = st;
+    if (step == gens) R.state[kStGen] = base + gens;
+  }
 }
 
 // The rest of the block for the row that the step's copy overwrote: one wave

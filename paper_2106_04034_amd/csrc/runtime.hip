@@ -102,6 +102,7 @@ struct Guard {
 
 struct Plan {
   size_t runs_dev, src_ptrs, state, spill, spill_bytes, total;
+  int32_t block_gens;  // generations a block, 0: one at a time
   std::vector<RunPlan> runs;
   std::vector<Guard> guards;
 };
@@ -109,11 +110,19 @@ struct Plan {
 // Flags that change what a run computes (the others change only how).
 constexpr uint32_t kResultFlags = GSGP_FLAG_LOCAL_SEARCH;
 
-// Whether free runs of this configuration take blocks of generations (see
-// k_mutate_block): no selection, no scaling by the fit, and a population
-// whose fitness one block of threads scans in a few microseconds a step.
-bool in_blocks(const gsgp_config& c) {
-  return c.tournament_size == 0 && !(c.flags & GSGP_FLAG_LOCAL_SEARCH) && c.pop_size <= 65536;
+// Generations a block that free runs of this configuration take (see
+// k_mutate_block), 0 for one at a time: blocks need a loop without selection
+// and without scaling by the fit, and a population whose fitness one block of
+// threads scans in a few microseconds a step.  A longer block reads and writes
+// the population less often, a shorter one has fewer rows to follow after
+// elite copies: they meet at 2e7 values a generation (2,048 individuals on
+// 10,240 cases 25.8 us with 7, 25.4 with 15; 4,000 on 30,000 104 and 93; 600 on
+// 2,000 11.9 and 13.8).
+int32_t block_gens(const gsgp_config& c, const gsgp_run* runs, int32_t n_runs) {
+  if (c.tournament_size != 0 || (c.flags & GSGP_FLAG_LOCAL_SEARCH) || c.pop_size > 65536) return 0;
+  double values = 0;
+  for (int32_t i = 0; i < n_runs; ++i) values += (double)c.pop_size * (double)(runs[i].n_train + runs[i].n_test);
+  return values >= 2e7 ? kBlockGens : 7;
 }
 
 gsgp_status validate_config(const gsgp_config* c) {
@@ -152,6 +161,8 @@ gsgp_status make_plan(const gsgp_config* c, const gsgp_run* runs, int32_t n_runs
   const bool guarded = (c->flags & GSGP_FLAG_GUARDS) != 0;
   const bool ls = (c->flags & GSGP_FLAG_LOCAL_SEARCH) != 0;
   plan->guards.clear();
+  plan->block_gens = block_gens(*c, runs, n_runs);
+  const int32_t bg = plan->block_gens;
   size_t off = 0;
   // reserves `bytes` at the next aligned offset, plus a guard when asked
   auto take_at = [&](size_t bytes, int32_t run, const char* name) {
@@ -200,9 +211,9 @@ gsgp_status make_plan(const gsgp_config* c, const gsgp_run* runs, int32_t n_runs
     // chunk partial sums: one per individual, three with local search, one a
     // generation for blocks of generations, which keep their fitness table
     // and state behind them
-    const size_t sums = sizeof(double) * (p.nch_tr + p.nch_te) * m * (ls ? 3 : in_blocks(*c) ? kBlockGens : 1);
-    const size_t table = in_blocks(*c) ? sizeof(double) * 2 * (kBlockGens - 1) * m : 0;
-    p.part = take_at(sums + table + (in_blocks(*c) ? sizeof(BlockState) : 0), i, "chunk partial sums");
+    const size_t sums = sizeof(double) * (p.nch_tr + p.nch_te) * m * (ls ? 3 : bg ? bg : 1);
+    const size_t table = bg ? sizeof(double) * 2 * (kBlockGens - 1) * m : 0;
+    p.part = take_at(sums + table + (bg ? sizeof(BlockState) : 0), i, "chunk partial sums");
     p.block_F = p.part + sums;
     p.block = p.block_F + table;
     p.F0 = take_at(8 * m, i, "F[0]");
@@ -257,7 +268,7 @@ struct gsgp_handle {
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph_k = nullptr;     // kGraphGens generations back to back
   hipGraphExec_t exec_k = nullptr;
-  hipGraph_t graph_b = nullptr;     // one block of kBlockGens generations
+  hipGraph_t graph_b = nullptr;     // one whole block of generations
   hipGraphExec_t exec_b = nullptr;
   int32_t* pinned = nullptr;  // read-back in mapped host memory: state words [n_runs][kStWords], or what a getter returns
   size_t pinned_bytes = 0;
@@ -446,10 +457,11 @@ gsgp_status run_generations(gsgp_handle* h, int32_t n_gens, bool free_run) {
   int32_t left = n_gens;
   // without selection: whole blocks, then an odd number (a block ends in the
   // other population buffer), at most one generation by itself
-  while (free_run && in_blocks(h->cfg) && left >= 3) {
-    const int32_t gens = std::min(kBlockGens, left - (left % 2 == 0 ? 1 : 0));
-    if (graph && gens == kBlockGens) {
-      gsgp_status st = capture(h, &h->graph_b, &h->exec_b, [&](hipStream_t s) { return enqueue_block(h, kBlockGens, s); });
+  const int32_t most = h->plan.block_gens;
+  while (free_run && most && left >= 3) {
+    const int32_t gens = std::min(most, left - (left % 2 == 0 ? 1 : 0));
+    if (graph && gens == most) {
+      gsgp_status st = capture(h, &h->graph_b, &h->exec_b, [&](hipStream_t s) { return enqueue_block(h, most, s); });
       if (st != GSGP_OK) return st;
       HIPCHK(h, hipGraphLaunch(h->exec_b, h->stream));
     } else {
@@ -623,7 +635,7 @@ gsgp_status gsgp_init(const gsgp_config* cfg, const gsgp_run* runs, int32_t n_ru
     R.X = (double*)(ws + q.X);
     R.part = (double*)(ws + q.part);
     R.block_F = (double*)(ws + q.block_F);
-    R.block = in_blocks(*cfg) ? (BlockState*)(ws + q.block) : nullptr;
+    R.block = plan.block_gens ? (BlockState*)(ws + q.block) : nullptr;
     R.F[0] = (double*)(ws + q.F0);
     R.F[1] = (double*)(ws + q.F1);
     R.Ft[0] = (double*)(ws + q.Ft0);

@@ -35,7 +35,7 @@ def _same(A, B, runs, gens):
 @pytest.mark.parametrize("precision", ["fp32", "fp32_kahan", "fp64"])
 @pytest.mark.parametrize("m,r,n_train,n_test,step", [
     (1, 1, 70, 0, 0.1), (2, 3, 513, 64, 50.0), (3, 5, 1500, 300, 5.0), (17, 9, 64, 7, 2.0), (130, 40, 2048, 513, 0.5),
-    (2100, 64, 300, 0, 3.0)])
+    (2100, 64, 300, 0, 3.0), (20000, 10, 900, 150, 3.0)])
 def test_blocks_equal_single_generations(m, r, n_train, n_test, step, precision):
     gens = 7 + 5 + 4 + 16 + 2
     d = dataset(n_train, n_test, 3, seed=m)
@@ -43,7 +43,7 @@ def test_blocks_equal_single_generations(m, r, n_train, n_test, step, precision)
     A, B = gsgp.Runner(s, [d]), gsgp.Runner(s, [d])
     A.eval_population()
     B.eval_population()
-    for n in (7, 5, 4, 16, 2):  # 7; 5; 3 + 1; 7 + 7 + 1 + 1; 1 + 1
+    for n in (7, 5, 4, 16, 2):  # blocks of up to 7 (15 from 2e7 values on) and single ones
         A.generation(n, stats=False)
     for g in range(gens):
         B.generation(1, stats=False)
