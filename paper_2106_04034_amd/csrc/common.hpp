@@ -37,9 +37,10 @@ __host__ __device__ constexpr int64_t x_index(int64_t c, int64_t f, int64_t l) {
   return ((c / kXTile) * l + f) * kXTile + c % kXTile;
 }
 constexpr int kMaxTournament = 64;
-// The interpreter keeps the top two stack values in registers and the rest
-// (depth - 2 values per lane) in a lane-strided column: in LDS up to this
-// many values (63 x 2 cases x 64 lanes x 8 B = 63 KiB, one wave per block),
+// The interpreter of the deep programs keeps the top two stack values in
+// registers and the rest (depth - 2 values per lane) in a lane-strided column:
+// in LDS up to this many values (63 x 2 cases x 64 lanes x 8 B = 63 KiB, one
+// wave per block),
 // beyond it in a global-memory region of the workspace that a spill pass of
 // kSpillWaves waves shares, one column per wave.
 constexpr int kMaxLdsSlots = 63;
@@ -47,37 +48,50 @@ constexpr int kSpillWaves = 128;
 // Stack values below the top two that a genome of k genes can need: its
 // deepest stack up to its last valid function is at most k - 1 values.
 constexpr int64_t max_need(int64_t k) { return k > 3 ? k - 3 : 0; }
-// The interpreter runs in passes by stack need (LDS values per lane below
-// the two stack values kept in registers), each with the smallest LDS
-// column that holds its programs, so that a CU keeps as many waves resident
-// as the column allows: the compile step files each run's programs into
-// kLists lists; list b < kLists - 1 holds the programs whose need lies in
-// (kListSlots[b - 1], kListSlots[b]] (list 0: need <= kListSlots[0]); the
-// last list holds every deeper program (two-cases-per-lane passes with
-// columns up to kMaxLdsSlots, then the spill pass).
+// The compile step files each run's programs into kLists lists by stack need
+// (values below the top two), so that a CU keeps as many waves resident as the
+// programs' LDS columns allow: list b < kLists - 1 holds the programs whose
+// need lies in (kListSlots[b - 1], kListSlots[b]] (list 0: need <=
+// kListSlots[0]).  Those lists' interpreter keeps one value more in registers:
+// list 0 needs no LDS (82 % of random programs of 127 genes, 22 % of 1,023),
+// the others 2, 4 and 8 KiB a wave.  The last list holds every deeper program
+// (two-cases-per-lane passes with columns up to kMaxLdsSlots, then the spill
+// pass): 0.3 % at 127 genes, 1.3 % at 2,047.
 constexpr int kLists = 5;
-constexpr int kListSlots[kLists - 1] = {2, 3, 4, 6};
+constexpr int kListSlots[kLists - 1] = {1, 2, 3, 5};
 __host__ __device__ constexpr int list_of(int need) {
-  return need <= 2 ? 0 : need == 3 ? 1 : need == 4 ? 2 : need <= 6 ? 3 : 4;
+  return need <= 1 ? 0 : need == 2 ? 1 : need == 3 ? 2 : need <= 5 ? 3 : 4;
 }
 static_assert(list_of(kListSlots[0]) == 0 && list_of(kListSlots[1]) == 1 && list_of(kListSlots[2]) == 2 &&
                   list_of(kListSlots[3]) == 3 && list_of(kListSlots[3] + 1) == kLists - 1,
               "list_of must follow kListSlots");
-// The interpreter reads a program's ops eight at a time; the compiled-op
-// buffers carry this many entries of padding after the last program.
-constexpr int kOpPad = 8;
-
-// Compiled genome op word:
+// A compiled op.  `word`:
 //   bits 0..1   the function (OpFn), or for a push which terminal (OpPush);
 //   bits 2..3   the class (OpClass);
 //   bits 4..15  stack depth before the op (values, top included);
 //   bits 16..31 feature index.
 // A push directly followed by a function it feeds is compiled into one op
 // (kClsFeature / kClsConst) that applies the function to the top of the
-// stack and the terminal, leaving the rest of the stack untouched.  The op's
-// constant slot holds the constant of a constant op and, for a feature op,
-// the bits of the absolute address of the feature's row in the run's X.  The
-// word after a program's last op is an end word (push class, bit 1 set).
+// stack and the terminal, leaving the rest of the stack untouched.  `value`
+// holds the constant of a constant op and, for an op that uses a feature, the
+// bits of the byte offset, in a tile of X, of the row that the next such op
+// uses (0 for the last one).  A program's first entry is no op: its `value` is
+// the first such row.  The op after a program's last one is an end word (push
+// class, bit 1 set).  `code` is the byte offset of the op's handler in
+// eval_program_threaded's table.
+struct CompiledOp {
+  int32_t code, word;
+  double value;
+};
+static_assert(sizeof(CompiledOp) == 16, "four ops a 64-byte line");
+// The interpreters read a program's ops eight at a time, up to two batches
+// ahead: programs start on a multiple of four ops (op_stride), and kOpTail
+// entries follow the last program.
+constexpr int kOpPad = 8;
+constexpr int kOpTail = 3 * kOpPad;
+// the header, at most k - 1 ops and the end word
+__host__ __device__ constexpr int64_t op_stride(int64_t k) { return (k + 1 + 3) / 4 * 4; }
+
 enum OpClass : int32_t { kClsPush = 0, kClsStack = 1, kClsFeature = 2, kClsConst = 3 };
 enum OpFn : int32_t { kFnAdd = 0, kFnSub = 1, kFnMul = 2, kFnDiv = 3 };
 enum OpPush : int32_t { kPushFeature = 0, kPushConst = 1 };
@@ -139,12 +153,10 @@ struct RunDev {
   gsgp_gen_stats* elite_in; // supplied survival decisions, [gmax]
   int32_t* code;            // genomes, [m + r][k]
   double* cval;             // [m + r][k]
-  int32_t* ops;             // compiled genomes, [m + r][k] + kOpPad
-  double* opv;              // [m + r][k] + kOpPad
-  double* opy;              // per compiled op: a constant divisor's refined reciprocal, else 0, [m + r][k] + kOpPad
+  CompiledOp* ops;          // compiled genomes, [m + r][op_stride(k)] + kOpTail
   int32_t* nops;            // [m + r]
   int32_t* need;            // LDS stack values per lane each program needs, [m + r]
-  int32_t* lists;           // programs by stack need, [kLists][m + r] (counts in kStList0 ..)
+  int32_t* lists;           // programs list by list, [m + r] (counts in kStList0 ..)
   int32_t* state;           // [kStWords]
   double* ls;               // local search: (alpha, beta) of every individual, [gmax + 1][m][2]
   double* tsum;             // local search: sum t and sum t^2 over train, then over test cases
@@ -233,17 +245,16 @@ hipError_t launch_set_state(const RunDev* d_runs, int32_t n_runs, int32_t word, 
 hipError_t launch_reset_state(const RunDev* d_runs, int32_t n_runs, hipStream_t s);
 hipError_t launch_genome(const RunDev* d_runs, const Params& p, hipStream_t s);
 hipError_t launch_compile(const RunDev* d_runs, const Params& p, hipStream_t s);
-// Interpreter passes: each takes the programs of stack-need list `list` (at
-// most `progs` per run) with lo < need <= slots.  launch_interpret: two
-// cases per lane, any slots up to kMaxLdsSlots, case_blocks blocks of
-// kInterpCases cases; launch_interpret_wide: list < kLists - 1, whose
-// programs need at most kListSlots[list] values, two or four cases per lane
-// (blocks of kInterpCases or kXTile cases over all runs: blocks128,
-// blocks256).
-hipError_t launch_interpret(const RunDev* d_runs, const Params& p, int64_t case_blocks, int lo, int slots,
-                            int list, int32_t progs, hipStream_t s);
-hipError_t launch_interpret_wide(const RunDev* d_runs, const Params& p, int64_t blocks256, int64_t blocks128, int lo,
-                                 int list, int32_t progs, hipStream_t s);
+// Interpreter passes.  launch_interpret_wide: the programs of the stack-need
+// lists first .. last (< kLists - 1; at most `progs` per run together), four
+// cases per lane, case_blocks blocks of kXTile cases over all runs; a wave takes
+// per_wave (<= 32) programs one after the other on its block.
+// launch_interpret: the last list's programs with a need of at most `slots`
+// (<= kMaxLdsSlots), two cases per lane, blocks of kInterpCases cases.
+hipError_t launch_interpret_wide(const RunDev* d_runs, const Params& p, int64_t case_blocks, int first, int last,
+                                 int64_t progs, int32_t per_wave, hipStream_t s);
+hipError_t launch_interpret(const RunDev* d_runs, const Params& p, int64_t case_blocks, int slots, int32_t progs,
+                            hipStream_t s);
 // Last pass: every program of the last list whose need exceeds kMaxLdsSlots,
 // with its stack in `spill` (kSpillWaves columns of slots x 2 x 64 doubles).
 hipError_t launch_interpret_spill(const RunDev* d_runs, const Params& p, double* spill, int slots,
@@ -268,7 +279,7 @@ hipError_t launch_fetch_pair(const double* a, const double* b, int32_t n, double
 // Reconstruction helpers.
 hipError_t launch_transpose(const double* X, int64_t n, int32_t l, double* Xfm, int64_t ld,
                             hipStream_t s);
-hipError_t launch_interpret_list(const int32_t* ops, const double* opv, const int32_t* nops,
+hipError_t launch_interpret_list(const CompiledOp* ops, const int32_t* nops,
                                  int32_t k, const int32_t* prog, const int32_t* squash,
                                  int32_t nprog, const double* Xfm, int64_t ld, int64_t n,
                                  double* out, int slots, double* spill, hipStream_t s);

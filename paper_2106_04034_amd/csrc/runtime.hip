@@ -84,7 +84,7 @@ size_t storage_bytes(int32_t precision) { return precision == GSGP_FP64 ? 8 : 4;
 struct RunPlan {
   int64_t n_train, n_test, tr_pad, te_pad, ld;
   int32_t l, nch_tr, nch_te;
-  size_t X, y, S0, S1, sigR, part, block_F, block, F0, F1, Ft0, Ft1, extremes, rec, stats, elite_in, code, cval, ops, opv, opy, nops, need, lists;
+  size_t X, y, S0, S1, sigR, part, block_F, block, F0, F1, Ft0, Ft1, extremes, rec, stats, elite_in, code, cval, ops, nops, need, lists;
   size_t ls, tsum;
   size_t end;
 };
@@ -209,30 +209,27 @@ gsgp_status make_plan(const gsgp_config* c, const gsgp_run* runs, int32_t n_runs
     p.S1 = take_at(s * m * p.ld, i, "S[1]");
     p.sigR = take_at(s * r * p.ld, i, "sigmoid(S_R)");
     // chunk partial sums: one per individual, three with local search, one a
-    // generation for blocks of generations, which keep their fitness table
-    // and state behind them
+    // generation for blocks of generations
     const size_t sums = sizeof(double) * (p.nch_tr + p.nch_te) * m * (ls ? 3 : bg ? bg : 1);
     const size_t table = bg ? sizeof(double) * 2 * (kBlockGens - 1) * m : 0;
-    p.part = take_at(sums + table + (bg ? sizeof(BlockState) : 0), i, "chunk partial sums");
-    p.block_F = p.part + sums;
+    p.part = take_at(sums, i, "chunk partial sums");
+    // blocks of generations: fitness of the steps inside a block, and its state
+    p.block_F = take_at(table + (bg ? sizeof(BlockState) : 0), i, "block of generations");
     p.block = p.block_F + table;
     p.F0 = take_at(8 * m, i, "F[0]");
     p.F1 = take_at(8 * m, i, "F[1]");
     p.Ft0 = take_at(8 * m, i, "Ft[0]");
-    // Ft[1] and, behind it, the fitness extremes of every group
-    p.Ft1 = take_at(8 * m + sizeof(Extremes) * ((m + kFitGroup - 1) / kFitGroup), i, "Ft[1]");
-    p.extremes = p.Ft1 + 8 * m;
+    p.Ft1 = take_at(8 * m, i, "Ft[1]");
+    p.extremes = take_at(sizeof(Extremes) * ((m + kFitGroup - 1) / kFitGroup), i, "fitness extremes");
     p.rec = take_at(sizeof(gsgp_record) * G * m, i, "variation records");
     p.stats = take_at(sizeof(gsgp_gen_stats) * (G + 1), i, "summaries");
     p.elite_in = take_at(sizeof(gsgp_gen_stats) * G, i, "supplied survival decisions");
     p.code = take_at(4 * (m + r) * k, i, "genome codes");
     p.cval = take_at(8 * (m + r) * k, i, "genome constants");
-    p.ops = take_at(4 * ((m + r) * k + kOpPad), i, "compiled ops");
-    p.opv = take_at(8 * ((m + r) * k + kOpPad), i, "compiled constants");
-    p.opy = take_at(8 * ((m + r) * k + kOpPad), i, "compiled reciprocals");
+    p.ops = take_at(sizeof(CompiledOp) * ((m + r) * op_stride(k) + kOpTail), i, "compiled ops");
     p.nops = take_at(4 * (m + r), i, "program lengths");
     p.need = take_at(4 * (m + r), i, "program stack needs");
-    p.lists = take_at(4 * kLists * (m + r), i, "program lists by stack need");
+    p.lists = take_at(4 * (m + r), i, "program lists by stack need");
     // local search: the scaling table of every generation and the target sums
     p.ls = take_at(ls ? sizeof(double) * 2 * (G + 1) * m : 0, i, "scaling table");
     p.tsum = take_at(ls ? sizeof(double) * 4 : 0, i, "target sums");
@@ -646,9 +643,7 @@ gsgp_status gsgp_init(const gsgp_config* cfg, const gsgp_run* runs, int32_t n_ru
     R.elite_in = (gsgp_gen_stats*)(ws + q.elite_in);
     R.code = (int32_t*)(ws + q.code);
     R.cval = (double*)(ws + q.cval);
-    R.ops = (int32_t*)(ws + q.ops);
-    R.opv = (double*)(ws + q.opv);
-    R.opy = (double*)(ws + q.opy);
+    R.ops = (CompiledOp*)(ws + q.ops);
     R.nops = (int32_t*)(ws + q.nops);
     R.need = (int32_t*)(ws + q.need);
     R.lists = (int32_t*)(ws + q.lists);
@@ -753,22 +748,35 @@ gsgp_status gsgp_destroy(gsgp_handle* h) {
 
 namespace {
 
-// ComputeSemantics of every compiled program, in one pass per stack-need
-// list, each with the smallest LDS column that holds its programs (more
-// resident waves for the shallow lists): the first kLists - 1 lists with the
-// wide kernel, then the last list with columns up to kMaxLdsSlots, then the
-// programs beyond any LDS column (spill stacks).  counts[b]: the longest
-// list b over the runs.
+// From this many (program, case block) tasks on, the programs that need no LDS
+// column run by themselves (more resident waves), two to a wave; below it all
+// lists but the last share one launch (its LDS column is the largest one's,
+// but every launch of a list alone ends on a few long programs).  In one, in
+// two launches, ms with one program a wave / two: 1,536 tasks (500 FP64 cases)
+// 0.054 / 0.069, 0.070 / 0.101; 51,000 (5,000 cases) 0.201 / 0.201, 0.197 /
+// 0.218; 164,000 of 1,023 genes 2.06 / 2.03, 2.06 / 2.18; 1.0 million (125,000
+// cases) 1.74 / 1.65, 1.61 / 1.62; 10 million 15.6 / 14.9, 14.9 / 14.6; 8 million on
+// 1,024 features 13.2 / 12.6, 12.8 / 12.4.
+constexpr int64_t kSplitTasks = (int64_t)1 << 19;
+
+// ComputeSemantics of every compiled program, list by list of stack need: all
+// but the last with the wide kernel, then the last list with LDS columns up to
+// kMaxLdsSlots, then the programs beyond any LDS column (spill stacks).
+// counts[b]: the longest list b over the runs.
 hipError_t interpret_all(gsgp_handle* h, const int32_t (&counts)[kLists], hipStream_t s) {
   const Params& p = h->params;
+  int64_t rest = 0;
+  for (int b = 1; b < kLists - 1; ++b) rest += counts[b];
+  const int64_t blocks = h->interp_tasks_w;
   hipError_t e = hipSuccess;
-  for (int b = 0; b < kLists - 1 && e == hipSuccess; ++b) {
-    const int lo = b == 0 ? -1 : kListSlots[b - 1];
-    e = launch_interpret_wide(h->runs_d, p, h->interp_tasks_w, h->interp_tasks, lo, b, counts[b], s);
+  if (blocks * (counts[0] + rest) < kSplitTasks) {
+    e = launch_interpret_wide(h->runs_d, p, blocks, 0, kLists - 2, counts[0] + rest, 1, s);
+  } else {
+    e = launch_interpret_wide(h->runs_d, p, blocks, 0, 0, counts[0], 2, s);
+    if (e == hipSuccess) e = launch_interpret_wide(h->runs_d, p, blocks, 1, kLists - 2, rest, 2, s);
   }
   if (e == hipSuccess && h->slots > kListSlots[kLists - 2])
-    e = launch_interpret(h->runs_d, p, h->interp_tasks, kListSlots[kLists - 2], std::min(h->slots, kMaxLdsSlots),
-                         kLists - 1, counts[kLists - 1], s);
+    e = launch_interpret(h->runs_d, p, h->interp_tasks, std::min(h->slots, kMaxLdsSlots), counts[kLists - 1], s);
   if (e == hipSuccess && h->slots > kMaxLdsSlots)
     e = launch_interpret_spill(h->runs_d, p, (double*)(h->ws + h->plan.spill), h->slots, s);
   return e;
@@ -1436,9 +1444,9 @@ gsgp_status reconstruct_with(gsgp_handle* h, int32_t run, int32_t gen, int32_t i
   const int32_t* d_progp = d_sq0 + n0 + 1;
   const int32_t* d_sqp = d_progp + np + 1;
   HIPCHK(h, launch_transpose(d_X, n, R.l, Xfm, L.ld, h->stream));
-  HIPCHK(h, launch_interpret_list(R.ops, R.opv, R.nops, h->cfg.genome_len, d_prog0, d_sq0, (int32_t)n0, Xfm, L.ld, n,
+  HIPCHK(h, launch_interpret_list(R.ops, R.nops, h->cfg.genome_len, d_prog0, d_sq0, (int32_t)n0, Xfm, L.ld, n,
                                   bufA, h->slots, spill, h->stream));
-  HIPCHK(h, launch_interpret_list(R.ops, R.opv, R.nops, h->cfg.genome_len, d_progp, d_sqp, (int32_t)np, Xfm, L.ld, n,
+  HIPCHK(h, launch_interpret_list(R.ops, R.nops, h->cfg.genome_len, d_progp, d_sqp, (int32_t)np, Xfm, L.ld, n,
                                   pool, h->slots, spill, h->stream));
   // One launch for the lineage when two generations of at least one case fit
   // in LDS; the second row buffer, unused then, holds the node ranges.  The

@@ -67,3 +67,56 @@ def test_edge_genomes_are_bit_exact(k):
     for i in range(0, m, 7):
         assert np.array_equal(R.reconstruct(0, 0, i, X), want[i]), i
     R.close()
+
+
+def test_values_past_the_limits_take_the_checked_evaluator():
+    """The threaded interpreter tests its limits once at the end of a program:
+    results beyond FLT_MAX (clamped), infinite or NaN intermediates, values
+    whose high word reads as an FP32 NaN or denormal, tiny and zero divisors and
+    dividends, anywhere in a program and followed by harmless values, give the
+    oracle's bits."""
+    rng = np.random.default_rng(4)
+    k, rows = 24, []
+    big = [1e300, 1e307, 2e306, 1.5e308, -1e307, 3.5e38, 3.4028234663852886e38, 1e200]
+    small = [1e-7, 9.99999e-7, 1e-6, -1e-6, 1.0000001e-6, 1e-300, 1e-310, 5e-324, 0.0, -0.0]
+
+    def add(genes):
+        g = np.full((2, k), 0.0)
+        g[0, :] = 1  # trailing pushes never run
+        for i, x in enumerate(genes):
+            g[:, i] = (x, 0.0) if isinstance(x, int) else (-5, x)
+        rows.append(g)
+
+    for c in big + small + [0.5, -3.0, 1e19, 1e38]:
+        for tail in ([], [1e-300, -3], [0.0, -3], [1e300, -4], [2, -4, 3, -1], [1e-20, -3, 1e-20, -3, 1e-20, -3]):
+            add([0, c, -3] + tail)                      # x * c ...
+            add([c, 1, -1] + tail)                      # c + x ...
+            add([c, 1, -2, 0, -3] + tail)               # (c - x) * x ...
+            add([0, c, -4] + tail)                      # x / c ...
+            add([c, 1, -4] + tail)                      # c / x ...
+            add([0, 1, -3, c, 2, -3, -4] + tail)        # x y / (c z) ...
+            add([c, 0, -3, c, 1, -3, -2] + tail)        # c x - c y ...
+            add([c, 0, -3, c, 0, -3, -4] + tail)        # c x / (c x) ...
+    for _ in range(60):                                 # 0 / x, x / 0, and squares up to overflow
+        i = int(rng.integers(L))
+        add([i, i, -2, 1, -4])
+        add([1, i, i, -2, -4])
+        add([i, 1e100, -3] + [2, 1e100, -3, -3] * 3 + [1, -1])
+    P = np.array(rows)
+    codes, consts = P[:, 0].astype(np.int32), P[:, 1]
+    m, r = codes.shape[0], 2
+    codes, consts = np.concatenate([codes, codes[:r]]), np.concatenate([consts, consts[:r]])
+    d = dataset(300, 20, L, seed=1)
+    d.X_train[7, 0] = 0.0
+    d.X_train[9, 1] = 1e-7
+    d.X_train[11, 2] = -1e-300
+    s = gsgp.Settings(pop_size=m, pool_size=r, genome_len=k, n_generations_max=1, seed=3)
+    R = gsgp.Runner(s, [d])
+    R.eval_population(codes, consts)
+    X = np.concatenate([d.X_train, d.X_test])
+    with np.errstate(all="ignore"):
+        want = orc.interpret(codes[:m], consts[:m], X)
+    got = R.semantics(0, 0)
+    bad = np.nonzero((got != want).any(1))[0]
+    assert bad.size == 0, (bad[:5], codes[bad[:1]], consts[bad[:1]])
+    R.close()
