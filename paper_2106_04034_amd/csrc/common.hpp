@@ -279,10 +279,12 @@ hipError_t launch_fetch_pair(const double* a, const double* b, int32_t n, double
 // Reconstruction helpers.
 hipError_t launch_transpose(const double* X, int64_t n, int32_t l, double* Xfm, int64_t ld,
                             hipStream_t s);
-hipError_t launch_interpret_list(const CompiledOp* ops, const int32_t* nops,
-                                 int32_t k, const int32_t* prog, const int32_t* squash,
-                                 int32_t nprog, const double* Xfm, int64_t ld, int64_t n,
-                                 double* out, int slots, double* spill, hipStream_t s);
+// The n0 generation-0 trees tree0[] to out0 and the np pool trees pool[],
+// squashed, to outp ([program][ld]).
+hipError_t launch_interpret_list(const CompiledOp* ops, const int32_t* nops, int32_t k, int32_t m,
+                                 const int32_t* tree0, int32_t n0, const int32_t* pool, int32_t np, const double* Xfm,
+                                 int64_t ld, int64_t n, double* out0, double* outp, int slots, double* spill,
+                                 hipStream_t s);
 struct ReplayNode {
   int32_t op;     // 0 mutation, 1 crossover, 2 copy
   int32_t a, b;   // source slots (previous generation); b = -1 unless crossover
@@ -291,9 +293,20 @@ struct ReplayNode {
   double ms;
   double alpha, beta;  // local search: the offspring is alpha + beta * (operator output)
 };
+// The part of an ancestry that one individual depends on, walked on the device
+// (see k_lineage): lineage_lds bytes of LDS must not exceed kReplayLdsBytes.
+// Nodes of generation g go to begin[gen - g] .. begin[gen - g + 1] - 1, as many
+// as node_cap allows; the summary counts them all.
+struct LineageSummary {
+  int32_t max_slots, n0, np, total_nodes;
+};
+constexpr int64_t lineage_lds(int64_t m, int64_t r) { return 4 * (3 * m + r); }
+hipError_t launch_lineage(const RunDev* d_runs, const Params& p, int32_t run, int32_t gen, int32_t individual,
+                          int32_t* begin, int32_t* tree0, int32_t* pool, ReplayNode* nodes, int64_t node_cap,
+                          LineageSummary* out, hipStream_t s);
 // A whole lineage of `gen` generations in one launch: nodes of generation g at
-// begin[g] .. begin[g + 1] - 1 (device array of gen + 2), at most `slots` rows
-// a generation; replay_cases(slots) must not be 0.
+// begin[gen - g] .. begin[gen - g + 1] - 1 (device array of gen + 1), at most
+// `slots` rows a generation; replay_cases(slots) must not be 0.
 constexpr int64_t kReplayLdsBytes = 128 << 10;
 int replay_cases(int64_t slots);
 hipError_t launch_replay_lineage(const ReplayNode* nodes, const int32_t* begin, int32_t gen, int32_t n0, int32_t np,

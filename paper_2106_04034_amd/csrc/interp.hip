@@ -1198,67 +1198,64 @@ __global__ __launch_bounds__(64) void k_interpret_spill(const RunDev* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// One (program, 128-case block) task of the list interpreter: nprog
-// programs (prog[j], squashed by the logistic when squash[j]) on cases of
-// the feature-major Xfm, out[j][ld].
+// One (program, 128-case block) task of the list interpreter: the n0
+// generation-0 trees (as they are, to out0[j][ld]) and then the np pool trees
+// (squashed by the logistic, to outp[j][ld]) of a lineage on cases of the
+// feature-major Xfm.
+struct ListArgs {
+  const CompiledOp* ops;
+  const int32_t* nops;
+  int32_t k, m;
+  const int32_t *tree0, *pool;
+  int32_t n0, np;
+  const double* Xfm;
+  int64_t ld, n;
+  double *out0, *outp;
+};
+
 template <typename Stack>
-__device__ __forceinline__ void list_task(const CompiledOp* ops, const int32_t* nops, int32_t k,
-                                          const int32_t* prog, const int32_t* squash, int32_t nprog,
-                                          const double* Xfm, int64_t ld, int64_t n, double* out, int64_t task,
-                                          Stack stk, int lane) {
+__device__ __forceinline__ void list_task(const ListArgs& a, int64_t task, Stack stk, int lane) {
+  const int nprog = a.n0 + a.np;
   const int64_t cb = task / nprog;
   const int j = (int)(task - cb * nprog);
-  const int pr = uni(prog[j]);
+  const bool sq = j >= a.n0;
+  const int pr = uni(sq ? a.m + a.pool[j - a.n0] : a.tree0[j]);
   int64_t col[kInterpV];
   bool ok[kInterpV];
 #pragma unroll
   for (int v = 0; v < kInterpV; ++v) {
     col[v] = cb * (kWave * kInterpV) + v * kWave + lane;
-    ok[v] = col[v] < ld;
+    ok[v] = col[v] < a.ld;
   }
   double val[kInterpV];
-  eval_program<kInterpV>(ops + (int64_t)pr * op_stride(k) + 1, uni(nops[pr]), Xfm, ld, col, ok, stk,
-                                lane, val);
-  const bool sq = squash[j] != 0;
+  eval_program<kInterpV>(a.ops + (int64_t)pr * op_stride(a.k) + 1, uni(a.nops[pr]), a.Xfm, a.ld, col, ok, stk, lane, val);
+  double* out = sq ? a.outp + (int64_t)(j - a.n0) * a.ld : a.out0 + (int64_t)j * a.ld;
 #pragma unroll
   for (int v = 0; v < kInterpV; ++v) {
     if (!ok[v]) continue;
     double x = val[v];
     if (sq) x = 1.0 / (1.0 + exp(-x));
-    out[(int64_t)j * ld + col[v]] = col[v] < n ? x : 0.0;
+    out[col[v]] = col[v] < a.n ? x : 0.0;
   }
 }
 
-__global__ __launch_bounds__(256) void k_interpret_list(const CompiledOp* __restrict__ ops,
-                                                        const int32_t* __restrict__ nops, int32_t k,
-                                                        const int32_t* __restrict__ prog,
-                                                        const int32_t* __restrict__ squash,
-                                                        int32_t nprog, const double* __restrict__ Xfm,
-                                                        int64_t ld, int64_t n, double* __restrict__ out,
-                                                        int slots, int64_t total) {
+__global__ __launch_bounds__(256) void k_interpret_list(ListArgs a, int slots, int64_t total) {
   extern __shared__ double lds[];
   const int lane = threadIdx.x & 63;
   const int wave = uni(threadIdx.x >> 6);
   const int64_t task = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
   if (task >= total) return;
   double* stk = lds + wave * slots * kInterpV * kWave;
-  list_task(ops, nops, k, prog, squash, nprog, Xfm, ld, n, out, task, (LdsStack)stk, lane);
+  list_task(a, task, (LdsStack)stk, lane);
 }
 
 // The same with stacks deeper than an LDS column: kSpillWaves one-wave
 // blocks, each with a column of `slots` x kInterpV x 64 doubles in `spill`,
 // sweep the tasks.
-__global__ __launch_bounds__(64) void k_interpret_list_spill(const CompiledOp* __restrict__ ops,
-                                                             const int32_t* __restrict__ nops, int32_t k,
-                                                             const int32_t* __restrict__ prog,
-                                                             const int32_t* __restrict__ squash,
-                                                             int32_t nprog, const double* __restrict__ Xfm,
-                                                             int64_t ld, int64_t n, double* __restrict__ out,
-                                                             double* spill, int slots, int64_t total) {
+__global__ __launch_bounds__(64) void k_interpret_list_spill(ListArgs a, double* spill, int slots, int64_t total) {
   const int lane = threadIdx.x & 63;
   double* stk = spill + (int64_t)blockIdx.x * slots * kInterpV * kWave;
-  for (int64_t task = blockIdx.x; task < total; task += gridDim.x)
-    list_task(ops, nops, k, prog, squash, nprog, Xfm, ld, n, out, task, (GlobalStack)stk, lane);
+  for (int64_t task = blockIdx.x; task < total; task += gridDim.x) list_task(a, task, (GlobalStack)stk, lane);
 }
 
 // Waves per interpreter block so that the LDS stacks of one block stay
@@ -1331,24 +1328,23 @@ hipError_t launch_interpret_spill(const RunDev* d_runs, const Params& p, double*
   return hipGetLastError();
 }
 
-hipError_t launch_interpret_list(const CompiledOp* ops, const int32_t* nops,
-                                 int32_t k, const int32_t* prog, const int32_t* squash,
-                                 int32_t nprog, const double* Xfm, int64_t ld, int64_t n,
-                                 double* out, int slots, double* spill, hipStream_t s) {
-  if (nprog <= 0) return hipSuccess;
+hipError_t launch_interpret_list(const CompiledOp* ops, const int32_t* nops, int32_t k, int32_t m,
+                                 const int32_t* tree0, int32_t n0, const int32_t* pool, int32_t np, const double* Xfm,
+                                 int64_t ld, int64_t n, double* out0, double* outp, int slots, double* spill,
+                                 hipStream_t s) {
+  if (n0 + np <= 0) return hipSuccess;
   if (slots < 1) slots = 1;
+  const ListArgs a{ops, nops, k, m, tree0, pool, n0, np, Xfm, ld, n, out0, outp};
   const int64_t cblocks = (ld + kWave * kInterpV - 1) / (kWave * kInterpV);
-  const int64_t total = cblocks * nprog;
+  const int64_t total = cblocks * (n0 + np);
   if (slots > kMaxLdsSlots) {
     if (!spill) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_interpret_list_spill, dim3(kSpillWaves), dim3(kWave), 0, s, ops, nops, k, prog,
-                       squash, nprog, Xfm, ld, n, out, spill, slots, total);
+    hipLaunchKernelGGL(k_interpret_list_spill, dim3(kSpillWaves), dim3(kWave), 0, s, a, spill, slots, total);
     return hipGetLastError();
   }
   const int waves = interp_waves(slots);
   const size_t shmem = (size_t)waves * slots * kInterpV * kWave * sizeof(double);
-  hipLaunchKernelGGL(k_interpret_list, dim3(blocks_for(total, waves)), dim3(waves * kWave),
-                     shmem, s, ops, nops, k, prog, squash, nprog, Xfm, ld, n, out, slots, total);
+  hipLaunchKernelGGL(k_interpret_list, dim3(blocks_for(total, waves)), dim3(waves * kWave), shmem, s, a, slots, total);
   return hipGetLastError();
 }
 

@@ -1199,21 +1199,64 @@ namespace {
 // individuals of a generation, and the pool trees, in the order in which the
 // walk back meets them.
 struct Lineage {
+  bool on_device = false;                  // walked there: the d_ arrays hold it
   std::vector<int32_t> tree0;              // generation-0 individual of every slot
   std::vector<int32_t> pool;               // pool tree of every pool slot
   std::vector<ReplayNode> nodes;           // by generation, the last one first
   std::vector<int32_t> count;              // nodes of generation g
-  size_t max_slots = 1, total_nodes = 0;
+  int32_t *d_begin = nullptr, *d_tree0 = nullptr, *d_pool = nullptr;
+  ReplayNode* d_nodes = nullptr;
+  size_t n0 = 0, np = 0, max_slots = 1, total_nodes = 0;
   int64_t ld = 0;
   size_t off_X = 0, off_pool = 0, off_A = 0, off_B = 0, off_prog = 0, off_nodes = 0, off_spill = 0, total = 0;
 };
 
-// Walks the ancestry record back from `individual`, one pass over the records
-// of the individuals it depends on.  (Ordered sets of the individuals of
-// every generation, walked once to size the scratch and again to build the
-// nodes through maps, took 18 of the 21 ms of a reconstruction after 200
-// generations of 1,024.)
-gsgp_status walk_lineage(gsgp_handle* h, int32_t run, int32_t gen, int32_t individual, int64_t n, Lineage* L) {
+// Populations from this size on are walked on the device: a generation takes
+// about 2 us there whatever m, and 0.009 us per individual on the host (its
+// records are copied out).
+constexpr int32_t kDeviceWalkPop = 256;
+
+// The walk on the device, into the population buffer that holds no generation
+// (see fetch_semantics); on_device stays false where the maps or the replay do
+// not fit LDS or the lists and nodes do not fit that buffer.
+gsgp_status walk_on_device(gsgp_handle* h, int32_t run, int32_t gen, int32_t individual, Lineage* L) {
+  const int64_t m = h->cfg.pop_size, r = h->cfg.pool_size;
+  if (gen < 1 || m < kDeviceWalkPop || lineage_lds(m, r) > kReplayLdsBytes || gen * m > INT32_MAX) return GSGP_OK;
+  const RunDev& R = h->runs_h[run];
+  char* at = (char*)R.S[(h->gen & 1) ^ 1];
+  const size_t bytes = storage_bytes(h->cfg.precision) * m * R.ld;
+  size_t off = 0;
+  auto take = [&](size_t n) {
+    const size_t q = off;
+    off = align_up(off + n);
+    return at + q;
+  };
+  L->d_begin = (int32_t*)take(sizeof(int32_t) * (gen + 1));
+  L->d_tree0 = (int32_t*)take(sizeof(int32_t) * m);
+  L->d_pool = (int32_t*)take(sizeof(int32_t) * r);
+  L->d_nodes = (ReplayNode*)(at + off);
+  if (off > bytes) return GSGP_OK;
+  const int64_t cap = (int64_t)((bytes - off) / sizeof(ReplayNode));
+  const OnDevice here(h);
+  LineageSummary* sum = (LineageSummary*)h->pinned;
+  HIPCHK(h, launch_lineage(h->runs_d, h->params, run, gen, individual, L->d_begin, L->d_tree0, L->d_pool, L->d_nodes,
+                           cap, sum, h->stream));
+  HIPCHK(h, hipStreamSynchronize(h->stream));
+  if (sum->total_nodes > cap || replay_cases(sum->max_slots) == 0) return GSGP_OK;
+  L->on_device = true;
+  L->n0 = sum->n0;
+  L->np = sum->np;
+  L->max_slots = sum->max_slots;
+  L->total_nodes = sum->total_nodes;
+  return GSGP_OK;
+}
+
+// The walk on the host: the whole record is copied out, and one pass over the
+// records of the individuals that matter numbers the slots and builds the
+// nodes.  (Ordered sets of every generation's individuals, walked once to size
+// the scratch and again to build the nodes through maps, took 18 of the 21 ms
+// of a reconstruction after 200 generations of 1,024; this takes 1.8 ms a walk.)
+gsgp_status walk_on_host(gsgp_handle* h, int32_t run, int32_t gen, int32_t individual, Lineage* L) {
   const int32_t m = h->cfg.pop_size;
   const RunDev& R = h->runs_h[run];
   HIPCHK(h, hipStreamSynchronize(h->stream));
@@ -1280,7 +1323,19 @@ gsgp_status walk_lineage(gsgp_handle* h, int32_t run, int32_t gen, int32_t indiv
   }
   L->max_slots = std::max(L->max_slots, now.size());
   L->tree0 = now;
+  L->n0 = L->tree0.size();
+  L->np = L->pool.size();
   L->total_nodes = L->nodes.size();
+  return GSGP_OK;
+}
+
+// The lineage of `individual` and the scratch its reconstruction on n cases
+// needs.
+gsgp_status walk_lineage(gsgp_handle* h, int32_t run, int32_t gen, int32_t individual, int64_t n, Lineage* L) {
+  const RunDev& R = h->runs_h[run];
+  gsgp_status st = walk_on_device(h, run, gen, individual, L);
+  if (st == GSGP_OK && !L->on_device) st = walk_on_host(h, run, gen, individual, L);
+  if (st != GSGP_OK) return st;
   L->ld = pad_to(n, kSegPad);
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -1289,10 +1344,10 @@ gsgp_status walk_lineage(gsgp_handle* h, int32_t run, int32_t gen, int32_t indiv
     return at;
   };
   L->off_X = take(sizeof(double) * R.l * L->ld);
-  L->off_pool = take(sizeof(double) * std::max<size_t>(1, L->pool.size()) * L->ld);
+  L->off_pool = take(sizeof(double) * std::max<size_t>(1, L->np) * L->ld);
   L->off_A = take(sizeof(double) * L->max_slots * L->ld);
   L->off_B = take(sizeof(double) * L->max_slots * L->ld);
-  L->off_prog = take(sizeof(int32_t) * 2 * (L->tree0.size() + L->pool.size() + 2));
+  L->off_prog = take(sizeof(int32_t) * 2 * (L->n0 + L->np + 2));
   L->off_nodes = take(sizeof(ReplayNode) * std::max<size_t>(1, L->total_nodes));
   // stack columns for programs deeper than an LDS column (spill interpreter)
   L->off_spill = take(h->slots > kMaxLdsSlots ? sizeof(double) * kSpillWaves * h->slots * 2 * kWave : 0);
@@ -1416,55 +1471,47 @@ gsgp_status reconstruct_with(gsgp_handle* h, int32_t run, int32_t gen, int32_t i
   ReplayNode* nodes = (ReplayNode*)(sc + L.off_nodes);
   double* spill = h->slots > kMaxLdsSlots ? (double*)(sc + L.off_spill) : nullptr;
 
-  // host-side lists: generation-0 programs, pool programs, replay nodes
-  const size_t n0 = L.tree0.size(), np = L.pool.size();
-  std::vector<int32_t> lists(2 * (n0 + np + 2), 0);
-  int32_t* prog0 = lists.data();
-  int32_t* sq0 = prog0 + n0 + 1;
-  int32_t* progp = sq0 + n0 + 1;
-  int32_t* sqp = progp + np + 1;
-  std::copy(L.tree0.begin(), L.tree0.end(), prog0);
-  for (size_t j = 0; j < np; ++j) {
-    progp[j] = m + L.pool[j];
-    sqp[j] = 1;
-  }
-  // nodes in the order of the generations: begin[g] .. begin[g + 1] - 1
-  std::vector<int64_t> begin(gen + 2, 0);
-  for (int32_t g = 1; g <= gen; ++g) begin[g + 1] = begin[g] + L.count[g];
-  std::vector<ReplayNode> all_nodes(L.total_nodes);
-  int64_t from = 0;
-  for (int32_t g = gen; g >= 1; from += L.count[g], --g)
-    std::copy(L.nodes.begin() + from, L.nodes.begin() + from + L.count[g], all_nodes.begin() + begin[g]);
-  HIPCHK(h, hipMemcpyAsync(prog, lists.data(), sizeof(int32_t) * lists.size(), hipMemcpyHostToDevice, h->stream));
-  if (!all_nodes.empty())
-    HIPCHK(h, hipMemcpyAsync(nodes, all_nodes.data(), sizeof(ReplayNode) * all_nodes.size(), hipMemcpyHostToDevice,
-                             h->stream));
-  const int32_t* d_prog0 = prog;
-  const int32_t* d_sq0 = prog + n0 + 1;
-  const int32_t* d_progp = d_sq0 + n0 + 1;
-  const int32_t* d_sqp = d_progp + np + 1;
-  HIPCHK(h, launch_transpose(d_X, n, R.l, Xfm, L.ld, h->stream));
-  HIPCHK(h, launch_interpret_list(R.ops, R.nops, h->cfg.genome_len, d_prog0, d_sq0, (int32_t)n0, Xfm, L.ld, n,
-                                  bufA, h->slots, spill, h->stream));
-  HIPCHK(h, launch_interpret_list(R.ops, R.nops, h->cfg.genome_len, d_progp, d_sqp, (int32_t)np, Xfm, L.ld, n,
-                                  pool, h->slots, spill, h->stream));
+  const int32_t *d_begin = L.d_begin, *d_tree0 = L.d_tree0, *d_pool = L.d_pool;
+  const ReplayNode* d_nodes = L.d_nodes;
   // One launch for the lineage when two generations of at least one case fit
-  // in LDS; the second row buffer, unused then, holds the node ranges.  The
-  // individual's slot is 0: the walk starts with it.
-  const size_t begin_bytes = sizeof(int32_t) * begin.size();
-  if (gen > 0 && replay_cases((int64_t)L.max_slots) > 0 && begin_bytes <= sizeof(double) * L.max_slots * L.ld &&
-      L.total_nodes <= (size_t)INT32_MAX) {
-    const std::vector<int32_t> begin32(begin.begin(), begin.end());
-    HIPCHK(h, hipMemcpyAsync(bufB, begin32.data(), begin_bytes, hipMemcpyHostToDevice, h->stream));
-    HIPCHK(h, launch_replay_lineage(nodes, (const int32_t*)bufB, gen, (int32_t)n0, (int32_t)np, (int32_t)L.max_slots,
+  // in LDS; the second row buffer, unused then, holds the node ranges.
+  bool one_launch = gen > 0 && replay_cases((int64_t)L.max_slots) > 0;
+  std::vector<int32_t> lists, begin(1, 0);
+  if (!L.on_device) {
+    lists.reserve(L.n0 + L.np);
+    lists.insert(lists.end(), L.tree0.begin(), L.tree0.end());
+    lists.insert(lists.end(), L.pool.begin(), L.pool.end());
+    HIPCHK(h, hipMemcpyAsync(prog, lists.data(), sizeof(int32_t) * lists.size(), hipMemcpyHostToDevice, h->stream));
+    d_tree0 = prog;
+    d_pool = prog + L.n0;
+    if (!L.nodes.empty())
+      HIPCHK(h, hipMemcpyAsync(nodes, L.nodes.data(), sizeof(ReplayNode) * L.nodes.size(), hipMemcpyHostToDevice,
+                               h->stream));
+    d_nodes = nodes;
+    const size_t begin_bytes = sizeof(int32_t) * ((size_t)gen + 1);
+    one_launch = one_launch && begin_bytes <= sizeof(double) * L.max_slots * L.ld && L.total_nodes <= (size_t)INT32_MAX;
+    if (one_launch) {
+      for (int32_t g = gen; g >= 1; --g) begin.push_back(begin.back() + L.count[g]);
+      HIPCHK(h, hipMemcpyAsync(bufB, begin.data(), begin_bytes, hipMemcpyHostToDevice, h->stream));
+      d_begin = (const int32_t*)bufB;
+    }
+  }
+  HIPCHK(h, launch_transpose(d_X, n, R.l, Xfm, L.ld, h->stream));
+  HIPCHK(h, launch_interpret_list(R.ops, R.nops, h->cfg.genome_len, m, d_tree0, (int32_t)L.n0, d_pool, (int32_t)L.np,
+                                  Xfm, L.ld, n, bufA, pool, h->slots, spill, h->stream));
+  // the individual's slot is 0: the walk starts with it
+  if (one_launch) {
+    HIPCHK(h, launch_replay_lineage(d_nodes, d_begin, gen, (int32_t)L.n0, (int32_t)L.np, (int32_t)L.max_slots,
                                     (int64_t)L.total_nodes, 0, bufA, pool, L.ld, n, d_out, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
     return GSGP_OK;
   }
   double* cur = bufA;
   double* nxt = bufB;
+  size_t end = L.total_nodes;
   for (int32_t g = 1; g <= gen; ++g) {
-    HIPCHK(h, launch_replay_nodes(nodes + begin[g], L.count[g], cur, pool, nxt, L.ld, n, h->stream));
+    end -= L.count[g];
+    HIPCHK(h, launch_replay_nodes(nodes + end, L.count[g], cur, pool, nxt, L.ld, n, h->stream));
     std::swap(cur, nxt);
   }
   HIPCHK(h, hipMemcpyAsync(d_out, cur, sizeof(double) * n, hipMemcpyDeviceToDevice, h->stream));

@@ -1,6 +1,7 @@
-"""Lineage reconstruction over every route of the replay: 8, 4, 2 and 1 cases
-per block with two generations of rows in LDS, and a launch per generation
-beyond that.  On the training and test cases an individual's reconstruction
+"""Lineage reconstruction over every route of the walk (on the host; on the
+device from 256 individuals on, unless its nodes or maps do not fit) and of the
+replay: 8, 4, 2 and 1 cases per block with two generations of rows in LDS, and a
+launch per generation beyond that.  On the training and test cases an individual's reconstruction
 repeats the FP64 operations that formed its stored semantics, in their order,
 so the values are equal."""
 from __future__ import annotations
@@ -24,6 +25,11 @@ pytestmark = pytest.mark.gpu
     (12000, 50, 18, 0),        # 1
     (30000, 50, 18, 0),        # beyond LDS: a launch per generation
     (64, 64, 30, gsgp.FLAG_LOCAL_SEARCH),
+    (256, 31, 40, gsgp.FLAG_LOCAL_SEARCH),
+    (255, 300, 20, 0),         # the largest walked on the host
+    (256, 300, 150, 0),        # the nodes of 150 generations exceed the buffer the device walk uses
+    (8000, 8100, 12, 0),       # the largest maps in LDS
+    (8192, 8200, 9, 0),        # just beyond them
 ])
 def test_reconstruction_repeats_the_stored_semantics(m, r, gens, flags):
     d = dataset(21, 6, 3, seed=m)
