@@ -285,32 +285,36 @@ hipError_t launch_interpret_list(const CompiledOp* ops, const int32_t* nops, int
                                  const int32_t* tree0, int32_t n0, const int32_t* pool, int32_t np, const double* Xfm,
                                  int64_t ld, int64_t n, double* out0, double* outp, int slots, double* spill,
                                  hipStream_t s);
-struct ReplayNode {
+struct alignas(16) ReplayNode {
   int32_t op;     // 0 mutation, 1 crossover, 2 copy
-  int32_t a, b;   // source slots (previous generation); b = -1 unless crossover
-  int32_t r1, r2; // pool slots
+  int32_t a, b;   // source slots (previous generation); b is 0 unless crossover
+  int32_t r1, r2; // pool slots, 0 where the operation reads none
   int32_t out;    // destination slot
   double ms;
   double alpha, beta;  // local search: the offspring is alpha + beta * (operator output)
 };
 // The part of an ancestry that one individual depends on, walked on the device
-// (see k_lineage): lineage_lds bytes of LDS must not exceed kReplayLdsBytes.
-// Nodes of generation g go to begin[gen - g] .. begin[gen - g + 1] - 1, as many
-// as node_cap allows; the summary counts them all.
+// (see k_lineage): lineage_lds bytes of LDS must not exceed kReplayLdsBytes,
+// and the population not kLineagePop.  `slots`, lineage_slots int32 or null, is
+// what the nodes are made from: those of generation g go to begin[gen - g] ..
+// begin[gen - g + 1] - 1.
 struct LineageSummary {
   int32_t max_slots, n0, np, total_nodes;
 };
-constexpr int64_t lineage_lds(int64_t m, int64_t r) { return 4 * (3 * m + r); }
-hipError_t launch_lineage(const RunDev* d_runs, const Params& p, int32_t run, int32_t gen, int32_t individual,
-                          int32_t* begin, int32_t* tree0, int32_t* pool, ReplayNode* nodes, int64_t node_cap,
-                          LineageSummary* out, hipStream_t s);
+constexpr int32_t kLineagePop = 8192;
+constexpr int64_t lineage_lds(int64_t m, int64_t r) { return 4 * (2 * m + r); }
+constexpr int64_t lineage_slots(int64_t m, int64_t r, int64_t gen) { return (gen + 1) * m + r; }
+hipError_t launch_lineage(const RunDev& R, const Params& p, int32_t gen, int32_t individual, int32_t* begin,
+                          int32_t* tree0, int32_t* pool, int32_t* slots, LineageSummary* out, hipStream_t s);
+hipError_t launch_lineage_nodes(const RunDev& R, const Params& p, int32_t gen, const int32_t* begin,
+                                const int32_t* slots, ReplayNode* nodes, hipStream_t s);
 // A whole lineage of `gen` generations in one launch: nodes of generation g at
 // begin[gen - g] .. begin[gen - g + 1] - 1 (device array of gen + 1), at most
-// `slots` rows a generation; replay_cases(slots) must not be 0.
+// `slots` rows a generation; replay_cases(slots, n) must not be 0.
 constexpr int64_t kReplayLdsBytes = 128 << 10;
-int replay_cases(int64_t slots);
+int replay_cases(int64_t slots, int64_t n);
 hipError_t launch_replay_lineage(const ReplayNode* nodes, const int32_t* begin, int32_t gen, int32_t n0, int32_t np,
-                                 int32_t slots, int64_t total_nodes, int32_t out_slot, const double* first,
+                                 int32_t slots, int32_t out_slot, const double* first,
                                  const double* pool, int64_t ld, int64_t n, double* out, hipStream_t s);
 hipError_t launch_replay_nodes(const ReplayNode* nodes, int32_t nnodes, const double* prev,
                                const double* pool, double* next, int64_t ld, int64_t n,

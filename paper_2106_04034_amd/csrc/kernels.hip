@@ -1344,18 +1344,16 @@ __global__ __launch_bounds__(256) void k_transpose(const double* __restrict__ X,
   for (int f = 0; f < l; ++f) Xfm[(int64_t)f * ld + c] = c < n ? X[c * l + f] : 0.0;
 }
 
-// One recorded step on one case: the parents' values a (and b, crossover) and
-// the squashed pool values r1 (and r2, mutation).
-__device__ __forceinline__ double replay_step(const ReplayNode& nd, double a, double b, double r1, double r2) {
-  double o = a;
-  if (nd.op == 0)
-    o = a + nd.ms * (r1 - r2);
-  else if (nd.op == 1)
-    o = a * r1 + b * (1.0 - r1);
-  // local search: the offspring's recorded scaling (never for copies, and
-  // skipped when it is the identity so that unscaled runs keep their bits)
-  if (nd.op != 2 && (nd.alpha != 0.0 || nd.beta != 1.0)) o = nd.alpha + nd.beta * o;
-  return o;
+// A recorded step on one case: the parents' values a (and b, crossover) and
+// the squashed pool values r1 (and r2, mutation), then the offspring's
+// recorded scaling of the local search (never for copies, and skipped when it
+// is the identity so that unscaled runs keep their bits).
+__device__ __forceinline__ double replay_mutant(const ReplayNode& nd, double a, double r1, double r2) {
+  return a + nd.ms * (r1 - r2);
+}
+__device__ __forceinline__ double replay_mix(double a, double b, double r1) { return a * r1 + b * (1.0 - r1); }
+__device__ __forceinline__ bool replay_scaled(const ReplayNode& nd) {
+  return nd.op != 2 && (nd.alpha != 0.0 || nd.beta != 1.0);
 }
 
 // One generation of a lineage, rows in global memory (for lineages whose
@@ -1367,125 +1365,218 @@ __global__ __launch_bounds__(256) void k_replay_nodes(const ReplayNode* __restri
   const ReplayNode nd = nodes[blockIdx.y];
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n) return;
-  const double a = prev[(int64_t)nd.a * ld + c];
-  const double b = nd.op == 1 ? prev[(int64_t)nd.b * ld + c] : 0.0;
-  const double r1 = nd.op != 2 ? pool[(int64_t)nd.r1 * ld + c] : 0.0;
-  const double r2 = nd.op == 0 ? pool[(int64_t)nd.r2 * ld + c] : 0.0;
-  next[(int64_t)nd.out * ld + c] = replay_step(nd, a, b, r1, r2);
+  double o = prev[(int64_t)nd.a * ld + c];
+  if (nd.op != 2) {
+    const double r1 = pool[(int64_t)nd.r1 * ld + c];
+    o = nd.op == 1 ? replay_mix(o, prev[(int64_t)nd.b * ld + c], r1)
+                   : replay_mutant(nd, o, r1, pool[(int64_t)nd.r2 * ld + c]);
+  }
+  if (replay_scaled(nd)) o = nd.alpha + nd.beta * o;
+  next[(int64_t)nd.out * ld + c] = o;
 }
 
-// The walk back through the ancestry record from one individual, on one block:
-// the individuals of a generation that matter are a list in LDS; each thread
-// takes some of them, reads their records and claims a slot for every parent
-// and pool tree met for the first time.  Slots are given in the order of the
-// claims: nothing depends on it.  What bounds it is a record's latency per
-// generation: 382 us for 200 generations of 1,024, where the walk on the host,
-// for which the whole record is copied out, took 1,800 us.
-__global__ __launch_bounds__(1024) void k_lineage(const RunDev* __restrict__ runs, Params p, int32_t run, int32_t gen,
+// The walk back through the ancestry record from one individual, on one block.
+// Thread t has individuals t, t + threads, ...: it reads their records up to
+// two generations ahead, and those whose individual matters claim a slot for
+// every parent and pool tree met for the first time.  Slots are given in the
+// order of the claims: nothing depends on it.  What bounds it is the chain of
+// LDS round trips of a generation (slot, claims, count, two barriers).  The
+// records of all individuals are read for that, but a list of those that
+// matter, whose records are then read, put the latency of that read on the
+// chain; so did building the nodes here, which k_lineage_nodes does from the
+// slots ([gen + 1][m], then the pool's; none are written without).  A walk over
+// 200 generations of 1,024 takes 186 us, over 100 of 128 59 us; with the list
+// 382 us, with the list and nodes built on the host 1,800 and 75 us.
+template <int K>
+__global__ __launch_bounds__(1024) void k_lineage(const gsgp_record* __restrict__ records,
+                                                  const gsgp_gen_stats* __restrict__ stats, Params p, int32_t gen,
                                                   int32_t individual, int32_t* __restrict__ begin,
                                                   int32_t* __restrict__ tree0, int32_t* __restrict__ pool,
-                                                  ReplayNode* __restrict__ nodes, int64_t node_cap,
-                                                  LineageSummary* __restrict__ out) {
-  extern __shared__ int32_t lin[];  // slots of the generation before [m], its list [m], this one's [m], pool slots [r]
-  __shared__ int32_t n_before, n_pool;
-  const RunDev& R = runs[run];
-  int32_t* slot = lin;
+                                                  int32_t* __restrict__ slots, LineageSummary* __restrict__ out) {
+  constexpr int kAhead = K > 4 ? 1 : 2;  // generations in registers
+  extern __shared__ int32_t lin[];  // slots of two generations' individuals, then of the pool trees; -1 without
+  __shared__ int32_t met[2];
+  int32_t* now = lin;
   int32_t* before = lin + p.m;
-  int32_t* now = lin + 2 * p.m;
-  int32_t* pslot = lin + 3 * p.m;
+  int32_t* pslot = lin + 2 * p.m;
   const int t = threadIdx.x, T = blockDim.x;
-  for (int i = t; i < p.m; i += T) slot[i] = -1;
-  for (int i = t; i < p.r; i += T) pslot[i] = -1;
+  for (int i = t; i < 2 * p.m + p.r; i += T) lin[i] = i == individual ? 0 : -1;
   if (t == 0) {
-    now[0] = individual;
-    n_pool = 0;
+    met[0] = met[1] = 0;
     begin[0] = 0;
   }
-  int n = 1, total = 0, most = 1;
-  gsgp_gen_stats s = R.stats[gen];
-  for (int g = gen; g >= 1; --g) {
-    if (t == 0) n_before = 0;
-    __syncthreads();
-    const gsgp_gen_stats s_next = R.stats[g - 1];
-    const gsgp_record* rec = R.rec + (int64_t)(g - 1) * p.m;
-    auto claim = [&](int q) {
-      if (atomicCAS(&slot[q], -1, -2) == -1) {
-        const int at = atomicAdd(&n_before, 1);
-        before[at] = q;
-        slot[q] = at;
-      }
-    };
-    auto claim_pool = [&](int q) {
-      if (atomicCAS(&pslot[q], -1, -2) == -1) {
-        const int at = atomicAdd(&n_pool, 1);
-        pool[at] = q;
-        pslot[q] = at;
-      }
-    };
-    gsgp_record first{};
-    for (int j = t; j < n; j += T) {
-      const int i = now[j];
-      if (s.elite_copied && i == s.elite_dst) {
-        claim(s.elite_src);
-        continue;
-      }
-      const gsgp_record d = rec[i];
-      if (j == t) first = d;
-      claim(d.p1);
-      claim_pool(d.r1);
-      if (d.op == 1)
-        claim(d.p2);
-      else
-        claim_pool(d.r2);
+  struct Step {
+    int copied, src, dst;
+    gsgp_record d[K];
+  };
+  int zero = 0;
+  asm("" : "+v"(zero));  // a vector load: a scalar one would be waited for with every LDS access
+  auto read = [&](int g) {
+    g = g < 1 ? 1 : g;
+    const gsgp_gen_stats& s = stats[g + zero];
+    Step x;
+    x.copied = s.elite_copied;
+    x.src = s.elite_src;
+    x.dst = s.elite_dst;
+    const gsgp_record* rec = records + (int64_t)(g - 1) * p.m;
+#pragma unroll
+    for (int k = 0; k < K; ++k) x.d[k] = rec[t + k * T < p.m ? t + k * T : 0];
+    return x;
+  };
+  int n = 1, np = 0, total = 0, most = 1;
+  auto walk = [&](int g, Step& x) {
+    // Up to three claims of an individual: a parent, a pool tree, and one of
+    // either.  They are in flight together, and a wave counts the ones that
+    // succeeded with one addition (parents in the low half, pool trees in the
+    // high half).
+    __syncthreads();  // the slots of `now` are complete
+    int j[K], first[K], tree[K], second[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int i = t + k * T;
+      j[k] = i < p.m ? now[i] : -1;
+      if (slots && i < p.m) slots[(int64_t)g * p.m + i] = j[k];
     }
-    __syncthreads();
-    for (int j = t; j < n; j += T) {
-      const int i = now[j];
-      ReplayNode nd{2, 0, -1, -1, -1, j, 0.0, 0.0, 1.0};
-      if (s.elite_copied && i == s.elite_dst) {
-        nd.a = slot[s.elite_src];
-      } else {
-        const gsgp_record d = j == t ? first : rec[i];
-        nd.op = d.op;
-        nd.a = slot[d.p1];
-        nd.r1 = pslot[d.r1];
-        if (d.op == 1) {
-          nd.b = slot[d.p2];
-        } else {
-          nd.r2 = pslot[d.r2];
-          nd.ms = d.ms;
-        }
-        if (p.ls) {
-          nd.alpha = R.ls[((int64_t)g * p.m + i) * 2];
-          nd.beta = R.ls[((int64_t)g * p.m + i) * 2 + 1];
-        }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int i = t + k * T;
+      first[k] = tree[k] = second[k] = 0;
+      if (j[k] < 0) continue;
+      gsgp_record& d = x.d[k];
+      now[i] = -1;
+      if (x.copied && i == x.dst) {
+        d.op = 2;
+        d.p1 = x.src;
       }
-      if (total + j < node_cap) nodes[total + j] = nd;
+      first[k] = atomicCAS(&before[d.p1], -1, -2);
+      if (d.op == 2) continue;
+      tree[k] = atomicCAS(&pslot[d.r1], -1, -2);
+      second[k] = atomicCAS(d.op == 1 ? &before[d.p2] : &pslot[d.r2], -1, -2);
     }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const gsgp_record& d = x.d[k];
+      const uint64_t c1 = __ballot(first[k] == -1), c2 = __ballot(second[k] == -1 && d.op == 1);
+      const uint64_t q1 = __ballot(tree[k] == -1), q2 = __ballot(second[k] == -1 && d.op == 0);
+      const int parents = __popcll(c1) + __popcll(c2), trees = __popcll(q1) + __popcll(q2);
+      if (parents + trees == 0) continue;
+      int at = 0;
+      if (t % kWave == 0) at = atomicAdd(&met[g & 1], parents | trees << 16);
+      at = uni(at);
+      const uint64_t below = ((uint64_t)1 << (t % kWave)) - 1;
+      const int at_parent = at & 0xffff, at_tree = np + (int)((unsigned)at >> 16);
+      auto give = [&](bool mine, int q, int to) {
+        if (mine) before[q] = to;
+      };
+      auto give_tree = [&](bool mine, int q, int to) {
+        if (mine) {
+          pslot[q] = to;
+          pool[to] = q;
+        }
+      };
+      give(first[k] == -1, d.p1, at_parent + __popcll(c1 & below));
+      give(second[k] == -1 && d.op == 1, d.p2, at_parent + __popcll(c1) + __popcll(c2 & below));
+      give_tree(tree[k] == -1, d.r1, at_tree + __popcll(q1 & below));
+      give_tree(second[k] == -1 && d.op == 0, d.r2, at_tree + __popcll(q1) + __popcll(q2 & below));
+    }
+    if (t == 0) met[(g & 1) ^ 1] = 0;
+    __builtin_amdgcn_sched_barrier(0);
+    x = read(g - kAhead);  // into the same registers: a copy would wait for it
+    __builtin_amdgcn_sched_barrier(0);
     total += n;
     if (t == 0) begin[gen - g + 1] = total;
     __syncthreads();
-    n = n_before;
+    const int counted = met[g & 1];
+    n = counted & 0xffff;
+    np += (int)((unsigned)counted >> 16);
     most = most > n ? most : n;
-    for (int j = t; j < n; j += T) slot[before[j]] = -1;
     int32_t* q = now;
     now = before;
     before = q;
-    s = s_next;
-    __syncthreads();  // n_before is read, slots are clear
+  };
+  // Generations in pairs and loads in the order of their use, so that each
+  // wait is for its own loads only.
+  int g = gen;
+  if (kAhead == 1 || (g & 1)) {
+    Step x = read(g);
+    for (; g >= 1 && (kAhead == 1 || (g & 1)); --g) walk(g, x);
   }
-  for (int j = t; j < n; j += T) tree0[j] = now[j];
-  if (t == 0) *out = LineageSummary{most, n, n_pool, total};
+  if constexpr (kAhead > 1) {
+    Step a = read(g);
+    __builtin_amdgcn_sched_barrier(0);
+    Step b = read(g - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    for (; g >= 1; g -= 2) {
+      walk(g, a);
+      walk(g - 1, b);
+    }
+  }
+  __syncthreads();
+  for (int i = t; i < p.m; i += T) {
+    if (slots) slots[i] = now[i];
+    if (now[i] >= 0) tree0[now[i]] = i;
+  }
+  if (slots)
+    for (int i = t; i < p.r; i += T) slots[(int64_t)(gen + 1) * p.m + i] = pslot[i];
+  if (t == 0) *out = LineageSummary{most, n, np, total};
+}
+
+// The nodes of a walk, one block a generation: the crossovers first and the
+// others last, for the waves of k_replay_lineage to have one kind.
+__global__ __launch_bounds__(1024) void k_lineage_nodes(const gsgp_record* __restrict__ records,
+                                                        const gsgp_gen_stats* __restrict__ stats,
+                                                        const double* __restrict__ ls, int32_t m, int32_t gen,
+                                                        const int32_t* __restrict__ begin,
+                                                        const int32_t* __restrict__ slots,
+                                                        ReplayNode* __restrict__ nodes) {
+  __shared__ int32_t front, back;
+  const int g = gen - (int)blockIdx.x;
+  const int32_t* own = slots + (int64_t)g * m;
+  const int32_t* before = own - m;
+  const int32_t* pslot = slots + (int64_t)(gen + 1) * m;
+  const gsgp_record* rec = records + (int64_t)(g - 1) * m;
+  const gsgp_gen_stats s = stats[g];
+  if (threadIdx.x == 0) {
+    front = begin[gen - g];
+    back = begin[gen - g + 1];
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < m; i += blockDim.x) {
+    const int j = own[i];
+    if (j < 0) continue;
+    ReplayNode nd{2, 0, 0, 0, 0, j, 0.0, 0.0, 1.0};
+    if (s.elite_copied && i == s.elite_dst) {
+      nd.a = before[s.elite_src];
+    } else {
+      const gsgp_record d = rec[i];
+      nd.op = d.op;
+      nd.a = before[d.p1];
+      nd.r1 = pslot[d.r1];
+      if (d.op == 1) {
+        nd.b = before[d.p2];
+      } else {
+        nd.r2 = pslot[d.r2];
+        nd.ms = d.ms;
+      }
+      if (ls) {
+        nd.alpha = ls[2 * ((int64_t)g * m + i)];
+        nd.beta = ls[2 * ((int64_t)g * m + i) + 1];
+      }
+    }
+    nodes[nd.op == 1 ? atomicAdd(&front, 1) : atomicSub(&back, 1) - 1] = nd;
+  }
 }
 
 // A whole lineage in one launch.  Cases are independent, so a block takes C
 // of them through every generation with the live rows of two generations
-// (and, when they fit too, the pool rows) in LDS: [slot][C].  Thread t works
-// on case t % C of nodes t / C, t / C + threads / C, ...; the next node is
-// read before the barrier that ends a generation, since nodes depend on no
-// value.  What bounds it is the chain of generations (a barrier, a node read
-// and two LDS round trips each); a launch a generation took 8.5 us for 10,000
-// cases and 2.7 us for 16, plus the gap to the next one.
+// (and, when they fit too, the pool rows) in LDS: [slot][C].  A thread works
+// on all C cases of nodes lane, lane + lanes, ....  What bounds it is the chain
+// of generations (a barrier and two LDS round trips each) and the bandwidth of
+// LDS, so nothing else may be on it: nodes depend on no value and are read
+// two generations ahead, and no wait is for more than it has to be. 10,000 cases of 200
+// generations with at most 251 live rows: 438 us; 492 with nodes one
+// generation ahead, 530 with both operators evaluated and chosen from, 1,435
+// with 8 cases a block, one a thread.
 template <int C, bool POOL>
 __global__ __launch_bounds__(1024) void k_replay_lineage(const ReplayNode* __restrict__ nodes,
                                                          const int32_t* __restrict__ begin, int32_t gen, int32_t n0,
@@ -1493,47 +1584,113 @@ __global__ __launch_bounds__(1024) void k_replay_lineage(const ReplayNode* __res
                                                          const double* __restrict__ first,
                                                          const double* __restrict__ pool, int64_t ld, int64_t n,
                                                          double* __restrict__ out) {
-  extern __shared__ double rows[];  // two generations of slots x C, then the pool's np x C
+  // A row is H pieces of P cases, each in a plane of its own: 16-byte accesses
+  // to 16-byte rows reach all banks, to 32-byte rows half of them (2 % slower).
+  constexpr int P = C > 1 ? 2 : 1, H = C / P;
+  struct alignas(8 * P) Piece {
+    double v[P];
+  };
+  struct Part {
+    Piece h[H];
+  };
+  extern __shared__ __attribute__((aligned(16))) double rows[];  // two generations of slots x C, then the pool's np x C
   const int64_t c0 = (int64_t)blockIdx.x * C;  // ld is a multiple of 64, so c0 + C <= ld
-  const int cl = threadIdx.x % C;
-  const int lane = threadIdx.x / C, lanes = blockDim.x / C;
+  const int lane = threadIdx.x, lanes = blockDim.x;
+  auto get = [](const double* p, int64_t row, int64_t row_step, int64_t plane) {
+    Part x;
+#pragma unroll
+    for (int h = 0; h < H; ++h) x.h[h] = *(const Piece*)(p + row * row_step + h * plane);
+    return x;
+  };
+  auto put = [](double* p, int row, int plane, const Part& x) {
+#pragma unroll
+    for (int h = 0; h < H; ++h) *(Piece*)(p + row * P + h * plane) = x.h[h];
+  };
+  const int plane = slots * P, pool_plane = np * P;
   double* cur = rows;
   double* nxt = rows + (int64_t)slots * C;
   double* pl = rows + 2 * (int64_t)slots * C;
-  for (int j = lane; j < n0; j += lanes) cur[j * C + cl] = first[(int64_t)j * ld + c0 + cl];
+  for (int j = lane; j < n0; j += lanes) put(cur, j, plane, get(first + c0, j, ld, P));
   if constexpr (POOL)
-    for (int j = lane; j < np; j += lanes) pl[j * C + cl] = pool[(int64_t)j * ld + c0 + cl];
-  auto pool_at = [&](int r) { return POOL ? pl[r * C + cl] : pool[(int64_t)r * ld + c0 + cl]; };
-  int b = begin[gen - 1], e = begin[gen];
-  ReplayNode nd{};
-  if (b + lane < e) nd = nodes[b + lane];
-  for (int g = 1; g <= gen; ++g) {
-    // the next generation's nodes
-    const int b2 = g < gen ? begin[gen - g - 1] : e, e2 = g < gen ? b : e;
-    __syncthreads();
-    for (int q = b + lane; q < e; q += lanes) {
-      const ReplayNode now = nd;
-      // the thread's next node in this generation, or its first in the next one
-      if (q + lanes < e)
-        nd = nodes[q + lanes];
-      else if (b2 + lane < e2)
-        nd = nodes[b2 + lane];
-      const double a = cur[now.a * C + cl];
-      const double bb = now.op == 1 ? cur[now.b * C + cl] : 0.0;
-      const double r1 = now.op != 2 ? pool_at(now.r1) : 0.0;
-      const double r2 = now.op == 0 ? pool_at(now.r2) : 0.0;
-      nxt[now.out * C + cl] = replay_step(now, a, bb, r1, r2);
+    for (int j = lane; j < np; j += lanes) put(pl, j, pool_plane, get(pool + c0, j, ld, P));
+  auto pool_at = [&](int r) { return POOL ? get(pl, r, P, pool_plane) : get(pool + c0, r, ld, P); };
+  // nodes of generation g: begin[gen - g] .. begin[gen - g + 1] - 1
+  const int last = begin[gen] - 1;
+  auto node = [&](int q) { return nodes[q < last ? q : last]; };
+  // A lane of each wave holds the start of one of 64 generations and moves on
+  // by 48: a scalar load would be waited for with every LDS read.
+  const int wl = threadIdx.x % kWave;
+  constexpr int kMove = kWave - 16;
+  auto starts = [&](int g) { return begin[g + wl < gen ? gen - g - wl : 0]; };
+  int base = 0, held = starts(0), held_next = starts(kMove);
+  auto start = [&](int g) { return __builtin_amdgcn_readlane(held, g - base); };
+  struct Ahead {
+    int from, end;
+    ReplayNode x;
+  };
+  auto read = [&](int g) {
+    const int from = start(g);
+    return Ahead{from, start(g - 1), node(from + lane)};
+  };
+  auto step = [&](const ReplayNode& x) {
+    const Part a = get(cur, x.a, P, plane), r1 = x.op == 2 ? a : pool_at(x.r1);
+    Part o = a;
+    if (x.op == 1) {
+      const Part b = get(cur, x.b, P, plane);
+#pragma unroll
+      for (int v = 0; v < C; ++v)
+        o.h[v / P].v[v % P] = replay_mix(a.h[v / P].v[v % P], b.h[v / P].v[v % P], r1.h[v / P].v[v % P]);
+    } else if (x.op == 0) {
+      const Part r2 = pool_at(x.r2);
+#pragma unroll
+      for (int v = 0; v < C; ++v)
+        o.h[v / P].v[v % P] = replay_mutant(x, a.h[v / P].v[v % P], r1.h[v / P].v[v % P], r2.h[v / P].v[v % P]);
     }
-    // threads without a node in this generation read their next one here
-    if (b + lane >= e && b2 + lane < e2) nd = nodes[b2 + lane];
-    b = b2;
-    e = e2;
+    if (replay_scaled(x)) {
+#pragma unroll
+      for (int v = 0; v < C; ++v) o.h[v / P].v[v % P] = x.alpha + x.beta * o.h[v / P].v[v % P];
+    }
+    put(nxt, x.out, plane, o);
+  };
+  auto generation = [&](int g, Ahead& q) {
+    __syncthreads();
+    const int from = q.from + lane;
+    if (from < q.end) step(q.x);
+    if (q.end - q.from > lanes) {
+      ReplayNode then = node(from + lanes);
+      for (int i = from + lanes; i < q.end; i += lanes) {
+        const ReplayNode x = then;
+        then = node(i + lanes);
+        step(x);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    q = read(g + 2);  // into the same registers: a copy would wait for it
+    __builtin_amdgcn_sched_barrier(0);
     double* t = cur;
     cur = nxt;
     nxt = t;
+  };
+  int g = 1;
+  if (gen & 1) {
+    Ahead q = read(1);
+    generation(g++, q);
+  }
+  Ahead odd = read(g);
+  __builtin_amdgcn_sched_barrier(0);
+  Ahead even = read(g + 1);
+  __builtin_amdgcn_sched_barrier(0);
+  for (; g < gen; g += 2) {
+    if (g + 3 - base >= kWave) {
+      base += kMove;
+      held = held_next;
+      held_next = starts(base + kMove);
+    }
+    generation(g, odd);
+    generation(g + 1, even);
   }
   __syncthreads();
-  if (lane == 0 && c0 + cl < n) out[c0 + cl] = cur[out_slot * C + cl];
+  if (lane < C && c0 + lane < n) out[c0 + lane] = cur[out_slot * P + lane / P * plane + lane % P];
 }
 
 // ---------------------------------------------------------------------------
@@ -1782,21 +1939,40 @@ hipError_t launch_transpose(const double* X, int64_t n, int32_t l, double* Xfm, 
   return hipGetLastError();
 }
 
-hipError_t launch_lineage(const RunDev* d_runs, const Params& p, int32_t run, int32_t gen, int32_t individual,
-                          int32_t* begin, int32_t* tree0, int32_t* pool, ReplayNode* nodes, int64_t node_cap,
-                          LineageSummary* out, hipStream_t s) {
+hipError_t launch_lineage(const RunDev& R, const Params& p, int32_t gen, int32_t individual, int32_t* begin,
+                          int32_t* tree0, int32_t* pool, int32_t* slots, LineageSummary* out, hipStream_t s) {
   const int64_t lds = lineage_lds(p.m, p.r);
   if (lds > kReplayLdsBytes || gen < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_lineage, dim3(1), dim3(1024), (size_t)lds, s, d_runs, p, run, gen, individual, begin, tree0, pool,
-                     nodes, node_cap, out);
+  const dim3 block((unsigned)(p.m < 1024 ? (p.m + kWave - 1) / kWave * kWave : 1024));
+  const int k = (p.m + 1023) / 1024;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(1), block, (size_t)lds, s, R.rec, R.stats, p, gen, individual, begin, tree0, pool,
+                       slots, out);
+    return hipGetLastError();
+  };
+  if (k <= 1) return go(k_lineage<1>);
+  if (k <= 2) return go(k_lineage<2>);
+  if (k <= 4) return go(k_lineage<4>);
+  return k <= kLineagePop / 1024 ? go(k_lineage<kLineagePop / 1024>) : hipErrorInvalidValue;
+}
+
+hipError_t launch_lineage_nodes(const RunDev& R, const Params& p, int32_t gen, const int32_t* begin,
+                                const int32_t* slots, ReplayNode* nodes, hipStream_t s) {
+  const dim3 block((unsigned)(p.m < 1024 ? (p.m + kWave - 1) / kWave * kWave : 1024));
+  hipLaunchKernelGGL(k_lineage_nodes, dim3((unsigned)gen), block, 0, s, R.rec, R.stats, p.ls ? R.ls : nullptr, p.m,
+                     gen, begin, slots, nodes);
   return hipGetLastError();
 }
 
-// Cases per block of k_replay_lineage: the most whose two generations of
-// rows fit in LDS, 0 when not even one case's do.  More cases a block read
-// each node less often, and 8 make a row's segment of a cache line.
-int replay_cases(int64_t slots) {
-  for (int c = 8; c >= 1; c >>= 1)
+// Cases per block of k_replay_lineage whose two generations of rows fit in
+// LDS, 0 when not even one case's do.  More cases a block read each node less
+// often and with more loads in flight.  When nodes were read one generation
+// ahead: 532 us for 4, 628 for 2 and 1,147 for 1 (10,000 cases, 200
+// generations with at most 251 live rows); 913 for 8, whose rows leave a CU
+// one block.  Where every block is resident anyway, fewer have the shorter
+// chain: 42, 36 and 35 us for 16 cases.
+int replay_cases(int64_t slots, int64_t n) {
+  for (int c = n > 512 ? 4 : 2; c >= 1; c >>= 1)
     if (2 * slots * c * (int64_t)sizeof(double) <= kReplayLdsBytes) return c;
   return 0;
 }
@@ -1815,20 +1991,19 @@ void launch_replay_lineage_as(bool pool_lds, dim3 grid, dim3 block, size_t shmem
 }
 
 hipError_t launch_replay_lineage(const ReplayNode* nodes, const int32_t* begin, int32_t gen, int32_t n0, int32_t np,
-                                 int32_t slots, int64_t total_nodes, int32_t out_slot, const double* first,
+                                 int32_t slots, int32_t out_slot, const double* first,
                                  const double* pool, int64_t ld, int64_t n, double* out, hipStream_t s) {
-  const int c = replay_cases(slots);
+  const int c = replay_cases(slots, n);
   if (c == 0 || gen < 1) return hipErrorInvalidValue;
   size_t shmem = 2 * (size_t)slots * c * sizeof(double);
-  const size_t pool_bytes = (size_t)np * c * sizeof(double);
+  const size_t pool_bytes = (size_t)(np > 0 ? np : 1) * c * sizeof(double);  // slot 0 is read where there is none
   const bool pool_lds = shmem + pool_bytes <= (size_t)kReplayLdsBytes;
   if (pool_lds) shmem += pool_bytes;
   // one sweep of the threads per generation where a block may be that large
-  const int64_t want = (total_nodes + gen - 1) / gen * c;
+  const int64_t want = slots;
   const int threads = (int)(want > 1024 ? 1024 : (want + kWave - 1) / kWave * kWave);
   const dim3 grid((unsigned)((n + c - 1) / c)), block(threads);
   switch (c) {
-    case 8: launch_replay_lineage_as<8>(pool_lds, grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot, first, pool, ld, n, out); break;
     case 4: launch_replay_lineage_as<4>(pool_lds, grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot, first, pool, ld, n, out); break;
     case 2: launch_replay_lineage_as<2>(pool_lds, grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot, first, pool, ld, n, out); break;
     default: launch_replay_lineage_as<1>(pool_lds, grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot, first, pool, ld, n, out); break;

@@ -1212,16 +1212,18 @@ struct Lineage {
 };
 
 // Populations from this size on are walked on the device: a generation takes
-// about 2 us there whatever m, and 0.009 us per individual on the host (its
-// records are copied out).
-constexpr int32_t kDeviceWalkPop = 256;
+// 0.5 to 1 us there, and 0.009 us per individual on the host (its records are
+// copied out).
+constexpr int32_t kDeviceWalkPop = 64;
 
 // The walk on the device, into the population buffer that holds no generation
 // (see fetch_semantics); on_device stays false where the maps or the replay do
 // not fit LDS or the lists and nodes do not fit that buffer.
-gsgp_status walk_on_device(gsgp_handle* h, int32_t run, int32_t gen, int32_t individual, Lineage* L) {
+gsgp_status walk_on_device(gsgp_handle* h, int32_t run, int32_t gen, int32_t individual, int64_t n, bool nodes,
+                           Lineage* L) {
   const int64_t m = h->cfg.pop_size, r = h->cfg.pool_size;
-  if (gen < 1 || m < kDeviceWalkPop || lineage_lds(m, r) > kReplayLdsBytes || gen * m > INT32_MAX) return GSGP_OK;
+  if (gen < 1 || m < kDeviceWalkPop || m > kLineagePop || lineage_lds(m, r) > kReplayLdsBytes || gen * m > INT32_MAX)
+    return GSGP_OK;
   const RunDev& R = h->runs_h[run];
   char* at = (char*)R.S[(h->gen & 1) ^ 1];
   const size_t bytes = storage_bytes(h->cfg.precision) * m * R.ld;
@@ -1234,15 +1236,16 @@ gsgp_status walk_on_device(gsgp_handle* h, int32_t run, int32_t gen, int32_t ind
   L->d_begin = (int32_t*)take(sizeof(int32_t) * (gen + 1));
   L->d_tree0 = (int32_t*)take(sizeof(int32_t) * m);
   L->d_pool = (int32_t*)take(sizeof(int32_t) * r);
+  int32_t* slots = (int32_t*)take(sizeof(int32_t) * lineage_slots(m, r, gen));
   L->d_nodes = (ReplayNode*)(at + off);
   if (off > bytes) return GSGP_OK;
-  const int64_t cap = (int64_t)((bytes - off) / sizeof(ReplayNode));
   const OnDevice here(h);
   LineageSummary* sum = (LineageSummary*)h->pinned;
-  HIPCHK(h, launch_lineage(h->runs_d, h->params, run, gen, individual, L->d_begin, L->d_tree0, L->d_pool, L->d_nodes,
-                           cap, sum, h->stream));
+  HIPCHK(h, launch_lineage(R, h->params, gen, individual, L->d_begin, L->d_tree0, L->d_pool, nodes ? slots : nullptr,
+                           sum, h->stream));
   HIPCHK(h, hipStreamSynchronize(h->stream));
-  if (sum->total_nodes > cap || replay_cases(sum->max_slots) == 0) return GSGP_OK;
+  if (off + sizeof(ReplayNode) * sum->total_nodes > bytes || replay_cases(sum->max_slots, n) == 0) return GSGP_OK;
+  if (nodes) HIPCHK(h, launch_lineage_nodes(R, h->params, gen, L->d_begin, slots, L->d_nodes, h->stream));
   L->on_device = true;
   L->n0 = sum->n0;
   L->np = sum->np;
@@ -1295,7 +1298,7 @@ gsgp_status walk_on_host(gsgp_handle* h, int32_t run, int32_t gen, int32_t indiv
     before.clear();
     for (size_t j = 0; j < now.size(); ++j) {
       const int32_t i = now[j];
-      ReplayNode nd{2, 0, -1, -1, -1, (int32_t)j, 0.0, 0.0, 1.0};
+      ReplayNode nd{2, 0, 0, 0, 0, (int32_t)j, 0.0, 0.0, 1.0};
       if (s.elite_copied && i == s.elite_dst) {
         nd.a = parent_at(s.elite_src);
       } else {
@@ -1316,6 +1319,7 @@ gsgp_status walk_on_host(gsgp_handle* h, int32_t run, int32_t gen, int32_t indiv
       }
       L->nodes.push_back(nd);
     }
+    std::partition(L->nodes.end() - now.size(), L->nodes.end(), [](const ReplayNode& q) { return q.op == 1; });
     L->count[g] = (int32_t)now.size();
     L->max_slots = std::max(L->max_slots, now.size());
     for (int32_t p : before) slot[p] = -1;
@@ -1331,9 +1335,10 @@ gsgp_status walk_on_host(gsgp_handle* h, int32_t run, int32_t gen, int32_t indiv
 
 // The lineage of `individual` and the scratch its reconstruction on n cases
 // needs.
-gsgp_status walk_lineage(gsgp_handle* h, int32_t run, int32_t gen, int32_t individual, int64_t n, Lineage* L) {
+gsgp_status walk_lineage(gsgp_handle* h, int32_t run, int32_t gen, int32_t individual, int64_t n, bool nodes,
+                         Lineage* L) {
   const RunDev& R = h->runs_h[run];
-  gsgp_status st = walk_on_device(h, run, gen, individual, L);
+  gsgp_status st = walk_on_device(h, run, gen, individual, n, nodes, L);
   if (st == GSGP_OK && !L->on_device) st = walk_on_host(h, run, gen, individual, L);
   if (st != GSGP_OK) return st;
   L->ld = pad_to(n, kSegPad);
@@ -1366,7 +1371,7 @@ gsgp_status gsgp_reconstruct_scratch_size(gsgp_handle* h, int32_t run, int32_t g
   if (individual < 0 || individual >= h->cfg.pop_size) return fail(GSGP_ERR_ARG, "individual out of range");
   if (n < 1 || n > ((int64_t)1 << 40)) return fail(GSGP_ERR_ARG, "n must be >= 1");
   Lineage L;
-  st = walk_lineage(h, run, gen, individual, n, &L);
+  st = walk_lineage(h, run, gen, individual, n, false, &L);
   if (st != GSGP_OK) return st;
   *bytes = L.total;
   return GSGP_OK;
@@ -1457,7 +1462,7 @@ gsgp_status check_reconstruct_args(gsgp_handle* h, int32_t run, int32_t gen, int
 gsgp_status reconstruct_with(gsgp_handle* h, int32_t run, int32_t gen, int32_t individual, const double* d_X,
                              int64_t n, double* d_out, char* sc, size_t scratch_bytes, const char* whose) {
   Lineage L;
-  gsgp_status st = walk_lineage(h, run, gen, individual, n, &L);
+  gsgp_status st = walk_lineage(h, run, gen, individual, n, true, &L);
   if (st != GSGP_OK) return st;
   if (scratch_bytes < L.total)
     return fail(GSGP_ERR_WORKSPACE, "%s has %zu bytes, this reconstruction needs %zu", whose, scratch_bytes, L.total);
@@ -1475,7 +1480,7 @@ gsgp_status reconstruct_with(gsgp_handle* h, int32_t run, int32_t gen, int32_t i
   const ReplayNode* d_nodes = L.d_nodes;
   // One launch for the lineage when two generations of at least one case fit
   // in LDS; the second row buffer, unused then, holds the node ranges.
-  bool one_launch = gen > 0 && replay_cases((int64_t)L.max_slots) > 0;
+  bool one_launch = gen > 0 && replay_cases((int64_t)L.max_slots, n) > 0;
   std::vector<int32_t> lists, begin(1, 0);
   if (!L.on_device) {
     lists.reserve(L.n0 + L.np);
@@ -1502,7 +1507,7 @@ gsgp_status reconstruct_with(gsgp_handle* h, int32_t run, int32_t gen, int32_t i
   // the individual's slot is 0: the walk starts with it
   if (one_launch) {
     HIPCHK(h, launch_replay_lineage(d_nodes, d_begin, gen, (int32_t)L.n0, (int32_t)L.np, (int32_t)L.max_slots,
-                                    (int64_t)L.total_nodes, 0, bufA, pool, L.ld, n, d_out, h->stream));
+                                    0, bufA, pool, L.ld, n, d_out, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
     return GSGP_OK;
   }
