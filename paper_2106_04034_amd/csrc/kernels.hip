@@ -540,13 +540,41 @@ __device__ __forceinline__ ValIdx pick_max(ValIdx a, ValIdx b) {
   return (b.v > a.v || (b.v == a.v && b.i < a.i)) ? b : a;
 }
 
-// Extrema over groups of W neighbouring lanes (a power of two).
+// A value and index from the lane that DPP control CTRL names.
+template <int CTRL>
+__device__ __forceinline__ ValIdx dpp_move(ValIdx x) {
+  const uint64_t v = __builtin_bit_cast(uint64_t, x.v);
+  const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)v, CTRL, 0xf, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), CTRL, 0xf, 0xf, false);
+  return ValIdx{__builtin_bit_cast(double, (uint64_t)hi << 32 | lo), __builtin_amdgcn_mov_dpp(x.i, CTRL, 0xf, 0xf, false)};
+}
+
+__device__ __forceinline__ ValIdx read_lane(ValIdx x, int lane) {
+  const uint64_t v = __builtin_bit_cast(uint64_t, x.v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
+  return ValIdx{__builtin_bit_cast(double, (uint64_t)hi << 32 | lo), __builtin_amdgcn_readlane(x.i, lane)};
+}
+
+// Extrema over groups of W lanes, 16 or 64: within a row of 16 by DPP (its
+// pairs, its quads' halves, the halves of its halves, its halves), and the
+// four rows through scalar registers; a round through LDS (__shfl_xor) waits
+// about 100 cycles for its six reads.
 template <int W>
 __device__ __forceinline__ void lane_extrema(ValIdx& lo, ValIdx& hi) {
+  static_assert(W == 16 || W == kWave, "a DPP row or a wave");
+  auto round = [&](ValIdx l, ValIdx h) {
+    lo = pick_min(lo, l);
+    hi = pick_max(hi, h);
+  };
+  round(dpp_move<0xb1>(lo), dpp_move<0xb1>(hi));    // quad_perm 1, 0, 3, 2
+  round(dpp_move<0x4e>(lo), dpp_move<0x4e>(hi));    // quad_perm 2, 3, 0, 1
+  round(dpp_move<0x141>(lo), dpp_move<0x141>(hi));  // row_half_mirror
+  round(dpp_move<0x140>(lo), dpp_move<0x140>(hi));  // row_mirror
+  if constexpr (W == kWave) {
+    const ValIdx l = lo, h = hi;
 #pragma unroll
-  for (int o = W / 2; o >= 1; o >>= 1) {
-    lo = pick_min(lo, ValIdx{__shfl_xor(lo.v, o, kWave), __shfl_xor(lo.i, o, kWave)});
-    hi = pick_max(hi, ValIdx{__shfl_xor(hi.v, o, kWave), __shfl_xor(hi.i, o, kWave)});
+    for (int row = 0; row < 4; ++row) round(read_lane(l, 16 * row), read_lane(h, 16 * row));
   }
 }
 
@@ -818,13 +846,75 @@ __device__ gsgp_record draw_record(const Params& p, uint32_t run_id, int gen_dra
   return rc;
 }
 
+// draw_record in two halves for tournaments of up to kAheadTournament: the
+// candidates and their fitness are read before it is known which individual
+// the elite replaces (`dst`, fitness f_dst, or -1), all of them at once.  A
+// tournament that reads one candidate after the other is a chain of L2 reads.
+constexpr int kAheadTournament = 4;
+struct DrawAhead {
+  Words4 w;
+  uint32_t w4;
+  int32_t c[2 * kAheadTournament];
+  double f[2 * kAheadTournament];
+};
+
+__device__ __forceinline__ DrawAhead draw_ahead(const Params& p, uint32_t run_id, int gen_draw, int i,
+                                                const GSGP_GLOBAL double* F) {
+  DrawAhead d;
+  d.w = philox4x32_10((uint32_t)i, 0, (uint32_t)gen_draw, 3u, p.seed, run_id);
+  const Words4 a = philox4x32_10((uint32_t)i, 1, (uint32_t)gen_draw, 3u, p.seed, run_id);
+  const Words4 b = philox4x32_10((uint32_t)i, 2, (uint32_t)gen_draw, 3u, p.seed, run_id);
+  const Words4 c = philox4x32_10((uint32_t)i, 3, (uint32_t)gen_draw, 3u, p.seed, run_id);
+  d.w4 = a.w0;
+  const uint32_t word[2 * kAheadTournament] = {a.w1, a.w2, a.w3, b.w0, b.w1, b.w2, b.w3, c.w0};
+#pragma unroll
+  for (int q = 0; q < 2 * kAheadTournament; ++q) {
+    d.c[q] = q < 2 * p.tsize ? draw_below(word[q], (uint32_t)p.m) : 0;
+    d.f[q] = F[d.c[q]];
+  }
+  return d;
+}
+
+__device__ __forceinline__ gsgp_record draw_finish(const Params& p, const DrawAhead& d, int dst, double f_dst) {
+  int32_t best[2] = {0, 0};
+  double fb[2] = {INFINITY, INFINITY};
+#pragma unroll
+  for (int q = 0; q < 2 * kAheadTournament; ++q) {
+    if (q >= 2 * p.tsize) continue;
+    const double f = d.c[q] == dst ? f_dst : d.f[q];
+    const bool second = q >= p.tsize;
+    // the first candidate of each tournament, then strictly smaller ones
+    if (q == 0 || q == p.tsize || f < fb[second]) {
+      if (second) {
+        best[1] = d.c[q];
+        fb[1] = f;
+      } else {
+        best[0] = d.c[q];
+        fb[0] = f;
+      }
+    }
+  }
+  const bool xo = (uint64_t)d.w.w0 < p.t_xo;
+  gsgp_record rc;
+  rc.reserved = 0;
+  rc.op = xo ? 1 : 0;
+  rc.p1 = best[0];
+  rc.p2 = xo ? best[1] : -1;
+  rc.r1 = draw_below(d.w.w1, (uint32_t)p.r);
+  rc.r2 = xo ? -1 : draw_below(d.w.w2, (uint32_t)p.r);
+  rc.ms = xo ? 0.0 : p.ms_random ? p.ms * draw_u53(d.w.w3, d.w4) : p.ms;
+  return rc;
+}
+
 // Best and worst of a run's fitness from its groups' extremes: every wave
-// reduces them for itself, so no barrier is needed.
-__device__ __forceinline__ void run_extrema(const RunDev& R, int m, ValIdx& lo, ValIdx& hi) {
+// reduces them for itself, so no barrier is needed; `first` is the lane's
+// first group's, where it has one.
+__device__ __forceinline__ void run_extrema(const RunDev& R, int m, const Extremes& first, ValIdx& lo, ValIdx& hi) {
   const int groups = (m + kFitGroup - 1) / kFitGroup;
-  lo = ValIdx{INFINITY, 0x7fffffff};
-  hi = ValIdx{-INFINITY, 0x7fffffff};
-  for (int g = threadIdx.x & 63; g < groups; g += kWave) {
+  const int lane = threadIdx.x & 63;
+  lo = lane < groups ? ValIdx{first.min, first.min_i} : ValIdx{INFINITY, 0x7fffffff};
+  hi = lane < groups ? ValIdx{first.max, first.max_i} : ValIdx{-INFINITY, 0x7fffffff};
+  for (int g = lane + kWave; g < groups; g += kWave) {
     const Extremes e = R.extremes[g];
     lo = pick_min(lo, ValIdx{e.min, e.min_i});
     hi = pick_max(hi, ValIdx{e.max, e.max_i});
@@ -846,41 +936,59 @@ __device__ __forceinline__ void run_extrema(const RunDev& R, int m, ValIdx& lo, 
 // a block) and the draws (64 a block: with the copy going on, one wave takes
 // them; a row of a few cases gave two blocks, whose one wave each drew 512).
 // The last block to arrive publishes the elite fitness and advances the
-// generation counter.  Bound by latency (the chain of counter, extremes,
-// decision, draws, arrival): 1,024 individuals on 5,000 cases 14.2 -> 7.5 us,
-// on 100,000 11.0 -> 8.1 us, 10,240 on 102,400 26.1 -> 9.5 us, 64 runs of 256
-// 15.7 -> 10.3 us.
+// generation counter.  Bound by latency: extremes, the last best and the
+// tournaments' candidates are read before any of them is waited for, and the
+// decision's reduction goes by DPP.  1,024 individuals on 5,000 cases 4.8 us,
+// on 100,000 5.9 us; 7.7 and 8.4 us when the draws began after the decision,
+// 14.2 and 11.0 us when every block reduced the whole fitness.
 template <typename T>
 __global__ __launch_bounds__(256) void k_survive(const RunDev* __restrict__ runs, Params p,
                                                  int32_t total, int mode) {
   __shared__ ValIdx sh[8];
-  __shared__ int is_last;
   const int run = find_run(p.n_runs, (int64_t)blockIdx.x, [&](int r) { return (int64_t)runs[r].surv_blk0; });
   const RunDev& R = runs[run];
   const int bl = blockIdx.x - R.surv_blk0;
   const int nb = R.surv_blks;
   const int m = p.m;
-  const int gen = (mode == kSurvInit) ? 0 : R.state[kStGen];
-  const int replay_elite = R.state[kStReplayElite];
-  const int replay_select = R.state[kStReplaySelect];
+  const int gen = (mode == kSurvInit) ? 0 : uni(cload(&R.state[kStGen]));
+  const int replay_elite = uni(cload(&R.state[kStReplayElite]));
+  const int replay_select = uni(cload(&R.state[kStReplaySelect]));
   const int cur = gen & 1, nxt = cur ^ 1;
-  const double* FP = R.F[cur];
-  const double* FtP = R.Ft[cur];
-  double* FO = R.F[nxt];
-  double* FtO = R.Ft[nxt];
+  const GSGP_GLOBAL double* FP = (const GSGP_GLOBAL double*)R.F[cur];
+  const GSGP_GLOBAL double* FtP = (const GSGP_GLOBAL double*)R.Ft[cur];
+  GSGP_GLOBAL double* FO = (GSGP_GLOBAL double*)R.F[nxt];
+  GSGP_GLOBAL double* FtO = (GSGP_GLOBAL double*)R.Ft[nxt];
   const bool gen_mode = mode == kSurvGen;
   int copied = 0, src = -1, dst = -1;
   ValIdx bo{0.0, 0}, wo{0.0, 0};
-  if (mode != kSurvSelectOnly) run_extrema(R, m, bo, wo);  // of the offspring, or of generation 0
+  // What the decision and the draws read, before either waits for it.
+  const int lane = threadIdx.x & 63;
+  const GSGP_GLOBAL Extremes* ex =
+      (const GSGP_GLOBAL Extremes*)R.extremes + (lane < (m + kFitGroup - 1) / kFitGroup ? lane : 0);
+  const Extremes first{ex->min, ex->max, ex->min_i, ex->max_i};
+  const GSGP_GLOBAL gsgp_gen_stats* stats = (const GSGP_GLOBAL gsgp_gen_stats*)R.stats;
+  const double prev_best = gen_mode ? stats[gen].best_train_rmse : 0.0;
+  const int prev_index = gen_mode ? stats[gen].best_index : 0;
+  const int gen_draw = gen_mode ? gen + 2 : gen + 1;
+  const bool draws = !replay_select && gen_draw <= p.gmax;
+  const bool ahead = draws && p.tsize > 0 && p.tsize <= kAheadTournament;
+  const int per_draw = (m + nb - 1) / nb;
+  const int i0 = per_draw * bl;
+  const int i1 = (i0 + per_draw) < m ? (i0 + per_draw) : m;
+  const GSGP_GLOBAL double* F = gen_mode ? FO : FP;
+  DrawAhead mine;
+  if (ahead && i0 + (int)threadIdx.x < i1) mine = draw_ahead(p, R.run_id, gen_draw, i0 + (int)threadIdx.x, F);
+  const double f_prev = gen_mode && (uint32_t)prev_index < (uint32_t)m ? FP[prev_index] : 0.0;
+  if (mode != kSurvSelectOnly) run_extrema(R, m, first, bo, wo);  // of the offspring, or of generation 0
   if (gen_mode) {
     if (replay_elite) {
       const gsgp_gen_stats e = R.elite_in[gen];
       copied = e.elite_copied;
       src = e.elite_src;
       dst = e.elite_dst;
-    } else if (R.stats[gen].best_train_rmse < bo.v) {
+    } else if (prev_best < bo.v) {
       copied = 1;
-      src = R.stats[gen].best_index;
+      src = prev_index;
       dst = wo.i;
     }
     if (copied) {
@@ -921,7 +1029,7 @@ __global__ __launch_bounds__(256) void k_survive(const RunDev* __restrict__ runs
       }
     }
   }
-  const double f_src = copied ? FP[src] : 0.0;
+  const double f_src = copied ? (replay_elite ? FP[src] : f_prev) : 0.0;
   // when the other waves copied the elite row, wave 0 alone takes the draws
   const bool draw_split = copied && blockDim.x > kWave;
   // fitness of the individuals the next draw selects from
@@ -948,25 +1056,21 @@ __global__ __launch_bounds__(256) void k_survive(const RunDev* __restrict__ runs
       R.stats[gen_mode ? gen + 1 : 0] = st;
     }
   }
-  const int gen_draw = gen_mode ? gen + 2 : gen + 1;
-  if (!replay_select && gen_draw <= p.gmax) {
-    const int per = (m + nb - 1) / nb;
-    const int i0 = per * bl;
-    const int i1 = (i0 + per) < m ? (i0 + per) : m;
+  if (draws) {
     gsgp_record* out = R.rec + (int64_t)(gen_draw - 1) * m;
     const int dn = draw_split ? kWave : (int)blockDim.x;  // threads taking draws
     for (int i = i0 + (int)threadIdx.x; (int)threadIdx.x < dn && i < i1; i += dn) {
-      out[i] = gen_mode ? draw_record(p, R.run_id, gen_draw, i, view_new)
-                        : draw_record(p, R.run_id, gen_draw, i, view_cur);
+      if (ahead) {
+        if (i != i0 + (int)threadIdx.x) mine = draw_ahead(p, R.run_id, gen_draw, i, F);
+        out[i] = draw_finish(p, mine, copied ? dst : -1, f_src);
+      } else {
+        out[i] = gen_mode ? draw_record(p, R.run_id, gen_draw, i, view_new)
+                          : draw_record(p, R.run_id, gen_draw, i, view_cur);
+      }
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const int old = atomicAdd(&R.state[kStDone], 1);
-    is_last = (old == nb - 1);
-  }
-  __syncthreads();
-  if (is_last && threadIdx.x == 0) {
+  if (threadIdx.x == 0 && atomicAdd(&R.state[kStDone], 1) == nb - 1) {
     R.state[kStDone] = 0;
     if (gen_mode) {
       if (copied) {
