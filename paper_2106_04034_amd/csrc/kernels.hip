@@ -140,33 +140,81 @@ __global__ __launch_bounds__(256) void k_genome(const RunDev* __restrict__ runs,
 }
 
 // ---------------------------------------------------------------------------
-// Wave reductions.  xor butterflies give every lane the same bits because
-// each step adds the same two operands in both partner lanes.
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+// Wave reductions.  A butterfly over lane distances 32, 16, 8, 4, 2, 1: each
+// step adds the same two operands in both partner lanes, so every lane has the
+// same bits.  It stays in the vector registers: halves and rows of 16 trade
+// places (permlane swaps), then a row rotates by DPP (after the step of
+// distance 8 the values repeat every 8 lanes, so a rotation by 4 reaches the
+// partner at distance 4, and so on).  Through LDS (__shfl_xor) a step took a
+// round trip and the LDS pipe of the CU: 128 individuals on 700 FP64 cases 4.2
+// -> 3.8 us a generation, local search (three sums) 27.9 -> 27.0 us for 512 on
+// 25,000 cases, blocks of 15 generations 160 -> 132 us for 2,048 on 10,240.
+struct LanePair {
+  uint32_t own, other;
+};
+template <int O>
+__device__ __forceinline__ LanePair lane_pair(uint32_t v) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  if constexpr (O == 32) {
+    const u2 r = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(v, v, false, false));
+    return LanePair{r[0], r[1]};
+  } else if constexpr (O == 16) {
+    const u2 r = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(v, v, false, false));
+    return LanePair{r[0], r[1]};
+  } else {
+    static_assert(O == 8 || O == 4 || O == 2 || O == 1, "a distance of the butterfly");
+    return LanePair{v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x120 + 16 - O, 0xf, 0xf, false)};  // row_ror
+  }
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, kWave);
+template <int O>
+__device__ __forceinline__ void lane_pair(float v, float& own, float& other) {
+  const LanePair q = lane_pair<O>(__builtin_bit_cast(uint32_t, v));
+  own = __builtin_bit_cast(float, q.own);
+  other = __builtin_bit_cast(float, q.other);
+}
+template <int O>
+__device__ __forceinline__ void lane_pair(double v, double& own, double& other) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const LanePair lo = lane_pair<O>((uint32_t)u), hi = lane_pair<O>((uint32_t)(u >> 32));
+  own = __builtin_bit_cast(double, (uint64_t)hi.own << 32 | lo.own);
+  other = __builtin_bit_cast(double, (uint64_t)hi.other << 32 | lo.other);
+}
+
+// step(O) for the distances of the butterfly in turn
+template <typename Step>
+__device__ __forceinline__ void butterfly(Step step) {
+  step(std::integral_constant<int, 32>{});
+  step(std::integral_constant<int, 16>{});
+  step(std::integral_constant<int, 8>{});
+  step(std::integral_constant<int, 4>{});
+  step(std::integral_constant<int, 2>{});
+  step(std::integral_constant<int, 1>{});
+}
+
+template <typename A>
+__device__ __forceinline__ A wave_sum(A v) {
+  butterfly([&](auto o) {
+    A own, other;
+    lane_pair<decltype(o)::value>(v, own, other);
+    v = own + other;
+  });
   return v;
 }
 
 // Compensated combination of Kahan pairs (value = s - c) with Knuth's
 // two-sum: exact error of s1 + s2 is folded into the compensation term.
 __device__ __forceinline__ void wave_sum_kahan(float& s, float& c) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const float s2 = __shfl_xor(s, o, kWave);
-    const float c2 = __shfl_xor(c, o, kWave);
-    const float sum = s + s2;
-    const float bp = sum - s;
-    const float err = (s - (sum - bp)) + (s2 - bp);
-    c = (c + c2) - err;
+  butterfly([&](auto o) {
+    float s1, s2, c1, c2;
+    lane_pair<decltype(o)::value>(s, s1, s2);
+    lane_pair<decltype(o)::value>(c, c1, c2);
+    const float sum = s1 + s2;
+    const float bp = sum - s1;
+    const float err = (s1 - (sum - bp)) + (s2 - bp);
+    c = (c1 + c2) - err;
     s = sum;
-  }
+  });
 }
 
 // Sum over one chunk of (o - t)^2 in the canonical order: each lane adds its
@@ -1996,12 +2044,20 @@ hipError_t launch_fitness(const RunDev* d_runs, const Params& p, bool init, hipS
   return hipGetLastError();
 }
 
+// Where a chunk's pool column is far larger than an XCD's L2, rows come from
+// the memory-side cache, and three blocks a CU (an LDS reservation keeps the
+// others out) ask for as much as it gives: pool columns of 20 MiB 12.7 -> 12.4
+// ms; of 12 MiB 3.22 -> 3.34, of 4 MiB 0.64 -> 0.97.
+constexpr size_t kFarPoolBytes = 16 << 20;
+constexpr size_t kFewBlocksLds = 53 << 10;
+
 template <typename T, int PREC>
 hipError_t launch_block_as(const RunDev* d_runs, const Params& p, const VaryLaunch& lc, int32_t gens,
                            int32_t row_blocks, hipStream_t s) {
   const int64_t draws = (int64_t)p.n_runs * gens * p.m;
   hipLaunchKernelGGL(k_block_draws, dim3(blocks_for(draws, 256)), dim3(256), 0, s, d_runs, p, gens, draws);
-  hipLaunchKernelGGL((k_mutate_block<T, PREC>), dim3((unsigned)lc.grid), dim3(lc.waves * kWave), 0, s, d_runs, p, lc, gens);
+  hipLaunchKernelGGL((k_mutate_block<T, PREC>), dim3((unsigned)lc.grid), dim3(lc.waves * kWave),
+                     (size_t)p.r * kChunkBytes > kFarPoolBytes ? kFewBlocksLds : 0, s, d_runs, p, lc, gens);
   const int32_t per_run = (p.m + kFitGroup - 1) / kFitGroup;
   hipLaunchKernelGGL(k_block_fitness, dim3((unsigned)(per_run * p.n_runs), (unsigned)gens), dim3(kFitRanges * kFitGroup),
                      0, s, d_runs, p, per_run, gens);
