@@ -48,6 +48,12 @@ __device__ __forceinline__ VT gload(const void* p) {
   return *(const GSGP_GLOBAL VT*)p;
 }
 
+// A load and a store of what is not used again soon.
+template <typename VT>
+__device__ __forceinline__ VT gload_nt(const void* p) {
+  return __builtin_nontemporal_load((const GSGP_GLOBAL VT*)p);
+}
+
 template <typename VT>
 __device__ __forceinline__ void gstore_nt(const VT& v, void* p) {
   __builtin_nontemporal_store(v, (GSGP_GLOBAL VT*)p);

@@ -1200,9 +1200,10 @@ __global__ __launch_bounds__(256) void k_block_draws(const RunDev* __restrict__ 
     R.rec[(int64_t)(g - 1) * p.m + i] = draw_record(p, R.run_id, g, i, [](int) { return 0.0; });
 }
 
+// One individual's chunk through the generations of a block.
 template <typename T, int PREC, bool FULL>
-__device__ __forceinline__ void mutate_block_task(const RunDev& R, const Params& p, const VaryLaunch& lc, int gens,
-                                                  int chunk, int grp, int lane, int wave) {
+__device__ __forceinline__ void mutate_block_one(const RunDev& R, const Params& p, int gens, int chunk, int i,
+                                                 int lane) {
   typedef typename VecOf<T>::type VT;
   constexpr int N = VecOf<T>::N;
   constexpr int kChunk = chunk_cases(sizeof(T));
@@ -1223,54 +1224,211 @@ __device__ __forceinline__ void mutate_block_task(const RunDev& R, const Params&
     ok[j] = FULL || e < len;
     t[j] = ok[j] ? gload<VT>(yv + e) : VT(0);
   }
+      VT x[NJ];
+  #pragma unroll
+      for (int j = 0; j < NJ; ++j) x[j] = ok[j] ? gload<VT>(Sc + (int64_t)i * len + j * kWave * N + lane * N) : VT(0);
+      // a step's pool rows are read while the step before is worked on
+      auto read = [&](int s, T& ms, VT (&a)[NJ], VT (&b)[NJ]) {
+        const gsgp_record* rc = R.rec + (int64_t)(gen + s) * p.m + i;
+        const T* A = gc + (int64_t)uni(cload(&rc->r1)) * len;
+        const T* B = gc + (int64_t)uni(cload(&rc->r2)) * len;
+        ms = (T)cload(&rc->ms);
+  #pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int e = j * kWave * N + lane * N;
+          a[j] = ok[j] ? gload<VT>(A + e) : VT(0);
+          b[j] = ok[j] ? gload<VT>(B + e) : VT(0);
+        }
+      };
+      auto step = [&](int s, T ms, const VT (&a)[NJ], const VT (&b)[NJ]) {
+        LaneSse<T, PREC> acc;
+  #pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          VT v = x[j] + ms * (a[j] - b[j]);
+          if constexpr (PREC != GSGP_FP64) {
+  #pragma unroll
+            for (int c = 0; c < N; ++c) v[c] = __builtin_amdgcn_fmed3f(v[c], (T)-kFltMax, (T)kFltMax);
+          }
+          x[j] = v;
+          if (ok[j]) acc.add(v, t[j]);
+        }
+        const double sse = sse_finish<T, PREC, NJ>(acc, ok, x, yv, lane);
+        if (lane == 0) R.part[((int64_t)s * R.nch + chunk) * p.m + i] = sse;
+      };
+      T ms0, ms1;
+      VT a0[NJ], b0[NJ], a1[NJ], b1[NJ];
+      read(0, ms0, a0, b0);
+      for (int s = 0;;) {
+        if (s + 1 < gens) read(s + 1, ms1, a1, b1);
+        step(s, ms0, a0, b0);
+        if (++s >= gens) break;
+        if (s + 1 < gens) read(s + 1, ms0, a0, b0);
+        step(s, ms1, a1, b1);
+        if (++s >= gens) break;
+      }
+  #pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        if (ok[j]) gstore_nt<VT>(x[j], Oc + (int64_t)i * len + j * kWave * N + lane * N);
+}
+
+template <typename T, int PREC, bool FULL>
+__device__ __forceinline__ void mutate_block_task(const RunDev& R, const Params& p, const VaryLaunch& lc, int gens,
+                                                  int chunk, int grp, int lane, int wave) {
   int i_end = (grp + 1) * lc.opb;
   i_end = i_end < p.m ? i_end : p.m;
-  for (int i = grp * lc.opb + wave; i < i_end; i += lc.waves) {
-    VT x[NJ];
+  for (int i = grp * lc.opb + wave; i < i_end; i += lc.waves) mutate_block_one<T, PREC, FULL>(R, p, gens, chunk, i, lane);
+}
+
+// k_mutate_block for pools whose chunk column is larger than an XCD's L2, FP32:
+// a wave takes a slice of eight lanes' cases (two pieces of 128 bytes a row) of
+// eight individuals through the generations, then the next slice, so that the
+// blocks of an XCD, which start together and do the same work, read an eighth
+// of the pool column at a time.  A lane's cases and their order are those of
+// k_mutate_block's lane 8 slice + lane % 8, so the slices are taken in
+// bit-reversed order and their sums added like the butterfly's first three
+// distances: 0 + 4, 2 + 6, ....  The draws of a block's individuals are in LDS,
+// which all slices read.  An individual with a sum that is not finite is done
+// again by mutate_block_one, which falls back to FP64.
+//
+// What bounds it is the L2 (73 % hits against 23 %) and the start of a slice,
+// whose rows come from HBM.  Blocks of 16 waves in step are the best: 15
+// generations of 10,240 on 25,600 cases 1,777 us, of 8 waves 2,020, of 4 2,700;
+// reading a step's rows one step ahead costs a quarter of the waves: 2,199.
+constexpr int kSlices = 8;
+constexpr int kSliceWaves = 16;                     // waves a block
+constexpr int kSliceGroup = kSliceWaves * kSlices;  // individuals a block
+
+struct SliceDraw {
+  uint32_t r1, r2;  // byte offsets of the pool rows in a chunk's column
+  float ms;
+};
+
+__global__ __launch_bounds__(kSliceWaves * kWave) void k_mutate_slices(const RunDev* __restrict__ runs, Params p,
+                                                                       VaryLaunch lc, int64_t total_tasks,
+                                                                       int32_t groups, int32_t gens) {
+  typedef float T;
+  typedef f4 VT;
+  constexpr int N = 4, NJ = 2, kLanes = kWave / kSlices;
+  constexpr int kChunk = chunk_cases(sizeof(T));
+  static_assert(kChunk == NJ * kWave * N, "a lane has two vectors of a chunk");
+  __shared__ SliceDraw draws[kBlockGens][kSliceGroup];
+  const int lane = threadIdx.x & 63;
+  const int wave = uni(threadIdx.x >> 6);
+  const int64_t task = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (task >= total_tasks) return;
+  const int64_t at = task / groups;  // chunk over all runs
+  const int run = find_run(p.n_runs, at, [&](int r) { return runs[r].vary_task0 / lc.ogroups; });
+  const RunDev& R = runs[run];
+  const int chunk = (int)(at - R.vary_task0 / lc.ogroups);
+  const int i0 = (int)(task - at * groups) * kSliceGroup;
+  const ChunkGeom g = chunk_geom(R.tr_pad, R.te_pad, R.nch_tr, chunk, kChunk);
+  if (g.len != kChunk) {
+    for (int q = wave; q < kSliceGroup && i0 + q < p.m; q += kSliceWaves)
+      mutate_block_one<T, GSGP_FP32, false>(R, p, gens, chunk, i0 + q, lane);
+    return;
+  }
+  const int gen = uni(cload(&R.state[kStGen]));
+  const int cur = gen & 1;
+  for (int q = threadIdx.x; q < gens * kSliceGroup; q += kSliceWaves * kWave) {
+    const int s = q / kSliceGroup, k = q % kSliceGroup;
+    const int i = i0 + k < p.m ? i0 + k : p.m - 1;
+    const gsgp_record* rc = R.rec + (int64_t)(gen + s) * p.m + i;
+    draws[s][k] = SliceDraw{(uint32_t)rc->r1 * kChunkBytes, (uint32_t)rc->r2 * kChunkBytes, (T)rc->ms};
+  }
+  __syncthreads();
+  const int own = wave * kSlices + lane / kLanes;  // the lane's individual in the block
+  const int i = i0 + own;
+  const bool live = i < p.m;
+  const int64_t row = (int64_t)(live ? i : p.m - 1) * kChunk;
+  const T* Sc = (const T*)R.S[cur] + (int64_t)p.m * g.cs + row;
+  T* Oc = (T*)R.S[cur ^ 1] + (int64_t)p.m * g.cs + row;  // gens is odd
+  const GSGP_GLOBAL char* gc = (const GSGP_GLOBAL char*)((const T*)R.sigR + (int64_t)p.r * g.cs);
+  const T* yv = (const T*)R.y + g.cs;
+  T sum[kBlockGens], pair[kBlockGens], quad[kBlockGens], half[kBlockGens];
+#pragma unroll 1
+  for (int v = 0; v < kSlices; ++v) {
+    const int slice = (v & 1) << 2 | (v & 2) | v >> 2;
+    const int e0 = (slice * kLanes + lane % kLanes) * N;
+    VT x[NJ], t[NJ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) x[j] = ok[j] ? gload<VT>(Sc + (int64_t)i * len + j * kWave * N + lane * N) : VT(0);
-    // a step's pool rows are read while the step before is worked on
-    auto read = [&](int s, T& ms, VT (&a)[NJ], VT (&b)[NJ]) {
-      const gsgp_record* rc = R.rec + (int64_t)(gen + s) * p.m + i;
-      const T* A = gc + (int64_t)uni(cload(&rc->r1)) * len;
-      const T* B = gc + (int64_t)uni(cload(&rc->r2)) * len;
-      ms = (T)cload(&rc->ms);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int e = j * kWave * N + lane * N;
-        a[j] = ok[j] ? gload<VT>(A + e) : VT(0);
-        b[j] = ok[j] ? gload<VT>(B + e) : VT(0);
-      }
-    };
-    auto step = [&](int s, T ms, const VT (&a)[NJ], const VT (&b)[NJ]) {
-      LaneSse<T, PREC> acc;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        VT v = x[j] + ms * (a[j] - b[j]);
-        if constexpr (PREC != GSGP_FP64) {
-#pragma unroll
-          for (int c = 0; c < N; ++c) v[c] = __builtin_amdgcn_fmed3f(v[c], (T)-kFltMax, (T)kFltMax);
-        }
-        x[j] = v;
-        if (ok[j]) acc.add(v, t[j]);
-      }
-      const double sse = sse_finish<T, PREC, NJ>(acc, ok, x, yv, lane);
-      if (lane == 0) R.part[((int64_t)s * R.nch + chunk) * p.m + i] = sse;
-    };
-    T ms0, ms1;
-    VT a0[NJ], b0[NJ], a1[NJ], b1[NJ];
-    read(0, ms0, a0, b0);
-    for (int s = 0;;) {
-      if (s + 1 < gens) read(s + 1, ms1, a1, b1);
-      step(s, ms0, a0, b0);
-      if (++s >= gens) break;
-      if (s + 1 < gens) read(s + 1, ms0, a0, b0);
-      step(s, ms1, a1, b1);
-      if (++s >= gens) break;
+    for (int j = 0; j < NJ; ++j) {
+      x[j] = gload_nt<VT>(Sc + e0 + j * kWave * N);
+      t[j] = gload<VT>(yv + e0 + j * kWave * N);
     }
+    struct Rows {
+      VT a[NJ], b[NJ];
+      T ms;
+    };
+    auto read = [&](int s) {
+      const SliceDraw d = draws[s][own];
+      Rows q;
+      q.ms = d.ms;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
-      if (ok[j]) gstore_nt<VT>(x[j], Oc + (int64_t)i * len + j * kWave * N + lane * N);
+      for (int j = 0; j < NJ; ++j) {
+        const uint32_t e = (uint32_t)(e0 + j * kWave * N) * sizeof(T);
+        q.a[j] = *(const GSGP_GLOBAL VT*)(gc + (d.r1 + e));
+        q.b[j] = *(const GSGP_GLOBAL VT*)(gc + (d.r2 + e));
+      }
+      return q;
+    };
+    // The steps past `gens` are branches, not a loop of its own for each
+    // number: in one region of code the compiler moves the reads of several
+    // steps together, and spills.
+#pragma unroll
+    for (int s = 0; s < kBlockGens; ++s) {
+      if (s >= gens) continue;
+      const Rows now = read(s);
+      LaneSse<T, GSGP_FP32> acc;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        VT u = x[j] + now.ms * (now.a[j] - now.b[j]);
+#pragma unroll
+        for (int c = 0; c < N; ++c) u[c] = __builtin_amdgcn_fmed3f(u[c], -kFltMax, (T)kFltMax);
+        x[j] = u;
+        acc.add(u, t[j]);
+      }
+      sum[s] = acc.s;
+    }
+    if (live) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) gstore_nt<VT>(x[j], Oc + e0 + j * kWave * N);
+    }
+    // the butterfly's distances 32, 16, 8
+#pragma unroll
+    for (int s = 0; s < kBlockGens; ++s) {
+      if (!(v & 1)) {
+        pair[s] = sum[s];
+      } else {
+        sum[s] = pair[s] + sum[s];
+        if (!(v & 2)) {
+          quad[s] = sum[s];
+        } else {
+          sum[s] = quad[s] + sum[s];
+          if (!(v & 4))
+            half[s] = sum[s];
+          else
+            sum[s] = half[s] + sum[s];
+        }
+      }
+    }
+    __syncthreads();  // the waves of a block stay at one slice
+  }
+  bool finite = true;
+#pragma unroll
+  for (int s = 0; s < kBlockGens; ++s) {
+    if (s >= gens) continue;
+    T w = sum[s];
+    w += __shfl_xor(w, 4, kWave);
+    w += __shfl_xor(w, 2, kWave);
+    w += __shfl_xor(w, 1, kWave);
+    finite = finite && isfinite(w);
+    if (live && lane % kLanes == 0) R.part[((int64_t)s * R.nch + chunk) * p.m + i] = (double)w;
+  }
+  uint64_t again = __builtin_amdgcn_ballot_w64(live && !finite && lane % kLanes == 0);
+  while (again) {
+    const int q = __builtin_ctzll(again);
+    again &= again - 1;
+    mutate_block_one<T, GSGP_FP32, true>(R, p, gens, chunk, i0 + wave * kSlices + q / kLanes, lane);
   }
 }
 
@@ -2044,20 +2202,27 @@ hipError_t launch_fitness(const RunDev* d_runs, const Params& p, bool init, hipS
   return hipGetLastError();
 }
 
-// Where a chunk's pool column is far larger than an XCD's L2, rows come from
-// the memory-side cache, and three blocks a CU (an LDS reservation keeps the
-// others out) ask for as much as it gives: pool columns of 20 MiB 12.7 -> 12.4
-// ms; of 12 MiB 3.22 -> 3.34, of 4 MiB 0.64 -> 0.97.
-constexpr size_t kFarPoolBytes = 16 << 20;
-constexpr size_t kFewBlocksLds = 53 << 10;
+// Slices from pool columns larger than an XCD's L2 on: 15 generations of 6 MiB
+// 1,078 -> 937 us (3,072 individuals on 51,200 cases), of 20 MiB 3,152 -> 1,777
+// us (10,240 on 25,600); of 4 MiB 649 and 641, of 2 MiB 306 and 329.  FP64 and
+// compensated sums would hold twice the registers a step.
+constexpr size_t kSlicePoolBytes = 4 << 20;
+constexpr int32_t kSliceMaxPool = 1 << 20;  // byte offsets of pool rows are 32 bits
 
 template <typename T, int PREC>
 hipError_t launch_block_as(const RunDev* d_runs, const Params& p, const VaryLaunch& lc, int32_t gens,
                            int32_t row_blocks, hipStream_t s) {
   const int64_t draws = (int64_t)p.n_runs * gens * p.m;
   hipLaunchKernelGGL(k_block_draws, dim3(blocks_for(draws, 256)), dim3(256), 0, s, d_runs, p, gens, draws);
-  hipLaunchKernelGGL((k_mutate_block<T, PREC>), dim3((unsigned)lc.grid), dim3(lc.waves * kWave),
-                     (size_t)p.r * kChunkBytes > kFarPoolBytes ? kFewBlocksLds : 0, s, d_runs, p, lc, gens);
+  if (PREC == GSGP_FP32 && (size_t)p.r * kChunkBytes > kSlicePoolBytes && p.r <= kSliceMaxPool) {
+    const int32_t groups = (p.m + kSliceGroup - 1) / kSliceGroup;
+    const int64_t tasks = lc.total_tasks / lc.ogroups * groups;
+    const dim3 grid((unsigned)((tasks + 7) / 8 * 8)), block(kSliceWaves * kWave);
+    hipLaunchKernelGGL(k_mutate_slices, grid, block, 0, s, d_runs, p, lc, tasks, groups, gens);
+  } else {
+    hipLaunchKernelGGL((k_mutate_block<T, PREC>), dim3((unsigned)lc.grid), dim3(lc.waves * kWave), 0, s, d_runs, p, lc,
+                       gens);
+  }
   const int32_t per_run = (p.m + kFitGroup - 1) / kFitGroup;
   hipLaunchKernelGGL(k_block_fitness, dim3((unsigned)(per_run * p.n_runs), (unsigned)gens), dim3(kFitRanges * kFitGroup),
                      0, s, d_runs, p, per_run, gens);

@@ -58,6 +58,30 @@ def test_blocks_equal_single_generations(m, r, n_train, n_test, step, precision)
         R.close()
 
 
+# FP32 pools of more than 2,048 rows go slice by slice: blocks of 128
+# individuals, whole chunks of 512 cases; products of features of 1e12 overflow
+# the FP32 sums of squares.
+@pytest.mark.parametrize("m,r,n_train,n_test,step,scale", [
+    (1, 2049, 512, 0, 0.1, 1.0), (130, 2100, 1100, 600, 0.5, 1.0), (128, 3000, 1024, 512, 5.0, 1.0),
+    (257, 2500, 513, 64, 0.5, 1e12)])
+def test_sliced_blocks_equal_single_generations(m, r, n_train, n_test, step, scale):
+    gens = 15 + 7 + 5 + 4 + 2
+    d = dataset(n_train, n_test, 3, seed=m)
+    d.X_train *= scale
+    d.X_test *= scale
+    s = _settings(m, r, gens, "fp32", step)
+    A, B = gsgp.Runner(s, [d]), gsgp.Runner(s, [d])
+    A.eval_population()
+    B.eval_population()
+    for n in (15, 7, 5, 4, 2):
+        A.generation(n, stats=False)
+    for g in range(gens):
+        B.generation(1, stats=False)
+    _same(A, B, 1, gens)
+    for R in (A, B):
+        R.close()
+
+
 def test_blocks_of_several_runs_plain_and_guarded():
     data = [dataset(500 + 300 * i, 90 * i, 2 + i, seed=i) for i in range(4)]
     gens = 24
