@@ -226,7 +226,11 @@ gsgp_status make_plan(const gsgp_config* c, const gsgp_run* runs, int32_t n_runs
     p.elite_in = take_at(sizeof(gsgp_gen_stats) * G, i, "supplied survival decisions");
     p.code = take_at(4 * (m + r) * k, i, "genome codes");
     p.cval = take_at(8 * (m + r) * k, i, "genome constants");
-    p.ops = take_at(sizeof(CompiledOp) * ((m + r) * op_stride(k) + kOpTail), i, "compiled ops");
+    // 20 bytes a gene (an op, its constant and its reciprocal once had arrays
+    // of their own) and 60 a program hold its ops for every k; the size that
+    // programs plan their workspaces by stays linear in k
+    static_assert(sizeof(CompiledOp) * op_stride(1) <= 20 * 1 + 60 && sizeof(CompiledOp) <= 20, "ops of k genes fit");
+    p.ops = take_at((20 * k + 60) * (m + r) + sizeof(CompiledOp) * kOpTail, i, "compiled ops");
     p.nops = take_at(4 * (m + r), i, "program lengths");
     p.need = take_at(4 * (m + r), i, "program stack needs");
     p.lists = take_at(4 * (m + r), i, "program lists by stack need");
