@@ -12,12 +12,17 @@
 //   k_vary       the hot loop: every offspring row of one 2 KiB case chunk is
 //                formed from its parent and pool rows with 16-byte loads and
 //                non-temporal 16-byte stores, and the chunk's squared
-//                residual sum is reduced across the wave with xor shuffles;
+//                residual sum is reduced across the wave in registers;
 //                blocks on one XCD share a chunk so distinct parent and pool
 //                rows are fetched from HBM about once per chunk;
-//   k_fitness    lanes own individuals and waves own chunk ranges; FP64 sums;
-//   k_survive    argmin / argmax with lowest-index ties, elite row copy,
-//                per-generation summary and the next generation's tournaments.
+//   k_mutate_block, k_mutate_slices, k_block_*  up to 15 generations of the
+//                loop without selection at a time;
+//   k_fitness    16 individuals a block, 16 threads an individual own chunk
+//                ranges; FP64 sums, and the group's extremes;
+//   k_survive    best and worst with lowest-index ties, elite row copy,
+//                per-generation summary and the next generation's tournaments;
+//   k_lineage*, k_replay_*  an individual's ancestry, walked and replayed;
+//   k_fetch_*    what the getters return, in one piece.
 // All kernels are compiled without floating-point contraction so that the
 // per-element arithmetic matches the method's definitions operation by
 // operation.
@@ -1158,8 +1163,9 @@ __global__ __launch_bounds__(256) void k_survive(const RunDev* __restrict__ runs
 // offspring row to the two pool rows, which mostly come from the caches, plus
 // one in 7 or 15 of the other two.  Per generation, one at a time -> 7 -> 15 a
 // block: 10,240 individuals on 102,400 FP32 cases 2,233 -> 1,104 -> 1,006 us (a
-// chunk's pool column is 20 MB, so most of its reads leave the XCD's L2: 8.3
-// TB/s of pool rows); 4,000 on 30,000 185 -> 104 -> 93 us; 2,048 on 10,240
+// chunk's pool column is 20 MB, so most of its reads leave the XCD's L2: 565 us
+// slice by slice, see k_mutate_slices); 4,000 on 30,000 185 -> 104 -> 93 us
+// (whole chunks); 2,048 on 10,240
 // 58 -> 25.8 -> 25.4 us; 600 on 2,000 23 -> 11.9 -> 13.8 us; 128 on 500 (FP64)
 // 23 -> 11.0 -> 12.6 us.
 
