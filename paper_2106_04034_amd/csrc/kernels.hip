@@ -1165,7 +1165,7 @@ __global__ __launch_bounds__(256) void k_survive(const RunDev* __restrict__ runs
 // block: 10,240 individuals on 102,400 FP32 cases 2,233 -> 1,104 -> 1,006 us (a
 // chunk's pool column is 20 MB, so most of its reads leave the XCD's L2: 565 us
 // slice by slice, see k_mutate_slices); 4,000 on 30,000 185 -> 104 -> 93 us
-// (whole chunks); 2,048 on 10,240
+// (whole chunks); 2,048 on 10,240 (22 us now, with sums in registers)
 // 58 -> 25.8 -> 25.4 us; 600 on 2,000 23 -> 11.9 -> 13.8 us; 128 on 500 (FP64)
 // 23 -> 11.0 -> 12.6 us.
 
@@ -1584,7 +1584,11 @@ __global__ __launch_bounds__(1024) void k_block_elite(const RunDev* __restrict__
 
 // The rest of the block for the row that the step's copy overwrote: one wave
 // a chunk forms its values along its line, the squared error sums of the
-// steps after the copy, and its values at the end of the block.
+// steps after the copy, and its values at the end of the block.  Bound by
+// latency: lane s reads the draws of the line's step s, so that they are one
+// round trip for all steps, and a step's pool rows are read while the step
+// before is worked on.  After blocks of 15 of 2,048 individuals on 10,240 cases
+// 9.0 -> 6.3 us, of 10,240 on 102,400 10.9 -> 7.5 us.
 template <typename T, int PREC, bool FULL>
 __device__ __forceinline__ void block_row_chunk(const RunDev& R, const Params& p, int gens, int step, int chunk, int at,
                                                 int lane) {
@@ -1609,19 +1613,36 @@ __device__ __forceinline__ void block_row_chunk(const RunDev& R, const Params& p
     x[j] = ok[j] ? gload<VT>(Sc + e) : VT(0);
     t[j] = ok[j] ? gload<VT>(yv + e) : VT(0);
   }
-  for (int s = 1; s <= gens; ++s) {
-    const int by = uni(B.by[at][s]);
-    if (by < 0) continue;
-    const gsgp_record* rc = R.rec + (int64_t)(base + s - 1) * p.m + by;
-    const T* A = gc + (int64_t)uni(cload(&rc->r1)) * len;
-    const T* C = gc + (int64_t)uni(cload(&rc->r2)) * len;
-    const T ms = (T)cload(&rc->ms);
-    LaneSse<T, PREC> acc;
+  const int own = lane >= 1 && lane <= gens ? lane : 1;
+  const int by = ((const GSGP_GLOBAL int32_t*)B.by[at])[own];
+  const GSGP_GLOBAL gsgp_record* rc =
+      (const GSGP_GLOBAL gsgp_record*)R.rec + (int64_t)(base + own - 1) * p.m + (by < 0 ? 0 : by);
+  const int r1 = rc->r1, r2 = rc->r2;
+  const double ms = rc->ms;
+  // the steps of the line (a copy's step applies nothing)
+  uint64_t left = __builtin_amdgcn_ballot_w64(lane >= 1 && lane <= gens && by >= 0);
+  struct Rows {
+    VT a[NJ], c[NJ];
+    int s;
+  };
+  auto read = [&](Rows& q) {
+    q.s = __builtin_ctzll(left);
+    left &= left - 1;
+    const T* A = gc + (int64_t)__builtin_amdgcn_readlane(r1, q.s) * len;
+    const T* C = gc + (int64_t)__builtin_amdgcn_readlane(r2, q.s) * len;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       const int e = j * kWave * N + lane * N;
-      const VT a = ok[j] ? gload<VT>(A + e) : VT(0), c = ok[j] ? gload<VT>(C + e) : VT(0);
-      VT v = x[j] + ms * (a - c);
+      q.a[j] = ok[j] ? gload<VT>(A + e) : VT(0);
+      q.c[j] = ok[j] ? gload<VT>(C + e) : VT(0);
+    }
+  };
+  auto apply = [&](const Rows& q) {
+    const T w = (T)lane_value(ms, q.s);
+    LaneSse<T, PREC> acc;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      VT v = x[j] + w * (q.a[j] - q.c[j]);
       if constexpr (PREC != GSGP_FP64) {
 #pragma unroll
         for (int k = 0; k < N; ++k) v[k] = __builtin_amdgcn_fmed3f(v[k], (T)-kFltMax, (T)kFltMax);
@@ -1629,9 +1650,23 @@ __device__ __forceinline__ void block_row_chunk(const RunDev& R, const Params& p
       x[j] = v;
       if (ok[j]) acc.add(v, t[j]);
     }
-    if (s > step) {
+    if (q.s > step) {
       const double sse = sse_finish<T, PREC, NJ>(acc, ok, x, yv, lane);
-      if (lane == 0) R.part[((int64_t)(s - 1) * R.nch + chunk) * p.m + dst] = sse;
+      if (lane == 0) R.part[((int64_t)(q.s - 1) * R.nch + chunk) * p.m + dst] = sse;
+    }
+  };
+  Rows q0, q1;
+  if (left) {
+    read(q0);
+    for (;;) {
+      const bool more = left != 0;
+      if (more) read(q1);
+      apply(q0);
+      if (!more) break;
+      const bool still = left != 0;
+      if (still) read(q0);
+      apply(q1);
+      if (!still) break;
     }
   }
 #pragma unroll
