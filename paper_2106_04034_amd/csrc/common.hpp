@@ -139,7 +139,7 @@ struct RunDev {
   void* S[2];               // population semantics ping-pong, [m][ld], storage type
   void* sigR;               // squashed pool semantics, [r][ld]
   void* y;                  // target, [ld], storage type, zero pads
-  double* X;                // features in case tiles, [ceil(ld / kXTile)][l][kXTile], zero pads
+  double* X;                // features in case tiles, [ceil(ld / kXTile)][l][kXTile], pads repeat a case (see k_prep)
   double* part;             // chunk partial sums of squared residuals, [nch][m]; with local
                             // search the generation's sums of o, o^2 and o * t, [nch][3][m];
                             // for blocks of generations [generations a block][nch][m]
@@ -172,7 +172,7 @@ struct RunDev {
   int64_t vary_task0;       // first task of this run in the variation launch
   int64_t cblk0;            // first 128-case block of this run (interpreter)
   int64_t cblk0w;           // first 256-case block of this run (wide interpreter)
-  int64_t col0;             // first padded column of this run (data prep)
+  int64_t col0;             // first column of this run's X tiles over all runs (data prep)
 };
 
 // Run-independent parameters, passed by value to every kernel.

@@ -665,7 +665,7 @@ gsgp_status gsgp_init(const gsgp_config* cfg, const gsgp_run* runs, int32_t n_ru
     R.nch = q.nch_tr + q.nch_te;
     R.run_id = (uint32_t)i;
     R.col0 = col;
-    col += q.ld;
+    col += pad_to(q.ld, kXTile);
     R.cblk0 = itask;
     itask += (q.ld + kInterpCases - 1) / kInterpCases;
     R.cblk0w = itask_w;
@@ -704,12 +704,6 @@ gsgp_status gsgp_init(const gsgp_config* cfg, const gsgp_run* runs, int32_t n_ru
     e = hipMemcpyAsync((void*)d_src, src.data(), sizeof(double*) * src.size(), hipMemcpyHostToDevice, h->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(state, zeros.data(), sizeof(int32_t) * zeros.size(), hipMemcpyHostToDevice, h->stream);
-  // X's last tile of each run is whole: its columns past the padded cases
-  // are read by interpreter lanes whose values are never stored; zeros
-  for (int32_t i = 0; i < n_runs && e == hipSuccess; ++i) {
-    const RunPlan& q = plan.runs[i];
-    e = hipMemsetAsync(ws + q.X, 0, sizeof(double) * q.l * ((q.ld + kXTile - 1) / kXTile) * kXTile, h->stream);
-  }
   if (e == hipSuccess) e = launch_prep(h->runs_d, p, col, d_src, nullptr, h->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(h->pinned, state, sizeof(int32_t) * kStWords * n_runs, hipMemcpyDeviceToHost, h->stream);
