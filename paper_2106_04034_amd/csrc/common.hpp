@@ -97,6 +97,12 @@ enum OpFn : int32_t { kFnAdd = 0, kFnSub = 1, kFnMul = 2, kFnDiv = 3 };
 enum OpPush : int32_t { kPushFeature = 0, kPushConst = 1 };
 constexpr int kOpDepthMax = 0xFFF;
 
+// After the state words of all runs: programs that each launch of the wide
+// interpreter has given up so far, a cache line of words for every XCD.
+constexpr int kWideLaunches = 2;
+constexpr int kGivenUpStride = 32;
+constexpr int kGivenUpWords = 8 * kGivenUpStride;  // a launch
+
 // Per-run device state words.
 enum StateWord : int {
   kStGen = 0,           // last completed generation
@@ -242,17 +248,18 @@ hipError_t launch_prep(const RunDev* d_runs, const Params& p, int64_t total_cols
                        const double* const* Xsrc, const double* const* ysrc, hipStream_t s);
 hipError_t launch_set_state(const RunDev* d_runs, int32_t n_runs, int32_t word, int32_t value,
                             hipStream_t s);
-hipError_t launch_reset_state(const RunDev* d_runs, int32_t n_runs, hipStream_t s);
+hipError_t launch_reset_state(const RunDev* d_runs, int32_t n_runs, int32_t* given_up, hipStream_t s);
 hipError_t launch_genome(const RunDev* d_runs, const Params& p, hipStream_t s);
 hipError_t launch_compile(const RunDev* d_runs, const Params& p, hipStream_t s);
 // Interpreter passes.  launch_interpret_wide: the programs of the stack-need
 // lists first .. last (< kLists - 1; at most `progs` per run together), four
 // cases per lane, case_blocks blocks of kXTile cases over all runs; a wave takes
-// per_wave (<= 32) programs one after the other on its block.
+// per_wave (<= 32) programs one after the other on its block.  given_up:
+// kGivenUpWords of the launch's own, zero before it.
 // launch_interpret: the last list's programs with a need of at most `slots`
 // (<= kMaxLdsSlots), two cases per lane, blocks of kInterpCases cases.
 hipError_t launch_interpret_wide(const RunDev* d_runs, const Params& p, int64_t case_blocks, int first, int last,
-                                 int64_t progs, int32_t per_wave, hipStream_t s);
+                                 int64_t progs, int32_t per_wave, int32_t* given_up, hipStream_t s);
 hipError_t launch_interpret(const RunDev* d_runs, const Params& p, int64_t case_blocks, int slots, int32_t progs,
                             hipStream_t s);
 // Last pass: every program of the last list whose need exceeds kMaxLdsSlots,

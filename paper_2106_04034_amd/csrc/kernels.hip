@@ -2110,8 +2110,9 @@ __global__ void k_set_state(const RunDev* __restrict__ runs, int32_t n_runs, int
 
 // The state words that a restart begins from, in one launch (one launch a
 // word cost an initialisation ten).
-__global__ void k_reset_state(const RunDev* __restrict__ runs, int32_t n_runs) {
+__global__ void k_reset_state(const RunDev* __restrict__ runs, int32_t n_runs, int32_t* __restrict__ given_up) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r < kWideLaunches * 8) given_up[r * kGivenUpStride] = 0;
   if (r >= n_runs) return;
   int32_t* st = runs[r].state;
   st[kStGen] = 0;
@@ -2158,8 +2159,8 @@ hipError_t launch_set_state(const RunDev* d_runs, int32_t n_runs, int32_t word, 
   return hipGetLastError();
 }
 
-hipError_t launch_reset_state(const RunDev* d_runs, int32_t n_runs, hipStream_t s) {
-  hipLaunchKernelGGL(k_reset_state, dim3(blocks_for(n_runs, 256)), dim3(256), 0, s, d_runs, n_runs);
+hipError_t launch_reset_state(const RunDev* d_runs, int32_t n_runs, int32_t* given_up, hipStream_t s) {
+  hipLaunchKernelGGL(k_reset_state, dim3(blocks_for(n_runs, 256)), dim3(256), 0, s, d_runs, n_runs, given_up);
   return hipGetLastError();
 }
 

@@ -101,7 +101,7 @@ struct Guard {
 };
 
 struct Plan {
-  size_t runs_dev, src_ptrs, state, spill, spill_bytes, total;
+  size_t runs_dev, src_ptrs, state, given_up, spill, spill_bytes, total;
   int32_t block_gens;  // generations a block, 0: one at a time
   std::vector<RunPlan> runs;
   std::vector<Guard> guards;
@@ -176,7 +176,9 @@ gsgp_status make_plan(const gsgp_config* c, const gsgp_run* runs, int32_t n_runs
   };
   plan->runs_dev = take_at(sizeof(RunDev) * n_runs, -1, "run descriptors");
   plan->src_ptrs = take_at(sizeof(double*) * 4 * n_runs, -1, "input pointers");
-  plan->state = take_at(sizeof(int32_t) * kStWords * n_runs, -1, "state words");
+  plan->given_up = align_up(sizeof(int32_t) * kStWords * n_runs);
+  plan->state = take_at(plan->given_up + sizeof(int32_t) * kWideLaunches * kGivenUpWords, -1, "state words");
+  plan->given_up += plan->state;
   // stack columns of the interpreter's spill pass, sized for the deepest
   // stack a genome of k genes can need; none when every stack fits in LDS
   const int64_t need_cap = max_need(k);
@@ -746,16 +748,19 @@ gsgp_status gsgp_destroy(gsgp_handle* h) {
 
 namespace {
 
-// From this many (program, case block) tasks on, the programs that need no LDS
-// column run by themselves (more resident waves), two to a wave; below it all
-// lists but the last share one launch (its LDS column is the largest one's,
-// but every launch of a list alone ends on a few long programs).  In one, in
-// two launches, ms with one program a wave / two: 1,536 tasks (500 FP64 cases)
-// 0.054 / 0.069, 0.070 / 0.101; 51,000 (5,000 cases) 0.201 / 0.201, 0.197 /
-// 0.218; 164,000 of 1,023 genes 2.06 / 2.03, 2.06 / 2.18; 1.0 million (125,000
-// cases) 1.74 / 1.65, 1.61 / 1.62; 10 million 15.6 / 14.9, 14.9 / 14.6; 8 million on
-// 1,024 features 13.2 / 12.6, 12.8 / 12.4.
-constexpr int64_t kSplitTasks = (int64_t)1 << 19;
+// From kSplitTasks (program, case block) tasks on, the programs with the deepest
+// LDS column run by themselves, so that the others' waves are not held to 20 a
+// CU by it; below it all lists but the last share one launch, as every launch
+// ends on a few long programs.  From kPairTasks on a wave takes two programs,
+// which pays its set-up once and loosens the end of a launch.  Whole
+// initialisations, us, in one launch / in two with one program a wave / two:
+// 100,000 tasks of 1,023 genes 1,275 / 1,340 / 1,428, of 127 genes 248 / 248 /
+// 248; 395,000 in 64 runs 938 / 879 / 858 (127 genes), 2,647 / 2,636 / 2,782 (511);
+// 500,000 of 255 genes 1,607 / 1,647 / 1,614, on data that need the checked
+// evaluator 2,609 / 2,362 / 2,304; 1.0 million of 127 genes 1,764 and 1,770 (two
+// launches), on such data 2,632 and 2,497.
+constexpr int64_t kSplitTasks = (int64_t)1 << 18;
+constexpr int64_t kPairTasks = (int64_t)1 << 19;
 
 // ComputeSemantics of every compiled program, list by list of stack need: all
 // but the last with the wide kernel, then the last list with LDS columns up to
@@ -763,15 +768,20 @@ constexpr int64_t kSplitTasks = (int64_t)1 << 19;
 // counts[b]: the longest list b over the runs.
 hipError_t interpret_all(gsgp_handle* h, const int32_t (&counts)[kLists], hipStream_t s) {
   const Params& p = h->params;
+  constexpr int deep = kLists - 2;  // the deepest of the wide interpreter's lists
   int64_t rest = 0;
-  for (int b = 1; b < kLists - 1; ++b) rest += counts[b];
-  const int64_t blocks = h->interp_tasks_w;
+  for (int b = 0; b < deep; ++b) rest += counts[b];
+  const int64_t blocks = h->interp_tasks_w, tasks = blocks * (rest + counts[deep]);
+  int32_t* given_up = (int32_t*)(h->ws + h->plan.given_up);
   hipError_t e = hipSuccess;
-  if (blocks * (counts[0] + rest) < kSplitTasks) {
-    e = launch_interpret_wide(h->runs_d, p, blocks, 0, kLists - 2, counts[0] + rest, 1, s);
+  if (tasks < kSplitTasks) {
+    e = launch_interpret_wide(h->runs_d, p, blocks, 0, deep, rest + counts[deep], 1, given_up, s);
   } else {
-    e = launch_interpret_wide(h->runs_d, p, blocks, 0, 0, counts[0], 2, s);
-    if (e == hipSuccess) e = launch_interpret_wide(h->runs_d, p, blocks, 1, kLists - 2, rest, 2, s);
+    static_assert(kWideLaunches == 2, "counters for each of them");
+    const int per_wave = tasks < kPairTasks ? 1 : 2;
+    e = launch_interpret_wide(h->runs_d, p, blocks, 0, deep - 1, rest, per_wave, given_up, s);
+    if (e == hipSuccess)
+      e = launch_interpret_wide(h->runs_d, p, blocks, deep, deep, counts[deep], per_wave, given_up + kGivenUpWords, s);
   }
   if (e == hipSuccess && h->slots > kListSlots[kLists - 2])
     e = launch_interpret(h->runs_d, p, h->interp_tasks, std::min(h->slots, kMaxLdsSlots), counts[kLists - 1], s);
@@ -800,7 +810,7 @@ gsgp_status eval_impl(gsgp_handle* h, const int32_t* h_codes, const double* h_co
     }
   }
   if (ev) HIPCHK(h, hipEventRecord(ev[0], h->stream));
-  HIPCHK(h, launch_reset_state(h->runs_d, h->n_runs, h->stream));
+  HIPCHK(h, launch_reset_state(h->runs_d, h->n_runs, (int32_t*)(h->ws + h->plan.given_up), h->stream));
   if (h_codes) {
     for (int32_t r = 0; r < h->n_runs; ++r) {
       HIPCHK(h, hipMemcpyAsync(h->runs_h[r].code, h_codes + r * per, 4 * per, hipMemcpyHostToDevice, h->stream));
