@@ -1300,11 +1300,11 @@ __device__ __forceinline__ void mutate_block_task(const RunDev& R, const Params&
   for (int i = grp * lc.opb + wave; i < i_end; i += lc.waves) mutate_block_one<T, PREC, FULL>(R, p, gens, chunk, i, lane);
 }
 
-// k_mutate_block for pools whose chunk column is larger than an XCD's L2, FP32:
-// a wave takes a slice of eight lanes' cases (two pieces of 128 bytes a row) of
-// eight individuals through the generations, then the next slice, so that the
-// blocks of an XCD, which start together and do the same work, read an eighth
-// of the pool column at a time.  A lane's cases and their order are those of
+// k_mutate_block for pools whose chunk column is larger than an XCD's L2, FP32
+// (where: slices_pay): a wave takes a slice of eight lanes' cases (two pieces of
+// 128 bytes a row) of eight individuals through the generations, then the next
+// slice, so that the blocks of an XCD, which start together and do the same
+// work, read an eighth of the pool column at a time.  A lane's cases and their order are those of
 // k_mutate_block's lane 8 slice + lane % 8, so the slices are taken in
 // bit-reversed order and their sums added like the butterfly's first three
 // distances: 0 + 4, 2 + 6, ....  The draws of a block's individuals are in LDS,
@@ -2259,21 +2259,45 @@ hipError_t launch_fitness(const RunDev* d_runs, const Params& p, bool init, hipS
   return hipGetLastError();
 }
 
-// Slices from pool columns larger than an XCD's L2 on: 15 generations of 6 MiB
-// 1,078 -> 937 us (3,072 individuals on 51,200 cases), of 20 MiB 3,152 -> 1,777
-// us (10,240 on 25,600); of 4 MiB 649 and 641, of 2 MiB 306 and 329.  FP64 and
-// compensated sums would hold twice the registers a step.
-constexpr size_t kSlicePoolBytes = 4 << 20;
+// Where k_mutate_slices is faster than k_mutate_block: pool columns beyond an
+// XCD's L2 (those just beyond it only in many rounds of blocks), read by a
+// population large enough to come back to a slice, and blocks (one a CU) that
+// fill their last round of the CUs to three fifths at least.  A generation, us,
+// k_mutate_block / slices, at the lines:
+//   pool: 10,240 individuals on 25,600 cases, pools of 1,024 rows 20 / 22, of 2,048 43 / 43;
+//     10,000 on 40,000, pools of 2,200 189 / 165, of 4,000 271 / 171, of 20,000 444 / 296;
+//     5,000 on 5,000, pools of 2,560 26.9 / 31.2, of 4,000 31.7 / 31.6, of 7,000 37.0 / 32.1;
+//     pools of 2,200 in 790, 1,264, 1,576 and 1,738 blocks 38.5 / 41.4, 52.6 / 53.5, 66.8 / 71.2,
+//     65.9 / 59.6;
+//   population: 1,000 on 100,000 cases, pool of 4,000, 87.7 / 81.9; 500, pool of 10,000, 66.8 / 80.4;
+//     128 on 6,250, pool of 40,000, 13.4 / 24.5;
+//   blocks: 160 (2,000 on 5,000 cases, pool of 4,000) 20.8 / 22.5; 208 24.0 / 23.5; 264
+//     (1,400 on 12,000) 26.2 / 30.8; 384 (2,000) 30.6 / 27.5.
+// There is no form for FP64 and compensated sums, which would hold twice the
+// registers a step.
+constexpr size_t kSlicePoolBytes = (size_t)4 << 20;
+constexpr size_t kSlicePoolFar = (size_t)11 << 19;
+constexpr int64_t kSliceBlocksNear = 1600;  // pools between the two
 constexpr int32_t kSliceMaxPool = 1 << 20;  // byte offsets of pool rows are 32 bits
+constexpr int32_t kSlicePop = 1000;
+constexpr int64_t kSliceBlocks = 200;
+constexpr int64_t kCUs = 256;
+
+inline bool slices_pay(const Params& p, int64_t blocks) {
+  const size_t pool = (size_t)p.r * kChunkBytes;
+  const int64_t rounds = (blocks + kCUs - 1) / kCUs;
+  return pool > kSlicePoolBytes && p.r <= kSliceMaxPool && p.m >= kSlicePop &&
+         blocks >= (pool > kSlicePoolFar ? kSliceBlocks : kSliceBlocksNear) && 5 * blocks >= 3 * rounds * kCUs;
+}
 
 template <typename T, int PREC>
 hipError_t launch_block_as(const RunDev* d_runs, const Params& p, const VaryLaunch& lc, int32_t gens,
                            int32_t row_blocks, hipStream_t s) {
   const int64_t draws = (int64_t)p.n_runs * gens * p.m;
   hipLaunchKernelGGL(k_block_draws, dim3(blocks_for(draws, 256)), dim3(256), 0, s, d_runs, p, gens, draws);
-  if (PREC == GSGP_FP32 && (size_t)p.r * kChunkBytes > kSlicePoolBytes && p.r <= kSliceMaxPool) {
-    const int32_t groups = (p.m + kSliceGroup - 1) / kSliceGroup;
-    const int64_t tasks = lc.total_tasks / lc.ogroups * groups;
+  const int32_t groups = (p.m + kSliceGroup - 1) / kSliceGroup;
+  const int64_t tasks = lc.total_tasks / lc.ogroups * groups;
+  if (PREC == GSGP_FP32 && slices_pay(p, tasks)) {
     const dim3 grid((unsigned)((tasks + 7) / 8 * 8)), block(kSliceWaves * kWave);
     hipLaunchKernelGGL(k_mutate_slices, grid, block, 0, s, d_runs, p, lc, tasks, groups, gens);
   } else {
