@@ -25,6 +25,9 @@ constexpr int chunk_cases(int storage_bytes) { return kChunkBytes / storage_byte
 // multiple of this many cases; rows therefore start 256-byte aligned.
 constexpr int kSegPad = 64;
 constexpr int kWave = 64;
+// Threads of one launch in a dimension: HIP takes fewer than 2^32.  Launches that
+// could have more go in pieces of at most this many.
+constexpr int64_t kMaxThreads = (int64_t)1 << 31;
 // Interpreter work unit: a block of kInterpCases cases (kWave lanes x 2 cases).
 constexpr int kInterpCases = 128;
 // X is stored in tiles of kXTile cases, each tile feature-major: element

@@ -533,7 +533,8 @@ gsgp_status fetch_semantics(gsgp_handle* h, int32_t run, int32_t which, int64_t 
   const int64_t total = n_rows * n_cases;
   const bool mapped = sizeof(double) * (size_t)total <= h->pinned_bytes;
   double* to = mapped ? (double*)h->pinned : (double*)R.S[(h->gen & 1) ^ 1];
-  const int64_t most = mapped ? total : (int64_t)(storage_bytes(h->cfg.precision) * h->cfg.pop_size * R.ld / sizeof(double));
+  const int64_t room = (int64_t)(storage_bytes(h->cfg.precision) * h->cfg.pop_size * R.ld / sizeof(double));
+  const int64_t most = mapped ? total : std::min(room, kMaxThreads);  // a thread a value
   for (int64_t e = 0; e < total; e += most) {
     const int64_t count = std::min(most, total - e);
     HIPCHK(h, launch_fetch_semantics(h->cfg.precision, R, buf, rows, row0, case0, n_cases, e, count, ls, to, h->stream));

@@ -1,0 +1,62 @@
+"""The kernel launches of the host code, without a GPU: the library runs in a
+child process on a stand-in for the HIP runtime (hip_stub.c) that notes every
+launch and refuses those of 2^32 threads or more, as HIP does.  Handles of any
+size cost nothing there: device pointers are made up."""
+from __future__ import annotations
+
+import os
+import subprocess
+import sys
+
+import pytest
+
+from tests.conftest import ROOT
+
+HEAD = """
+import ctypes, sys
+sys.path.insert(0, {root!r})
+from paper_2106_04034_amd import gsgp
+L, P = gsgp.lib(), ctypes.c_void_p
+WS, DATA = 1 << 40, 1 << 44  # made-up device addresses
+def handle(shapes, **settings):
+    s = gsgp.Settings(**settings)
+    runs = gsgp.run_descs([(*x, (DATA, DATA, DATA if x[1] else None, DATA if x[1] else None)) for x in shapes])
+    cfg, h, size = s.c(), P(0), ctypes.c_size_t(0)
+    gsgp.check(L.gsgp_workspace_size(ctypes.byref(cfg), runs, len(shapes), ctypes.byref(size)), "size")
+    gsgp.check(L.gsgp_init(ctypes.byref(cfg), runs, len(shapes), P(WS), size.value, None, ctypes.byref(h)), "init")
+    gsgp.check(L.gsgp_eval_population(h, None, None), "eval")
+    return h
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "libhip_stub.so")
+    subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "hip_stub.c")])
+    return so
+
+
+@pytest.fixture
+def launches(stub, tmp_path):
+    """run(code, lineage) -> [(kernel, grid x, block x, device)] of the child."""
+    def run(code, lineage=""):
+        log = tmp_path / "log"
+        env = dict(os.environ, LD_PRELOAD=stub, HIP_STUB_LOG=str(log))
+        if lineage:
+            env["HIP_STUB_LINEAGE"] = lineage
+        out = subprocess.run([sys.executable, "-c", HEAD.format(root=ROOT) + code], env=env, cwd=ROOT,
+                             capture_output=True, text=True, timeout=120)
+        assert out.returncode == 0, out.stderr[-2000:]
+        rows = [l.split() for l in log.read_text().splitlines()]
+        return [(r[0], int(r[1]), int(r[4]), int(r[5])) for r in rows]
+    return run
+
+
+def test_semantics_of_more_than_2_to_32_values(launches):
+    """8,192 individuals on 1,000,000 FP64 cases: every value has its thread."""
+    got = launches("""
+h = handle([(1_000_000, 0, 1)], pop_size=8192, pool_size=16, genome_len=15)
+gsgp.check(L.gsgp_get_semantics(h, 0, 0, P(DATA)), "semantics")
+""")
+    threads = [g * b for k, g, b, _ in got if "k_fetch_semantics" in k]
+    assert sum(threads) >= 8192 * 1_000_000 and max(threads) < 2**32
