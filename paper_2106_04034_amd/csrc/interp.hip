@@ -1292,10 +1292,14 @@ inline int interp_waves(int slots) {
 
 hipError_t launch_compile(const RunDev* d_runs, const Params& p, hipStream_t s) {
   const int32_t groups = (p.m + p.r + kCompileWaves - 1) / kCompileWaves;  // blocks per run
-  hipLaunchKernelGGL(k_compile, dim3((unsigned)p.n_runs * groups), dim3(kCompileWaves * kWave),
-                     sizeof(uint16_t) * kCompileWaves * p.k, s, d_runs, p, groups);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const int32_t most = (int32_t)(kMaxThreads / ((int64_t)groups * kCompileWaves * kWave));  // runs a launch: at least 4
+  for (int32_t run = 0; run < p.n_runs; run += most) {
+    const int32_t n = p.n_runs - run < most ? p.n_runs - run : most;
+    hipLaunchKernelGGL(k_compile, dim3((unsigned)n * groups), dim3(kCompileWaves * kWave),
+                       sizeof(uint16_t) * kCompileWaves * p.k, s, d_runs + run, p, groups);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   // length bins: (k - length) >> shift < kOrderBins for lengths 0 .. k
   int shift = 0;
   while ((p.k >> shift) >= kOrderBins) ++shift;

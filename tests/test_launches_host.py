@@ -60,3 +60,10 @@ gsgp.check(L.gsgp_get_semantics(h, 0, 0, P(DATA)), "semantics")
 """)
     threads = [g * b for k, g, b, _ in got if "k_fetch_semantics" in k]
     assert sum(threads) >= 8192 * 1_000_000 and max(threads) < 2**32
+
+
+def test_more_than_2_to_26_genomes(launches):
+    """17 pools of 2^22 trees: a wave a genome, over all runs."""
+    got = launches("handle([(64, 0, 1)] * 17, pop_size=4, pool_size=1 << 22, genome_len=1, n_generations_max=1)")
+    waves = [g * b // 64 for k, g, b, _ in got if "k_compile" in k]
+    assert sum(waves) >= 17 * (4 + (1 << 22)) and max(waves) * 64 < 2**32
