@@ -1261,11 +1261,11 @@ __device__ __forceinline__ void list_task(const ListArgs& a, int64_t task, Stack
   }
 }
 
-__global__ __launch_bounds__(256) void k_interpret_list(ListArgs a, int slots, int64_t total) {
+__global__ __launch_bounds__(256) void k_interpret_list(ListArgs a, int slots, int64_t task0, int64_t total) {
   extern __shared__ double lds[];
   const int lane = threadIdx.x & 63;
   const int wave = uni(threadIdx.x >> 6);
-  const int64_t task = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
+  const int64_t task = task0 + (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
   if (task >= total) return;
   double* stk = lds + wave * slots * kInterpV * kWave;
   list_task(a, task, (LdsStack)stk, lane);
@@ -1371,8 +1371,15 @@ hipError_t launch_interpret_list(const CompiledOp* ops, const int32_t* nops, int
   }
   const int waves = interp_waves(slots);
   const size_t shmem = (size_t)waves * slots * kInterpV * kWave * sizeof(double);
-  hipLaunchKernelGGL(k_interpret_list, dim3(blocks_for(total, waves)), dim3(waves * kWave), shmem, s, a, slots, total);
-  return hipGetLastError();
+  const int64_t most = kMaxThreads / (waves * kWave) * waves;  // tasks a launch
+  hipError_t e = hipSuccess;
+  for (int64_t task0 = 0; task0 < total && e == hipSuccess; task0 += most) {
+    const int64_t tasks = total - task0 < most ? total - task0 : most;
+    hipLaunchKernelGGL(k_interpret_list, dim3(blocks_for(tasks, waves)), dim3(waves * kWave), shmem, s, a, slots, task0,
+                       task0 + tasks);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 }  // namespace gsgp

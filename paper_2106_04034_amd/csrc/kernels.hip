@@ -2413,13 +2413,24 @@ hipError_t launch_replay_lineage(const ReplayNode* nodes, const int32_t* begin, 
   // one sweep of the threads per generation where a block may be that large
   const int64_t want = slots;
   const int threads = (int)(want > 1024 ? 1024 : (want + kWave - 1) / kWave * kWave);
-  const dim3 grid((unsigned)((n + c - 1) / c)), block(threads);
-  switch (c) {
-    case 4: launch_replay_lineage_as<4>(pool_lds, grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot, first, pool, ld, n, out); break;
-    case 2: launch_replay_lineage_as<2>(pool_lds, grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot, first, pool, ld, n, out); break;
-    default: launch_replay_lineage_as<1>(pool_lds, grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot, first, pool, ld, n, out); break;
+  const dim3 block(threads);
+  const int64_t most = kMaxThreads / threads * c;  // cases a launch
+  hipError_t e = hipSuccess;
+  for (int64_t c0 = 0; c0 < n && e == hipSuccess; c0 += most) {
+    const int64_t nc = n - c0 < most ? n - c0 : most;
+    const dim3 grid((unsigned)((nc + c - 1) / c));
+    auto go = [&](auto launch) {
+      launch(pool_lds, grid, block, shmem, s, nodes, begin, gen, n0, np, slots, out_slot, first + c0, pool + c0, ld, nc,
+             out + c0);
+    };
+    switch (c) {
+      case 4: go(launch_replay_lineage_as<4>); break;
+      case 2: go(launch_replay_lineage_as<2>); break;
+      default: go(launch_replay_lineage_as<1>); break;
+    }
+    e = hipGetLastError();
   }
-  return hipGetLastError();
+  return e;
 }
 
 hipError_t launch_replay_nodes(const ReplayNode* nodes, int32_t nnodes, const double* prev,

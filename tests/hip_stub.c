@@ -68,7 +68,7 @@ int hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t shmem, vo
     return last_error = 9; /* hipErrorInvalidConfiguration */
   const char* found = getenv("HIP_STUB_LINEAGE");
   if (found && strstr(name, "k_lineageI")) {
-    int32_t* sum = *(int32_t**)args[8];
+    int32_t* sum = *(int32_t**)args[9];
     sscanf(found, "%d %d %d %d", &sum[0], &sum[1], &sum[2], &sum[3]);
   }
   return 0;

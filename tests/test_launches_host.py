@@ -67,3 +67,26 @@ def test_more_than_2_to_26_genomes(launches):
     got = launches("handle([(64, 0, 1)] * 17, pop_size=4, pool_size=1 << 22, genome_len=1, n_generations_max=1)")
     waves = [g * b // 64 for k, g, b, _ in got if "k_compile" in k]
     assert sum(waves) >= 17 * (4 + (1 << 22)) and max(waves) * 64 < 2**32
+
+
+RECONSTRUCT = """
+h = handle([(100_000, 0, 2)], pop_size=1024, pool_size=1024, genome_len=15, n_generations_max={gen})
+gsgp.check(L.gsgp_generation(h, {gen}, None), "generation")
+size = ctypes.c_size_t(0)
+gsgp.check(L.gsgp_reconstruct_scratch_size(h, 0, {gen}, 0, {n}, ctypes.byref(size)), "size")
+gsgp.check(L.gsgp_reconstruct(h, 0, {gen}, 0, P(DATA), {n}, P(DATA), P(DATA), size.value), "reconstruct")
+"""
+
+
+def test_programs_of_a_lineage_on_many_cases(launches):
+    """1,500 programs on 6,000,000 cases: a wave a program and 128 cases."""
+    got = launches(RECONSTRUCT.format(gen=9, n=6_000_000), "600 500 1000 5000")
+    waves = [g * b // 64 for k, g, b, _ in got if "k_interpret_list" in k]
+    assert sum(waves) >= 1500 * 6_000_000 // 128 and max(waves) * 64 < 2**32
+
+
+def test_replay_of_a_small_lineage_on_many_cases(launches):
+    """Three rows on 300,000,000 cases: a wave for four cases."""
+    got = launches(RECONSTRUCT.format(gen=2, n=300_000_000), "3 3 4 5")
+    blocks = [(g, g * b) for k, g, b, _ in got if "k_replay_lineage" in k]
+    assert sum(g for g, _ in blocks) >= 300_000_000 // 4 and max(t for _, t in blocks) < 2**32
