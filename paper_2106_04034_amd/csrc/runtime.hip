@@ -291,9 +291,8 @@ gsgp_status hip_fail(gsgp_handle* h, hipError_t e, const char* what) {
     if (e_ != hipSuccess) return hip_fail(h, e_, #call); \
   } while (0)
 
-// The handle's device, current for as long as this lives (getters may be
-// called with another device current, and a NULL stream belongs to the
-// current one).
+// The handle's device, current for as long as this lives (calls may come with
+// another device current, and a NULL stream belongs to the current one).
 struct OnDevice {
   int before = -1;
   explicit OnDevice(const gsgp_handle* h) {
@@ -325,6 +324,7 @@ gsgp_status arm_guards(gsgp_handle* h) {
 // which poisons the handle and names the buffer it follows.
 gsgp_status check_guards(gsgp_handle* h, gsgp_status st) {
   if (st != GSGP_OK || h->plan.guards.empty()) return st;
+  const OnDevice here(h);
   HIPCHK(h, hipStreamSynchronize(h->stream));
   std::vector<uint32_t> got(kGuardBytes / 4);
   for (const Guard& g : h->plan.guards) {
@@ -740,6 +740,7 @@ gsgp_status gsgp_init(const gsgp_config* cfg, const gsgp_run* runs, int32_t n_ru
 
 gsgp_status gsgp_destroy(gsgp_handle* h) {
   if (!h) return GSGP_OK;
+  const OnDevice here(h);
   drop_graph(h);
   if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
   if (h->pinned) (void)hipHostFree(h->pinned);
@@ -797,6 +798,7 @@ hipError_t interpret_all(gsgp_handle* h, const int32_t (&counts)[kLists], hipStr
 gsgp_status eval_impl(gsgp_handle* h, const int32_t* h_codes, const double* h_consts, hipEvent_t* ev) {
   gsgp_status st = usable(h);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   if ((h_codes == nullptr) != (h_consts == nullptr)) return fail(GSGP_ERR_ARG, "give both codes and constants, or neither");
   const Params& p = h->params;
   const int64_t per = (int64_t)(p.m + p.r) * p.k;
@@ -859,6 +861,7 @@ static gsgp_status eval_population_body(gsgp_handle* h, const int32_t* h_codes, 
 static gsgp_status time_eval_body(gsgp_handle* h, double* h_ms) {
   gsgp_status st = usable(h);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   if (!h_ms) return fail(GSGP_ERR_ARG, "h_ms is NULL");
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   for (auto& e : ev) {
@@ -893,6 +896,7 @@ static gsgp_status time_eval_body(gsgp_handle* h, double* h_ms) {
 static gsgp_status generation_body(gsgp_handle* h, int32_t n_gens, gsgp_gen_stats* h_stats) {
   gsgp_status st = usable(h);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   if (!h->evaluated) return fail(GSGP_ERR_STATE, "gsgp_eval_population has not run");
   if (n_gens < 1) return fail(GSGP_ERR_ARG, "n_gens must be >= 1");
   if ((int64_t)h->gen + n_gens > h->cfg.n_generations_max)
@@ -908,6 +912,7 @@ static gsgp_status generation_replay_body(gsgp_handle* h, int32_t n_gens, const 
                                           const gsgp_gen_stats* h_elite, gsgp_gen_stats* h_stats) {
   gsgp_status st = usable(h);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   if (!h->evaluated) return fail(GSGP_ERR_STATE, "gsgp_eval_population has not run");
   if (n_gens < 1 || !h_records) return fail(GSGP_ERR_ARG, "need n_gens >= 1 and records");
   if ((int64_t)h->gen + n_gens > h->cfg.n_generations_max)
@@ -1011,6 +1016,7 @@ gsgp_status gsgp_get_records(gsgp_handle* h, int32_t run, int32_t gen0, int32_t 
                              gsgp_record* h_out) {
   gsgp_status st = check_run(h, run);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   if (!h_out || n_gens < 1 || gen0 < 1 || (int64_t)gen0 + n_gens - 1 > h->gen)
     return fail(GSGP_ERR_ARG, "records of generations %d..%d are not available (current %d)", gen0, gen0 + n_gens - 1, h->gen);
   HIPCHK(h, hipStreamSynchronize(h->stream));
@@ -1040,6 +1046,7 @@ gsgp_status gsgp_get_stats(gsgp_handle* h, int32_t run, int32_t gen0, int32_t n_
 gsgp_status gsgp_get_scaling(gsgp_handle* h, int32_t run, int32_t gen0, int32_t n_gens, double* h_out) {
   gsgp_status st = check_run(h, run);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   if (!h_out || n_gens < 1 || gen0 < 0 || (int64_t)gen0 + n_gens - 1 > h->gen)
     return fail(GSGP_ERR_ARG, "scaling of generations %d..%d is not available (current %d)", gen0, gen0 + n_gens - 1, h->gen);
   const int64_t m = h->cfg.pop_size;
@@ -1059,6 +1066,7 @@ gsgp_status gsgp_get_scaling(gsgp_handle* h, int32_t run, int32_t gen0, int32_t 
 gsgp_status gsgp_get_genomes(gsgp_handle* h, int32_t run, int32_t* h_codes, double* h_consts) {
   gsgp_status st = check_run(h, run);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   HIPCHK(h, hipStreamSynchronize(h->stream));
   const int64_t per = (int64_t)(h->cfg.pop_size + h->cfg.pool_size) * h->cfg.genome_len;
   if (h_codes) HIPCHK(h, hipMemcpy(h_codes, h->runs_h[run].code, 4 * per, hipMemcpyDeviceToHost));
@@ -1069,6 +1077,7 @@ gsgp_status gsgp_get_genomes(gsgp_handle* h, int32_t run, int32_t* h_codes, doub
 static gsgp_status time_stages_body(gsgp_handle* h, int32_t n_gens, double* h_ms) {
   gsgp_status st = usable(h);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   if (!h->evaluated) return fail(GSGP_ERR_STATE, "gsgp_eval_population has not run");
   if (!h_ms || n_gens < 1) return fail(GSGP_ERR_ARG, "need n_gens >= 1 and an output array");
   if ((int64_t)h->gen + n_gens > h->cfg.n_generations_max)
@@ -1128,6 +1137,7 @@ gsgp_status gsgp_set_launch(gsgp_handle* h, int32_t waves_per_block, int32_t off
                             int32_t max_blocks) {
   gsgp_status st = usable(h);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   const int32_t w = waves_per_block ? waves_per_block : h->vary.waves;
   const int32_t o = offspring_per_block ? offspring_per_block : h->vary.opb;
   if (w < 1 || w > 8) return fail(GSGP_ERR_ARG, "waves_per_block must be in [1, 8]");
@@ -1144,6 +1154,7 @@ gsgp_status gsgp_set_launch(gsgp_handle* h, int32_t waves_per_block, int32_t off
 static gsgp_status autotune_body(gsgp_handle* h, int32_t* h_best) {
   gsgp_status st = usable(h);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   if (!h->evaluated) return fail(GSGP_ERR_STATE, "gsgp_eval_population has not run");
   // the trial launches read the next generation's records
   if (h->gen >= h->cfg.n_generations_max)
@@ -1248,7 +1259,6 @@ gsgp_status walk_on_device(gsgp_handle* h, int32_t run, int32_t gen, int32_t ind
   int32_t* slots = (int32_t*)take(sizeof(int32_t) * lineage_slots(m, r, gen));
   L->d_nodes = (ReplayNode*)(at + off);
   if (off > bytes) return GSGP_OK;
-  const OnDevice here(h);
   LineageSummary* sum = (LineageSummary*)h->pinned;
   HIPCHK(h, launch_lineage(R, h->params, gen, individual, L->d_begin, L->d_tree0, L->d_pool, nodes ? slots : nullptr,
                            sum, h->stream));
@@ -1379,6 +1389,7 @@ gsgp_status gsgp_reconstruct_scratch_size(gsgp_handle* h, int32_t run, int32_t g
   if (gen < 0 || gen > h->gen) return fail(GSGP_ERR_ARG, "generation %d not in [0, %d]", gen, h->gen);
   if (individual < 0 || individual >= h->cfg.pop_size) return fail(GSGP_ERR_ARG, "individual out of range");
   if (n < 1 || n > ((int64_t)1 << 40)) return fail(GSGP_ERR_ARG, "n must be >= 1");
+  const OnDevice here(h);
   Lineage L;
   st = walk_lineage(h, run, gen, individual, n, false, &L);
   if (st != GSGP_OK) return st;
@@ -1390,6 +1401,7 @@ gsgp_status gsgp_export_linear(gsgp_handle* h, int32_t run, int32_t gen, int32_t
                                double* h_affine, double* h_weights) {
   gsgp_status st = check_run(h, run);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   if (gen < 0 || gen > h->gen) return fail(GSGP_ERR_ARG, "generation %d not in [0, %d]", gen, h->gen);
   if (individual < 0 || individual >= h->cfg.pop_size) return fail(GSGP_ERR_ARG, "individual out of range");
   if (!h_tree || !h_affine || !h_weights) return fail(GSGP_ERR_ARG, "NULL output pointer");
@@ -1470,6 +1482,7 @@ gsgp_status check_reconstruct_args(gsgp_handle* h, int32_t run, int32_t gen, int
 // `whose` names it in errors.
 gsgp_status reconstruct_with(gsgp_handle* h, int32_t run, int32_t gen, int32_t individual, const double* d_X,
                              int64_t n, double* d_out, char* sc, size_t scratch_bytes, const char* whose) {
+  const OnDevice here(h);
   Lineage L;
   gsgp_status st = walk_lineage(h, run, gen, individual, n, true, &L);
   if (st != GSGP_OK) return st;
@@ -1695,6 +1708,7 @@ gsgp_status gsgp_checkpoint_size(gsgp_handle* h, size_t* bytes) {
 gsgp_status gsgp_checkpoint_save(gsgp_handle* h, void* h_buf, size_t bytes) {
   gsgp_status st = usable(h);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   if (!h_buf) return fail(GSGP_ERR_ARG, "h_buf is NULL");
   if (!h->evaluated) return fail(GSGP_ERR_STATE, "gsgp_eval_population has not run");
   const std::vector<CkptPiece> pieces = ckpt_pieces(h);
@@ -1720,6 +1734,7 @@ gsgp_status gsgp_checkpoint_save(gsgp_handle* h, void* h_buf, size_t bytes) {
 gsgp_status gsgp_checkpoint_load(gsgp_handle* h, const void* h_buf, size_t bytes) {
   gsgp_status st = usable(h);
   if (st != GSGP_OK) return st;
+  const OnDevice here(h);
   if (!h_buf || bytes < sizeof(CkptHeader)) return fail(GSGP_ERR_ARG, "no checkpoint");
   CkptHeader c;
   std::memcpy(&c, h_buf, sizeof c);

@@ -90,3 +90,40 @@ def test_replay_of_a_small_lineage_on_many_cases(launches):
     got = launches(RECONSTRUCT.format(gen=2, n=300_000_000), "3 3 4 5")
     blocks = [(g, g * b) for k, g, b, _ in got if "k_replay_lineage" in k]
     assert sum(g for g, _ in blocks) >= 300_000_000 // 4 and max(t for _, t in blocks) < 2**32
+
+
+def test_every_launch_goes_to_the_handles_device(launches):
+    """A handle of device 0 with device 1 current, on the NULL stream, which
+    belongs to the current device."""
+    got = launches("""
+import numpy as np
+h = handle([(5_000, 100, 2)], pop_size=1024, pool_size=64, genome_len=15, n_generations_max=60)
+hip = ctypes.CDLL(None)
+hip.hipSetDevice(1)
+def call(name, *args):
+    gsgp.check(getattr(L, name)(h, *args), name)
+    d = ctypes.c_int(-1)
+    hip.hipGetDevice(ctypes.byref(d))
+    assert d.value == 1, name
+out, i4 = np.zeros(1 << 20), np.zeros(4, np.int32)
+p = P(out.ctypes.data)
+call("gsgp_eval_population", None, None)
+call("gsgp_time_eval", p)
+call("gsgp_generation", 20, p)
+rec = np.zeros((2, 1024), gsgp.RECORD_DTYPE)
+call("gsgp_generation_replay", 2, P(rec.ctypes.data), None, p)
+call("gsgp_time_stages", 2, p)
+call("gsgp_set_launch", 2, 8, 1, 0)
+call("gsgp_autotune", P(i4.ctypes.data))
+call("gsgp_get_fitness", 0, p, p)
+call("gsgp_get_semantics_rows", 0, 0, 0, 2, p)
+call("gsgp_get_stats", 0, 0, 5, p)
+size = ctypes.c_size_t(0)
+call("gsgp_reconstruct_scratch_size", 0, 20, 0, 100, ctypes.byref(size))
+call("gsgp_reconstruct", 0, 20, 0, P(DATA), 100, P(DATA), P(DATA), size.value)
+call("gsgp_reconstruct_static", 0, 20, 0, P(DATA), 100, P(DATA))
+blob = ctypes.create_string_buffer(1 << 28)
+call("gsgp_checkpoint_save", blob, 1 << 28)
+call("gsgp_checkpoint_load", blob, 1 << 28)
+""", "3 3 4 5")
+    assert len(got) > 30 and {k for k, _, _, device in got if device != 0} == set()
