@@ -543,7 +543,7 @@ gsgp_status fetch_semantics(gsgp_handle* h, int32_t run, int32_t which, int64_t 
     HIPCHK(h, hipStreamSynchronize(h->stream));
     if (mapped) memcpy(h_out, h->pinned, sizeof(double) * count);
   }
-  return GSGP_OK;
+  return check_guards(h, GSGP_OK);
 }
 
 }  // namespace
@@ -973,7 +973,7 @@ gsgp_status gsgp_get_fitness(gsgp_handle* h, int32_t run, double* h_train, doubl
     HIPCHK(h, hipStreamSynchronize(h->stream));
     if (h_train) memcpy(h_train, h->pinned, bytes);
     if (h_test) memcpy(h_test, (char*)h->pinned + bytes, bytes);
-    return GSGP_OK;
+    return check_guards(h, GSGP_OK);
   }
   HIPCHK(h, hipStreamSynchronize(h->stream));
   if (h_train) HIPCHK(h, hipMemcpy(h_train, R.F[cur], 8 * h->cfg.pop_size, hipMemcpyDeviceToHost));
@@ -1040,7 +1040,7 @@ gsgp_status gsgp_get_stats(gsgp_handle* h, int32_t run, int32_t gen0, int32_t n_
   if (st != GSGP_OK) return st;
   if (!h_out || n_gens < 1 || gen0 < 0 || (int64_t)gen0 + n_gens - 1 > h->gen)
     return fail(GSGP_ERR_ARG, "summaries of generations %d..%d are not available (current %d)", gen0, gen0 + n_gens - 1, h->gen);
-  return copy_stats(h, run, 1, gen0, n_gens, h_out);
+  return check_guards(h, copy_stats(h, run, 1, gen0, n_gens, h_out));
 }
 
 gsgp_status gsgp_get_scaling(gsgp_handle* h, int32_t run, int32_t gen0, int32_t n_gens, double* h_out) {
@@ -1394,7 +1394,7 @@ gsgp_status gsgp_reconstruct_scratch_size(gsgp_handle* h, int32_t run, int32_t g
   st = walk_lineage(h, run, gen, individual, n, false, &L);
   if (st != GSGP_OK) return st;
   *bytes = L.total;
-  return GSGP_OK;
+  return check_guards(h, GSGP_OK);
 }
 
 gsgp_status gsgp_export_linear(gsgp_handle* h, int32_t run, int32_t gen, int32_t individual, int32_t* h_tree,
@@ -1555,7 +1555,8 @@ gsgp_status gsgp_reconstruct(gsgp_handle* h, int32_t run, int32_t gen, int32_t i
   gsgp_status st = check_reconstruct_args(h, run, gen, individual, d_X, n, d_out);
   if (st != GSGP_OK) return st;
   if (!d_scratch || ((uintptr_t)d_scratch) % kAlign) return fail(GSGP_ERR_WORKSPACE, "scratch must be non-NULL and 256-byte aligned");
-  return reconstruct_with(h, run, gen, individual, d_X, n, d_out, (char*)d_scratch, scratch_bytes, "the scratch");
+  return check_guards(h, reconstruct_with(h, run, gen, individual, d_X, n, d_out, (char*)d_scratch, scratch_bytes,
+                                          "the scratch"));
 }
 
 gsgp_status gsgp_reconstruct_static(gsgp_handle* h, int32_t run, int32_t gen, int32_t individual, const double* d_X,
@@ -1565,14 +1566,12 @@ gsgp_status gsgp_reconstruct_static(gsgp_handle* h, int32_t run, int32_t gen, in
   if (h->device < 0 || h->device >= kMaxDevices || !g_static[h->device].ptr)
     return fail(GSGP_ERR_UNSUPPORTED, "no static scratch on device %d", h->device);
   std::lock_guard<std::mutex> lock(g_static[h->device].call);
-  return reconstruct_with(h, run, gen, individual, d_X, n, d_out, g_static[h->device].ptr, kStaticScratchBytes,
-                          "the static scratch");
+  return check_guards(h, reconstruct_with(h, run, gen, individual, d_X, n, d_out, g_static[h->device].ptr,
+                                          kStaticScratchBytes, "the static scratch"));
 }
 
-
-
-// The entry points that launch kernels check the workspace guards
-// (GSGP_FLAG_GUARDS) before returning.
+// The entry points that launch kernels, getters and reconstruction among them,
+// check the workspace guards (GSGP_FLAG_GUARDS) before returning.
 gsgp_status gsgp_eval_population(gsgp_handle* h, const int32_t* h_codes, const double* h_consts) {
   return check_guards(h, eval_population_body(h, h_codes, h_consts));
 }
