@@ -35,15 +35,16 @@ constexpr int32_t kOpEnd = 2;
 // two Newton-Raphson steps, a quotient, and one correction by its residual,
 // all with FMA, inside an operand range scaling and a special-case fix-up.
 // When |b| lies in [1e-6, 2^128], |a| >= 2^-700 and the quotient is at most
-// 2^127 in magnitude, no operand, reciprocal or quotient comes near either
-// end of the exponent range, so the scaling and the fix-up leave every value
-// as it is and the core steps alone (div_recip, div_short) give the same
-// bits.  The reciprocal depends on b alone: for a constant divisor the
-// compile step refines it once.
+// FLT_MAX in magnitude (where nothing is clamped), |a| is at most 2^256: no
+// operand, reciprocal or quotient comes near either end of the exponent range
+// and no two exponents are far apart, so the scaling and the fix-up leave every
+// value as it is and the core steps alone (div_recip, div_short) give the same
+// bits.  The reciprocal depends on b alone: a constant divisor's is refined once
+// for all of a wave's cases, each time the op runs.
 constexpr double kDivShortMinDivisor = 1e-6;
 constexpr double kDivShortMaxDivisor = 0x1p128;
 constexpr double kDivShortMinDividend = 0x1p-700;
-constexpr double kDivShortMaxQuotient = 0x1p127;
+constexpr double kDivShortMaxQuotient = kFltMax;
 
 __device__ __forceinline__ double div_recip(double b) {
   double y = __builtin_amdgcn_rcp(b);
@@ -541,7 +542,7 @@ __device__ __forceinline__ void eval_program_wide(const CompiledOp* ops, const d
   };
   // The short division (div_short): taken when every case of the wave has
   // |b| >= 1e-6 (with y its reciprocal refinement), |tos| >= 2^-700 and a
-  // quotient of at most 2^127, where it gives the bits of the full one.
+  // quotient of at most FLT_MAX, where it gives the bits of the full one.
   auto divide = [&](const double (&b)[V], const double (&y)[V], uint64_t bad) {
     double q[V];
 #pragma unroll
@@ -1005,15 +1006,14 @@ __device__ __forceinline__ StoreSpan<T> store_span(const RunDev& R, const Params
 }
 
 // The logistic function 1 / (1 + e^-v) of a wave's values, by the short
-// division where every one allows it (1 + e^-v is at least 1, and below 2^127
-// neither it nor the quotient is near the ends of the exponent range).
+// division where every divisor is within its limits (1 + e^-v is at least 1).
 template <int V>
 __device__ __forceinline__ void squash(double (&x)[V]) {
   uint64_t far = 0;
 #pragma unroll
   for (int v = 0; v < V; ++v) {
     x[v] = 1.0 + exp(-x[v]);
-    far |= __builtin_amdgcn_ballot_w64(!(x[v] <= kDivShortMaxQuotient));
+    far |= __builtin_amdgcn_ballot_w64(!(x[v] <= kDivShortMaxDivisor));
   }
   if (far) {
 #pragma unroll
