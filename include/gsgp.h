@@ -21,6 +21,8 @@
  *  - All device work is enqueued on the HIP stream given to gsgp_init (NULL
  *    is the legacy default stream).  Calls that return host data (getters,
  *    h_stats != NULL) synchronise that stream.  A handle is not thread safe.
+ *    A handle belongs to the device that is current at gsgp_init; its calls
+ *    make that device current and restore the caller's.
  *  - After a HIP error the handle is poisoned: later calls return
  *    GSGP_ERR_STATE until gsgp_destroy.
  *  - gsgp_last_error() returns a thread-local message for the last failure.
@@ -62,7 +64,7 @@ typedef enum {
 typedef enum { GSGP_FP64 = 0, GSGP_FP32 = 1, GSGP_FP32_KAHAN = 2 } gsgp_precision;
 
 /* gsgp_config.flags */
-#define GSGP_FLAG_NO_GRAPH 1u  /* launch generations one by one, no HIP graph */
+#define GSGP_FLAG_NO_GRAPH 1u  /* launch every kernel by itself, no HIP graph */
 #define GSGP_FLAG_GUARDS 2u    /* debug: a 256-byte guard pattern after every workspace
                                   buffer (gsgp_workspace_size grows accordingly), checked
                                   after every call that launches kernels; an overwritten
@@ -144,7 +146,9 @@ typedef struct gsgp_handle gsgp_handle;
 
 /* Bytes of device workspace gsgp_init needs for these runs (Section 2.3's
  * memory complexity: O(mk + rk + 2mn + rn + nl), plus the ancestry record of
- * n_generations_max generations).  Pure host computation.
+ * n_generations_max generations and the chunk sums: 8 bytes per individual and
+ * 2 KiB of a semantic row, three times with local search, 7 or 15 times with
+ * tournament_size 0 for the generations of a block).  Pure host computation.
  * Errors: GSGP_ERR_ARG for an invalid config or run description. */
 gsgp_status gsgp_workspace_size(const gsgp_config* cfg, const gsgp_run* runs, int32_t n_runs,
                                 size_t* bytes);
@@ -180,10 +184,13 @@ gsgp_status gsgp_eval_population(gsgp_handle* h, const int32_t* h_codes, const d
 /* Algorithm 1's loop body, n_gens times: variation draws (tournaments),
  * GSM/GSC on train and test semantics, ComputeFitness, survival with
  * elitism (Section 2.2).  h_stats (HOST, nullable) receives
- * [n_runs][n_gens] summaries and synchronises the stream.  Unless
- * GSGP_FLAG_NO_GRAPH is set, one generation and a block of 16 generations
- * are each captured once in a HIP graph and replayed (16 at a time, then one
- * at a time for the rest).
+ * [n_runs][n_gens] summaries and synchronises the stream.  With
+ * tournament_size 0 (without local search, up to 65,536 individuals) a call
+ * for three generations or more runs them in blocks of up to 7 or 15, which
+ * take half of the time of single ones or less; the results are the same.
+ * Unless GSGP_FLAG_NO_GRAPH is set, what repeats is captured in a HIP graph the
+ * first time a call needs it, and replayed: 16 generations, one generation, a
+ * whole block.
  * Errors: GSGP_ERR_ARG (n_gens < 1 or beyond n_generations_max),
  * GSGP_ERR_STATE (before gsgp_eval_population), GSGP_ERR_HIP. */
 gsgp_status gsgp_generation(gsgp_handle* h, int32_t n_gens, gsgp_gen_stats* h_stats);
@@ -231,8 +238,8 @@ gsgp_status gsgp_reconstruct(gsgp_handle* h, int32_t run, int32_t gen, int32_t i
  * for the life of the process, instead of caller scratch.  The caller still
  * passes d_X and d_out (DEVICE).  The call makes no device allocation.  A
  * reconstruction that needs more scratch than the array holds (see
- * gsgp_reconstruct_scratch_size) is refused with GSGP_ERR_WORKSPACE before
- * any device work.  All calls on one GPU share its array, which keeps the
+ * gsgp_reconstruct_scratch_size) is refused with GSGP_ERR_WORKSPACE once the
+ * ancestry has been walked, which reads the record and changes no state.  All calls on one GPU share its array, which keeps the
  * last call's contents (every byte a call reads it has written first): the
  * library serialises such calls within a process with a lock, and the call
  * returns only after its work is done (it synchronises the stream).  Work on
@@ -331,7 +338,9 @@ gsgp_status gsgp_get_genomes(gsgp_handle* h, int32_t run, int32_t* h_codes, doub
 /* Runs n_gens generations without a graph, timing every stage with HIP
  * events on the library stream, and writes the mean milliseconds per launch
  * to h_ms[0..3]: selection+survival, variation (GSM/GSC + fitness partials),
- * fitness combination, and the whole generation.  Advances the runs. */
+ * fitness combination, and the whole generation.  Advances the runs.  The
+ * generations are single ones, also with tournament_size 0, where
+ * gsgp_generation runs blocks of them. */
 gsgp_status gsgp_time_stages(gsgp_handle* h, int32_t n_gens, double* h_ms);
 
 /* Runs gsgp_eval_population (Philox genomes) with HIP events between its
@@ -347,15 +356,18 @@ gsgp_status gsgp_time_eval(gsgp_handle* h, double* h_ms);
  * offspring per block task (0 keeps the current value for either), XCD-aware
  * block order (0 none; 1 each XCD takes a contiguous range of tasks; 2 the
  * XCDs take neighbouring case chunks side by side), and max_blocks (0 = one block per task; > 0 = a
- * persistent grid of at most that many blocks looping over tasks).  Shapes
- * never change results: partial sums follow a fixed chunking of the cases.
+ * persistent grid of at most that many blocks looping over tasks).  Blocks of
+ * generations (tournament_size 0) use waves, offspring and whether the order is
+ * XCD-aware; those that go slice by slice of the pool have a shape of their
+ * own.  Shapes never change results: partial sums follow a fixed chunking of the cases.
  * Errors: GSGP_ERR_ARG. */
 gsgp_status gsgp_set_launch(gsgp_handle* h, int32_t waves_per_block, int32_t offspring_per_block,
                             int32_t xcd_remap, int32_t max_blocks);
 
 /* Times candidate launch shapes of the variation kernel on the live buffers
  * (the kernel is idempotent within a generation, so the runs do not
- * advance) and keeps the fastest.  h_best (HOST, nullable) receives
+ * advance) and keeps the fastest for single generations (which are not what
+ * gsgp_generation mostly runs with tournament_size 0).  h_best (HOST, nullable) receives
  * {waves_per_block, offspring_per_block, xcd_remap, max_blocks}.
  * Errors: GSGP_ERR_STATE (also when no generation is left to run),
  * GSGP_ERR_HIP. */
