@@ -340,12 +340,11 @@ __global__ __launch_bounds__(1024) void k_order(const RunDev* __restrict__ runs,
 
 // Evaluate one compiled program on V cases per lane (Section 2.2
 // "Interpreter").  The op stream is wave-uniform and read with scalar loads,
-// eight ops per batch in one load of words and one of constants.  Stack
-// element i of depth d (0 = bottom) lives in
-// registers for the top two (tos = d-1, nos = d-2) and in LDS below them,
-// at stk[(i * V + v) * 64 + lane]; a function of the top two values reads
-// its new second operand from LDS only after it has produced its result, so
-// the LDS latency falls outside the op's dependency chain.  A fused op (a
+// eight ops (two 64-byte lines) a batch.  Stack element i of depth d (0 =
+// bottom) lives in registers for the top two (tos = d-1, nos = d-2) and in LDS
+// below them, at stk[(i * V + v) * 64 + lane]; a function of the top two values
+// reads its new second operand from LDS only after it has produced its result,
+// so the LDS latency falls outside the op's dependency chain.  A fused op (a
 // push the next function consumes) applies the function to tos and the
 // terminal and touches neither nos nor LDS.  The value of the program is the
 // output of its last function (the Out register), 0.0 if none runs.
@@ -382,8 +381,8 @@ __device__ __forceinline__ void eval_program(const CompiledOp* ops, int n, const
     double cv[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      // one contiguous batch (two scalar loads); the last batch of a program
-      // may read up to kBatch - 1 words past it, which the buffers' padding
+      // one contiguous batch (two 64-byte lines); the last batch of a program
+      // may read up to kBatch - 1 ops past it, which the buffer's padding
       // after the last program keeps in bounds, and never uses them
       wv[u] = cops[j0 + u].word;
       cv[u] = cops[j0 + u].value;
@@ -587,7 +586,7 @@ __device__ __forceinline__ void eval_program_wide(const CompiledOp* ops, const d
     double cv[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      // one batch per two scalar loads; reads past a program's end word
+      // one batch is two 64-byte lines; reads past a program's end word
       // stay inside the buffer's padding and are never used
       wv[u] = cops[j0 + u].word;
       cv[u] = cops[j0 + u].value;

@@ -823,23 +823,18 @@ __global__ __launch_bounds__(256) void k_target_sums(const RunDev* __restrict__ 
 
 // ---------------------------------------------------------------------------
 // Survival, summary and the next generation's variation draws.
-template <bool MAX, typename View>
-__device__ ValIdx block_arg(int m, View F, ValIdx* sh) {
+// The best of m individuals, by all threads of a block.
+template <typename View>
+__device__ ValIdx block_min(int m, View F, ValIdx* sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  ValIdx x{MAX ? -INFINITY : INFINITY, 0x7fffffff};
-  for (int i = threadIdx.x; i < m; i += blockDim.x) {
-    const ValIdx y{F(i), i};
-    x = MAX ? pick_max(x, y) : pick_min(x, y);
-  }
+  ValIdx x{INFINITY, 0x7fffffff};
+  for (int i = threadIdx.x; i < m; i += blockDim.x) x = pick_min(x, ValIdx{F(i), i});
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const ValIdx y{__shfl_xor(x.v, o, kWave), __shfl_xor(x.i, o, kWave)};
-    x = MAX ? pick_max(x, y) : pick_min(x, y);
-  }
+  for (int o = 32; o >= 1; o >>= 1) x = pick_min(x, ValIdx{__shfl_xor(x.v, o, kWave), __shfl_xor(x.i, o, kWave)});
   if (lane == 0) sh[wave] = x;
   __syncthreads();
   ValIdx r = sh[0];
-  for (int w = 1; w < nw; ++w) r = MAX ? pick_max(r, sh[w]) : pick_min(r, sh[w]);
+  for (int w = 1; w < nw; ++w) r = pick_min(r, sh[w]);
   __syncthreads();
   if (r.i < 0 || r.i >= m) r.i = 0;  // fitness is always finite; keep indices in range regardless
   return r;
@@ -1112,7 +1107,7 @@ __global__ __launch_bounds__(256) void k_survive(const RunDev* __restrict__ runs
     ValIdx b = bo;
     if (gen_mode) {
       if (replay_elite) {
-        b = block_arg<false>(m, view_new, sh);
+        b = block_min(m, view_new, sh);
       } else if (copied) {
         // an elite copy is strictly better than every offspring
         b = ValIdx{f_src, dst};
@@ -1245,51 +1240,51 @@ __device__ __forceinline__ void mutate_block_one(const RunDev& R, const Params& 
     ok[j] = FULL || e < len;
     t[j] = ok[j] ? gload<VT>(yv + e) : VT(0);
   }
-      VT x[NJ];
-  #pragma unroll
-      for (int j = 0; j < NJ; ++j) x[j] = ok[j] ? gload<VT>(Sc + (int64_t)i * len + j * kWave * N + lane * N) : VT(0);
-      // a step's pool rows are read while the step before is worked on
-      auto read = [&](int s, T& ms, VT (&a)[NJ], VT (&b)[NJ]) {
-        const gsgp_record* rc = R.rec + (int64_t)(gen + s) * p.m + i;
-        const T* A = gc + (int64_t)uni(cload(&rc->r1)) * len;
-        const T* B = gc + (int64_t)uni(cload(&rc->r2)) * len;
-        ms = (T)cload(&rc->ms);
-  #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          const int e = j * kWave * N + lane * N;
-          a[j] = ok[j] ? gload<VT>(A + e) : VT(0);
-          b[j] = ok[j] ? gload<VT>(B + e) : VT(0);
-        }
-      };
-      auto step = [&](int s, T ms, const VT (&a)[NJ], const VT (&b)[NJ]) {
-        LaneSse<T, PREC> acc;
-  #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          VT v = x[j] + ms * (a[j] - b[j]);
-          if constexpr (PREC != GSGP_FP64) {
-  #pragma unroll
-            for (int c = 0; c < N; ++c) v[c] = __builtin_amdgcn_fmed3f(v[c], (T)-kFltMax, (T)kFltMax);
-          }
-          x[j] = v;
-          if (ok[j]) acc.add(v, t[j]);
-        }
-        const double sse = sse_finish<T, PREC, NJ>(acc, ok, x, yv, lane);
-        if (lane == 0) R.part[((int64_t)s * R.nch + chunk) * p.m + i] = sse;
-      };
-      T ms0, ms1;
-      VT a0[NJ], b0[NJ], a1[NJ], b1[NJ];
-      read(0, ms0, a0, b0);
-      for (int s = 0;;) {
-        if (s + 1 < gens) read(s + 1, ms1, a1, b1);
-        step(s, ms0, a0, b0);
-        if (++s >= gens) break;
-        if (s + 1 < gens) read(s + 1, ms0, a0, b0);
-        step(s, ms1, a1, b1);
-        if (++s >= gens) break;
+  VT x[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) x[j] = ok[j] ? gload<VT>(Sc + (int64_t)i * len + j * kWave * N + lane * N) : VT(0);
+  // a step's pool rows are read while the step before is worked on
+  auto read = [&](int s, T& ms, VT (&a)[NJ], VT (&b)[NJ]) {
+    const gsgp_record* rc = R.rec + (int64_t)(gen + s) * p.m + i;
+    const T* A = gc + (int64_t)uni(cload(&rc->r1)) * len;
+    const T* B = gc + (int64_t)uni(cload(&rc->r2)) * len;
+    ms = (T)cload(&rc->ms);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int e = j * kWave * N + lane * N;
+      a[j] = ok[j] ? gload<VT>(A + e) : VT(0);
+      b[j] = ok[j] ? gload<VT>(B + e) : VT(0);
+    }
+  };
+  auto step = [&](int s, T ms, const VT (&a)[NJ], const VT (&b)[NJ]) {
+    LaneSse<T, PREC> acc;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      VT v = x[j] + ms * (a[j] - b[j]);
+      if constexpr (PREC != GSGP_FP64) {
+#pragma unroll
+        for (int c = 0; c < N; ++c) v[c] = __builtin_amdgcn_fmed3f(v[c], (T)-kFltMax, (T)kFltMax);
       }
-  #pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        if (ok[j]) gstore_nt<VT>(x[j], Oc + (int64_t)i * len + j * kWave * N + lane * N);
+      x[j] = v;
+      if (ok[j]) acc.add(v, t[j]);
+    }
+    const double sse = sse_finish<T, PREC, NJ>(acc, ok, x, yv, lane);
+    if (lane == 0) R.part[((int64_t)s * R.nch + chunk) * p.m + i] = sse;
+  };
+  T ms0, ms1;
+  VT a0[NJ], b0[NJ], a1[NJ], b1[NJ];
+  read(0, ms0, a0, b0);
+  for (int s = 0;;) {
+    if (s + 1 < gens) read(s + 1, ms1, a1, b1);
+    step(s, ms0, a0, b0);
+    if (++s >= gens) break;
+    if (s + 1 < gens) read(s + 1, ms0, a0, b0);
+    step(s, ms1, a1, b1);
+    if (++s >= gens) break;
+  }
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+    if (ok[j]) gstore_nt<VT>(x[j], Oc + (int64_t)i * len + j * kWave * N + lane * N);
 }
 
 template <typename T, int PREC, bool FULL>

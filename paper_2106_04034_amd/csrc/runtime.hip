@@ -459,7 +459,7 @@ gsgp_status run_generations(gsgp_handle* h, int32_t n_gens, bool free_run) {
   const bool graph = !(h->cfg.flags & GSGP_FLAG_NO_GRAPH);
   int32_t left = n_gens;
   // without selection: whole blocks, then an odd number (a block ends in the
-  // other population buffer), at most one generation by itself
+  // other population buffer), and one or two generations by themselves
   const int32_t most = h->plan.block_gens;
   while (free_run && most && left >= 3) {
     const int32_t gens = std::min(most, left - (left % 2 == 0 ? 1 : 0));
