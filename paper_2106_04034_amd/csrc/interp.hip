@@ -488,11 +488,11 @@ __device__ __forceinline__ void eval_program(const CompiledOp* ops, int n, const
 //     column is what bounds the resident waves of the deeper lists).
 // The FP64 operations and their order are those of eval_program, so results
 // are the same bits.
-template <int V, int REG, typename Stack>
+template <int V, int REG, int BATCH = kOpPad, typename Stack>
 __device__ __forceinline__ void eval_program_wide(const CompiledOp* ops, const double* X, bool short_feature_div,
                                                   const uint32_t (&off)[V], Stack stk, int lane, double (&out)[V]) {
   static_assert(REG == 0 || REG == 1, "two or three stack values in registers");
-  constexpr int kBatch = kOpPad;
+  constexpr int kBatch = BATCH;
   const GSGP_CONST CompiledOp* cops = (const GSGP_CONST CompiledOp*)ops;
   double tos[V], nos[V], n2[V];
 #pragma unroll
@@ -586,8 +586,8 @@ __device__ __forceinline__ void eval_program_wide(const CompiledOp* ops, const d
     double cv[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      // one batch is two 64-byte lines; reads past a program's end word
-      // stay inside the buffer's padding and are never used
+      // a batch of eight is two 64-byte lines; reads past a program's end
+      // word stay inside the buffer's padding and are never used
       wv[u] = cops[j0 + u].word;
       cv[u] = cops[j0 + u].value;
     }
@@ -1107,7 +1107,10 @@ __global__ __launch_bounds__(256) void k_interpret(const RunDev* __restrict__ ru
 // features, us: all features 0 or 1 3,718 -> 2,481, three of them 2,928 -> 2,156;
 // without the threaded code 2,759 and 2,452.  Of features in [-1, 1] 1,795 -> 1,754.
 // The checked evaluator keeps two stack values in registers where the column
-// holds the rest, else three: 6 % faster than three always (fewer copies).
+// holds the rest, else three: 6 % faster than three always (fewer copies).  The
+// second form reads two ops at a time, a quarter of the code: with both unrolled
+// eight times the kernel came to 112 KB, close to what a branch can span (128 KB;
+// 90 KB now), and beyond it without the optimisations of the normal build.
 constexpr int32_t kGivenUpLeast = 1024;
 constexpr int32_t kGivenUpShare = 4;
 constexpr int32_t kStopThreaded = 1 << 30;
@@ -1177,7 +1180,7 @@ __global__ __launch_bounds__(kWave, 7) void k_interpret_wide(const RunDev* __res
     if (uni(cload(&R.need[prog])) <= slots)
       eval_program_wide<V, 0>(ops, X, uni(R.x_big) == 0, off, (LdsStack)lds, lane, out);
     else
-      eval_program_wide<V, REG>(ops, X, uni(R.x_big) == 0, off, (LdsStack)lds, lane, out);
+      eval_program_wide<V, REG, 2>(ops, X, uni(R.x_big) == 0, off, (LdsStack)lds, lane, out);
     store(prog, out);
   }
 }
