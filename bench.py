@@ -152,7 +152,7 @@ def interpreter_rate_rows(codes: np.ndarray, n_cases: np.ndarray, ms: float) -> 
             "note": "one gene-step is one push or one valid function on one case; feature_bytes are the FP64 "
                     "feature values those steps read (8 bytes per feature push per case), which come from L2 "
                     "through each CU's vector memory path; the interpreter's counters show the vector ALU "
-                    "busy 79 % of the time"}
+                    "busy 86 % of the time"}
 
 
 def traffic_from_profile(path: str):

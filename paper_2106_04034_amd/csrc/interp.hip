@@ -718,12 +718,13 @@ done:
 //     exceeds 2^128.
 // The operations and their order are those of eval_program_wide (a - c is
 // compiled as a + (-c)), so results are the same bits.  Every load is waited
-// for inside the block.  What bounds it now is the vector unit (82 % busy; 324
+// for inside the block.  What bounds it now is the vector unit (86 % busy; 324
 // of about 500 instructions a program of 127 genes are its ops).  Whole
-// interpretation, compiled form -> this: 2,048 programs of 127 genes on 125,000
-// cases 1.94 -> 1.61 ms, 1,250,000 cases 17.3 -> 14.6 ms, 20,480 on 102,400 cases x
-// 1,024 features 14.6 -> 12.4 ms, 64 runs 2.89 -> 2.51 ms, 256 programs on 700
-// cases 80 -> 54 us (one launch for all lists).  Handlers that load each feature
+// interpretation, compiled form -> this -> with the launches and the padding of
+// now: 2,048 programs of 127 genes on 125,000 cases 1.94 -> 1.61 -> 1.33 ms,
+// 1,250,000 cases 17.3 -> 14.6 -> 14.5 ms, 20,480 on 102,400 cases x 1,024 features
+// 14.6 -> 12.4 -> 12.3 ms, 64 runs 2.89 -> 2.51 -> 2.0 ms, 256 programs on 700
+// cases 80 -> 54 -> 29 us (one launch for all lists).  Handlers that load each feature
 // where they use it were within 3 % either way (20 features 2 % slower, 1,024
 // features 3 % faster).
 //
